@@ -13,7 +13,8 @@ A case is a dict of plain values; ``kind`` names the workload:
 ``listed()`` holds the fixed cases, ``draw(rng)`` makes one more of the same ranges.  ``prepare(case, seed)``
 builds what a program has in hand before the call (all on the GPU), ``run(state)`` makes one pass through the
 public entry points of ``paper_1810_01993_amd.api`` and returns its outputs, ``work(case)`` counts the bytes and
-operations such a pass cannot do without, ``tolerance(case)`` says how far a correct result may be off.
+operations such a pass cannot do without, ``tolerance(case)`` says how far a correct result may be off,
+``exact(case, seed)`` gives the outputs of a first pass as plain 64-bit torch computes them.
 """
 from __future__ import annotations
 
@@ -351,3 +352,98 @@ def tolerance(case):
     if case["kind"] in ("block", "head"):
         return {"rel": 1e-2, "max": 0.3} if case["dtype"] == "bf16" else {"rel": 1.2e-3, "max": 0.05}
     return {"rel": 7e-3, "max": 0.016} if case["dtype"] == "bf16" else {"rel": 8e-4, "max": 2e-3}
+
+
+# ---- the same in 64 bits ----------------------------------------------------------
+def _taps(H, W, P, Q, R, stride, pad, dil):
+    """(r, s, rows, columns): the part of the zero-padded image that filter tap (r, s) meets, as slices."""
+    cut = lambda t, n: slice(t * dil, t * dil + (n - 1) * stride + 1, stride)                       # noqa: E731
+    return [(r, s, cut(r, P), cut(s, Q)) for r in range(R) for s in range(R)]
+
+
+def _conv64(d, x, w, dy):
+    """float64 (y, dx, dw) of the convolution d, tap by tap; what needs a missing operand is None."""
+    P, Q = _extent(d.H, d.R, d.stride_h, d.pad_h, d.dil_h), _extent(d.W, d.S, d.stride_w, d.pad_w, d.dil_w)
+    p = d.pad_h
+    xp = None if x is None else F.pad(x.double(), (0, 0, p, p, p, p))
+    g = None if dy is None else dy.double().reshape(-1, d.K)
+    y = torch.zeros((d.N * P * Q, d.K), dtype=torch.float64, device="cuda") if x is not None and w is not None else None
+    dxp = torch.zeros((d.N, d.H + 2 * p, d.W + 2 * p, d.C), dtype=torch.float64, device="cuda") if g is not None and w is not None else None
+    dw = torch.zeros((d.K, d.R, d.S, d.C), dtype=torch.float64, device="cuda") if g is not None and x is not None else None
+    for r, s, rows, cols in _taps(d.H, d.W, P, Q, d.R, d.stride_h, p, d.dil_h):
+        xt = None if xp is None else xp[:, rows, cols].reshape(-1, d.C)
+        wt = None if w is None else w[:, r, s].double().contiguous()
+        if y is not None:
+            y += xt @ wt.t()
+        if dxp is not None:
+            dxp[:, rows, cols] += (g @ wt).view(d.N, P, Q, d.C)
+        if dw is not None:
+            dw[:, r, s] = g.t() @ xt
+    return (None if y is None else y.view(d.N, P, Q, d.K),
+            None if dxp is None else dxp[:, p:p + d.H, p:p + d.W].contiguous(), dw)
+
+
+def _block64(s, c):
+    (d1, d2, d3), (w1, w2, w3), b = s["descs"], s["w"], [t.double() for t in s["b"]]
+    a = (_conv64(d1, s["x"], w1, None)[0] + b[0]).clamp_(min=0)
+    a = (_conv64(d2, a, w2, None)[0] + b[1]).clamp_(min=0)
+    y = (_conv64(d3, a, w3, None)[0] + b[2] + s["x"].double()).clamp_(min=0)
+    if not c["train"]:
+        return y
+    px, p1, p2, py = s["kept"]
+    total = lambda t: t.reshape(-1, t.shape[-1]).sum(0)                                             # noqa: E731
+    dz3 = s["dy"].double() * (py > 0)
+    _, da2, dw3 = _conv64(d3, p2, w3, dz3)
+    dz2 = da2 * (p2 > 0)
+    _, da1, dw2 = _conv64(d2, p1, w2, dz2)
+    dz1 = da1 * (p1 > 0)
+    _, dx, dw1 = _conv64(d1, px, w1, dz1)
+    return y, dz3, dx, dw1, dw2, dw3, total(dz1), total(dz2), total(dz3)
+
+
+def _head64(s, c):
+    n, C = c["N"] * c["H"] * c["W"], c["C"]
+    x, w, lab = s["x"].double().view(n, C), s["w"].double().view(3, C), s["labels"].view(n).long()
+    z = x @ w.t()
+    weight = (s["cw"].double()[lab] if s["map"] is None else s["map"].double().view(n)) * s["scale"]
+    lse = torch.logsumexp(z, 1)
+    loss = (weight * (lse - z.gather(1, lab[:, None])[:, 0])).sum().view(1)
+    dz = ((z - lse[:, None]).exp() - F.one_hot(lab, 3)) * weight[:, None]
+    dx, dw = dz @ w, dz.t() @ x
+    if c["fused"]:
+        return z, loss, dz, dx.view(s["x"].shape), dw.view(s["w"].shape)
+    z, dz = (t.view(c["N"], c["H"], c["W"], 3) for t in (z, dz))
+    return z, loss, dz, dx.view(s["x"].shape), dw.view(s["w"].shape)
+
+
+def _update64(s, c):
+    lr, trust, decay, momentum = 0.01, 0.001, 1e-4, 0.9 if c["momentum"] else 0.0
+    ws, vs, rates = [], [], []
+    for i, (w, g) in enumerate(zip(s["w"], s["g"])):
+        w, g = w.double(), g.double()
+        local = trust * w.norm() / (g.norm() + decay * w.norm())
+        rate = torch.clamp(local, max=lr)
+        v = rate * (g + decay * w)
+        if c["momentum"]:
+            v = v + momentum * s["v"][i].double()
+        ws.append(w - v)
+        vs.append(v)
+        rates.append(rate)
+    return torch.cat(ws), torch.cat(vs) if c["momentum"] else None, torch.stack(rates)
+
+
+def exact(case, seed):
+    c, s = case, prepare(case, seed)
+    kind = c["kind"]
+    if kind == "conv":
+        return _conv64(s["desc"], s["x"], s["w"], s["dy"])
+    if kind == "block":
+        return _block64(s, c)
+    if kind == "aspp":
+        return [t for d, x, w, dy in s["layers"] for t in _conv64(d, x, w, dy)]
+    if kind == "head":
+        return _head64(s, c)
+    if kind == "upsample":
+        y, dx, _ = _conv64(s["desc"], s["dy"], s["w"], s["x"])
+        return dx, y, _conv64(s["desc"], s["dy"], None, s["x"])[2]
+    return _update64(s, c)
