@@ -50,6 +50,16 @@ def test_mask_and_bias_gradient(api, n, K, dtype):
     _run(api, n, K, dtype, synth.seed_for(0, 1500 + (n * 7 + K) % 91))
 
 
+# column blocks with a ragged last one (8-channel groups and odd counts), slabs that end inside the run of four pixels,
+# the change from four to eight pixels per thread and the limit of 1024 partial rows
+EDGES = [(7, 264), (31, 520), (4097, 1024), (131, 257), (65, 511), (262145, 8), (131073, 24), (32801, 256)]
+
+
+@pytest.mark.parametrize("n,K", EDGES, ids=[f"{n}x{K}" for n, K in EDGES])
+def test_column_blocks_and_slab_edges(api, n, K):
+    _run(api, n, K, "f16", synth.seed_for(0, 1540 + (n + K) % 37))
+
+
 def test_without_relu_in_place_and_repeatable(api):
     _run(api, 3001, 72, "f16", synth.seed_for(0, 1590), relu=False)
     a = _run(api, 3001, 72, "bf16", synth.seed_for(0, 1591), alias=True)
