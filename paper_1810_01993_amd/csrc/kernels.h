@@ -263,6 +263,7 @@ constexpr int LARC_MAX = 64, LARC_SLICES = 256;
 struct LarcTensor { float *w; const void *g; float *v; int64_t count; };
 struct LarcBatch {
     LarcTensor t[LARC_MAX];
+    int32_t start[LARC_MAX + 1];    // running number of slices before tensor i (set by the launcher)
     float *partial, *rates;
     float lr, trust, wd, momentum, eps;
     int32_t clip, n, first;

@@ -68,6 +68,12 @@ def test_more_tensors_than_one_launch_holds_and_tiny_ones(api):
     _check(api, shapes, "f16", 12, lr=0.1, trust=0.01, wd=0.01, mom=0.5, clip=False)
 
 
+def test_slice_edges_and_a_full_table(api):
+    # around one slice (8192 elements), one trip of four loads (4096), 256 slices (2 M) and longer slices behind it
+    edge = [(n,) for n in [4095, 4096, 4097, 8191, 8192, 8193, 16385, (1 << 21) - 1, 1 << 21, (1 << 21) + 5, 3000001]]
+    _check(api, edge + [(7,)] * (64 - len(edge)), "f16", 15, lr=0.1, trust=0.01, wd=0.01, mom=0.9, clip=True)
+
+
 def test_clipping_both_ways_and_degenerate_tensors(api):
     shapes = [(64, 3, 3, 16)] * 4
     # gradient scales: tiny (clip caps the rate at lr), huge (local rate rules)
