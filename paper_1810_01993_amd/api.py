@@ -128,7 +128,8 @@ def _dev_ptr(t: torch.Tensor | None) -> int | None:
 
 
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    """The current stream of the current device (what torch.cuda.current_stream() names, without building the object)."""
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def dl_conv_out_shape(desc: ConvDesc):
@@ -150,6 +151,26 @@ def dl_conv_describe(desc: ConvDesc, which: int) -> str:
     return buf.value.decode()
 
 
+_plans: dict = {}               # bytes of a C descriptor -> its output extents and workspace sizes (bounded, see _plan)
+
+
+def _plan(desc: ConvDesc):
+    """(reference to the C descriptor, P, Q, workspace bytes per pass).
+
+    What the library answers for a descriptor depends on its values alone, so the answers are kept by those values: the
+    four queries take about 6 us, as long as a small layer's kernel."""
+    c = desc.c_struct()
+    ref, key = ctypes.byref(c), bytes(c)
+    p = _plans.get(key)
+    if p is None:
+        P, Q = dl_conv_out_shape(desc)
+        p = (P, Q, tuple(dl_conv_workspace_bytes(desc, which) for which in (PASS_FWD, PASS_BWD_DATA, PASS_BWD_FILTER)))
+        if len(_plans) >= 1024:
+            _plans.clear()
+        _plans[key] = p
+    return (ref, *p)
+
+
 def dl_ce_workspace_bytes(n_pixels: int) -> int:
     n = ctypes.c_size_t()
     _check(_lib.dl_ce_workspace_bytes(n_pixels, ctypes.byref(n)), "dl_ce_workspace_bytes")
@@ -162,6 +183,11 @@ def _workspace(nbytes: int, device, workspace: torch.Tensor | None):
     return workspace, workspace.numel() * workspace.element_size()
 
 
+def _conv_workspace(nbytes: int, device, workspace: torch.Tensor | None):
+    """As _workspace, for the calls that take none when they need none."""
+    return (None, 0) if workspace is None and nbytes == 0 else _workspace(nbytes, device, workspace)
+
+
 def _expect(t: torch.Tensor, shape, name: str):
     if tuple(t.shape) != tuple(shape):
         raise ValueError(f"{name}: expected shape {tuple(shape)}, got {tuple(t.shape)}")
@@ -169,7 +195,7 @@ def _expect(t: torch.Tensor, shape, name: str):
 
 def conv2d_fwd(desc: ConvDesc, x: torch.Tensor, w: torch.Tensor, y: torch.Tensor | None = None,
                workspace: torch.Tensor | None = None) -> torch.Tensor:
-    P, Q = dl_conv_out_shape(desc)
+    ref, P, Q, need = _plan(desc)
     _expect(x, (desc.N, desc.H, desc.W, desc.C), "x")
     _expect(w, (desc.K, desc.R, desc.S, desc.C), "w")
     if _dtype_code(x) != desc.dtype or w.dtype != x.dtype:
@@ -177,8 +203,8 @@ def conv2d_fwd(desc: ConvDesc, x: torch.Tensor, w: torch.Tensor, y: torch.Tensor
     if y is None:
         y = torch.empty((desc.N, P, Q, desc.K), dtype=x.dtype, device=x.device)
     _expect(y, (desc.N, P, Q, desc.K), "y")
-    ws, nb = _workspace(dl_conv_workspace_bytes(desc, PASS_FWD), x.device, workspace)
-    _check(_lib.conv2d_fwd(ctypes.byref(desc.c_struct()), _dev_ptr(x), _dev_ptr(w), _dev_ptr(y), _dev_ptr(ws), nb,
+    ws, nb = _conv_workspace(need[PASS_FWD], x.device, workspace)
+    _check(_lib.conv2d_fwd(ref, _dev_ptr(x), _dev_ptr(w), _dev_ptr(y), _dev_ptr(ws), nb,
                            _stream()), "conv2d_fwd")
     return y
 
@@ -186,7 +212,7 @@ def conv2d_fwd(desc: ConvDesc, x: torch.Tensor, w: torch.Tensor, y: torch.Tensor
 def conv2d_fwd_bias_relu(desc: ConvDesc, x: torch.Tensor, w: torch.Tensor, bias: torch.Tensor | None, relu: bool,
                          y: torch.Tensor | None = None, workspace: torch.Tensor | None = None) -> torch.Tensor:
     """y = act(conv(x, w) + bias): bias float32[K] on the device or None; relu cuts negative results."""
-    P, Q = dl_conv_out_shape(desc)
+    ref, P, Q, need = _plan(desc)
     _expect(x, (desc.N, desc.H, desc.W, desc.C), "x")
     _expect(w, (desc.K, desc.R, desc.S, desc.C), "w")
     if _dtype_code(x) != desc.dtype or w.dtype != x.dtype:
@@ -196,8 +222,8 @@ def conv2d_fwd_bias_relu(desc: ConvDesc, x: torch.Tensor, w: torch.Tensor, bias:
     if y is None:
         y = torch.empty((desc.N, P, Q, desc.K), dtype=x.dtype, device=x.device)
     _expect(y, (desc.N, P, Q, desc.K), "y")
-    ws, nb = _workspace(dl_conv_workspace_bytes(desc, PASS_FWD), x.device, workspace)
-    _check(_lib.conv2d_fwd_bias_relu(ctypes.byref(desc.c_struct()), _dev_ptr(x), _dev_ptr(w), _dev_ptr(bias),
+    ws, nb = _conv_workspace(need[PASS_FWD], x.device, workspace)
+    _check(_lib.conv2d_fwd_bias_relu(ref, _dev_ptr(x), _dev_ptr(w), _dev_ptr(bias),
                                      1 if relu else 0, _dev_ptr(y), _dev_ptr(ws), nb, _stream()),
            "conv2d_fwd_bias_relu")
     return y
@@ -207,7 +233,7 @@ def conv2d_fwd_bias_add_relu(desc: ConvDesc, x: torch.Tensor, w: torch.Tensor, b
                              residual: torch.Tensor | None, relu: bool, y: torch.Tensor | None = None,
                              workspace: torch.Tensor | None = None) -> torch.Tensor:
     """y = act(conv(x, w) + bias + residual): residual [N,P,Q,K] of x's dtype or None (a ResNet block's tail)."""
-    P, Q = dl_conv_out_shape(desc)
+    ref, P, Q, need = _plan(desc)
     _expect(x, (desc.N, desc.H, desc.W, desc.C), "x")
     _expect(w, (desc.K, desc.R, desc.S, desc.C), "w")
     if _dtype_code(x) != desc.dtype or w.dtype != x.dtype:
@@ -221,8 +247,8 @@ def conv2d_fwd_bias_add_relu(desc: ConvDesc, x: torch.Tensor, w: torch.Tensor, b
     if y is None:
         y = torch.empty((desc.N, P, Q, desc.K), dtype=x.dtype, device=x.device)
     _expect(y, (desc.N, P, Q, desc.K), "y")
-    ws, nb = _workspace(dl_conv_workspace_bytes(desc, PASS_FWD), x.device, workspace)
-    _check(_lib.conv2d_fwd_bias_add_relu(ctypes.byref(desc.c_struct()), _dev_ptr(x), _dev_ptr(w), _dev_ptr(bias),
+    ws, nb = _conv_workspace(need[PASS_FWD], x.device, workspace)
+    _check(_lib.conv2d_fwd_bias_add_relu(ref, _dev_ptr(x), _dev_ptr(w), _dev_ptr(bias),
                                          _dev_ptr(residual), 1 if relu else 0, _dev_ptr(y), _dev_ptr(ws), nb, _stream()),
            "conv2d_fwd_bias_add_relu")
     return y
@@ -230,7 +256,7 @@ def conv2d_fwd_bias_add_relu(desc: ConvDesc, x: torch.Tensor, w: torch.Tensor, b
 
 def conv2d_bwd_data(desc: ConvDesc, dy: torch.Tensor, w: torch.Tensor, dx: torch.Tensor | None = None,
                     workspace: torch.Tensor | None = None) -> torch.Tensor:
-    P, Q = dl_conv_out_shape(desc)
+    ref, P, Q, need = _plan(desc)
     _expect(dy, (desc.N, P, Q, desc.K), "dy")
     _expect(w, (desc.K, desc.R, desc.S, desc.C), "w")
     if _dtype_code(dy) != desc.dtype or w.dtype != dy.dtype:
@@ -238,15 +264,15 @@ def conv2d_bwd_data(desc: ConvDesc, dy: torch.Tensor, w: torch.Tensor, dx: torch
     if dx is None:
         dx = torch.empty((desc.N, desc.H, desc.W, desc.C), dtype=dy.dtype, device=dy.device)
     _expect(dx, (desc.N, desc.H, desc.W, desc.C), "dx")
-    ws, nb = _workspace(dl_conv_workspace_bytes(desc, PASS_BWD_DATA), dy.device, workspace)
-    _check(_lib.conv2d_bwd_data(ctypes.byref(desc.c_struct()), _dev_ptr(dy), _dev_ptr(w), _dev_ptr(dx), _dev_ptr(ws),
+    ws, nb = _conv_workspace(need[PASS_BWD_DATA], dy.device, workspace)
+    _check(_lib.conv2d_bwd_data(ref, _dev_ptr(dy), _dev_ptr(w), _dev_ptr(dx), _dev_ptr(ws),
                                 nb, _stream()), "conv2d_bwd_data")
     return dx
 
 
 def conv2d_bwd_filter(desc: ConvDesc, x: torch.Tensor, dy: torch.Tensor, dw: torch.Tensor | None = None,
                       workspace: torch.Tensor | None = None) -> torch.Tensor:
-    P, Q = dl_conv_out_shape(desc)
+    ref, P, Q, need = _plan(desc)
     _expect(x, (desc.N, desc.H, desc.W, desc.C), "x")
     _expect(dy, (desc.N, P, Q, desc.K), "dy")
     if _dtype_code(x) != desc.dtype or dy.dtype != x.dtype:
@@ -256,8 +282,8 @@ def conv2d_bwd_filter(desc: ConvDesc, x: torch.Tensor, dy: torch.Tensor, dw: tor
         dw = torch.empty((desc.K, desc.R, desc.S, desc.C), device=x.device,
                          dtype=torch.float32 if dwt == DL_F32 else x.dtype)
     _expect(dw, (desc.K, desc.R, desc.S, desc.C), "dw")
-    ws, nb = _workspace(dl_conv_workspace_bytes(desc, PASS_BWD_FILTER), x.device, workspace)
-    _check(_lib.conv2d_bwd_filter(ctypes.byref(desc.c_struct()), _dev_ptr(x), _dev_ptr(dy), _dev_ptr(dw),
+    ws, nb = _workspace(need[PASS_BWD_FILTER], x.device, workspace)
+    _check(_lib.conv2d_bwd_filter(ref, _dev_ptr(x), _dev_ptr(dy), _dev_ptr(dw),
                                   _dev_ptr(ws), nb, _stream()), "conv2d_bwd_filter")
     return dw
 
@@ -265,7 +291,7 @@ def conv2d_bwd_filter(desc: ConvDesc, x: torch.Tensor, dy: torch.Tensor, dw: tor
 def conv2d_transpose_fwd(desc: ConvDesc, x: torch.Tensor, w: torch.Tensor, y: torch.Tensor | None = None,
                          workspace: torch.Tensor | None = None) -> torch.Tensor:
     """x: [N,P,Q,K] -> y: [N,H,W,C]; ``desc`` names the underlying convolution (see the header)."""
-    P, Q = dl_conv_out_shape(desc)
+    ref, P, Q, need = _plan(desc)
     _expect(x, (desc.N, P, Q, desc.K), "x")
     _expect(w, (desc.K, desc.R, desc.S, desc.C), "w")
     if _dtype_code(x) != desc.dtype or w.dtype != x.dtype:
@@ -273,8 +299,8 @@ def conv2d_transpose_fwd(desc: ConvDesc, x: torch.Tensor, w: torch.Tensor, y: to
     if y is None:
         y = torch.empty((desc.N, desc.H, desc.W, desc.C), dtype=x.dtype, device=x.device)
     _expect(y, (desc.N, desc.H, desc.W, desc.C), "y")
-    ws, nb = _workspace(dl_conv_workspace_bytes(desc, PASS_BWD_DATA), x.device, workspace)
-    _check(_lib.conv2d_transpose_fwd(ctypes.byref(desc.c_struct()), _dev_ptr(x), _dev_ptr(w), _dev_ptr(y),
+    ws, nb = _conv_workspace(need[PASS_BWD_DATA], x.device, workspace)
+    _check(_lib.conv2d_transpose_fwd(ref, _dev_ptr(x), _dev_ptr(w), _dev_ptr(y),
                                      _dev_ptr(ws), nb, _stream()), "conv2d_transpose_fwd")
     return y
 
@@ -282,7 +308,7 @@ def conv2d_transpose_fwd(desc: ConvDesc, x: torch.Tensor, w: torch.Tensor, y: to
 def conv2d_transpose_bwd_data(desc: ConvDesc, dy: torch.Tensor, w: torch.Tensor, dx: torch.Tensor | None = None,
                               workspace: torch.Tensor | None = None) -> torch.Tensor:
     """dy: [N,H,W,C] -> dx: [N,P,Q,K]."""
-    P, Q = dl_conv_out_shape(desc)
+    ref, P, Q, need = _plan(desc)
     _expect(dy, (desc.N, desc.H, desc.W, desc.C), "dy")
     _expect(w, (desc.K, desc.R, desc.S, desc.C), "w")
     if _dtype_code(dy) != desc.dtype or w.dtype != dy.dtype:
@@ -290,8 +316,8 @@ def conv2d_transpose_bwd_data(desc: ConvDesc, dy: torch.Tensor, w: torch.Tensor,
     if dx is None:
         dx = torch.empty((desc.N, P, Q, desc.K), dtype=dy.dtype, device=dy.device)
     _expect(dx, (desc.N, P, Q, desc.K), "dx")
-    ws, nb = _workspace(dl_conv_workspace_bytes(desc, PASS_FWD), dy.device, workspace)
-    _check(_lib.conv2d_transpose_bwd_data(ctypes.byref(desc.c_struct()), _dev_ptr(dy), _dev_ptr(w), _dev_ptr(dx),
+    ws, nb = _conv_workspace(need[PASS_FWD], dy.device, workspace)
+    _check(_lib.conv2d_transpose_bwd_data(ref, _dev_ptr(dy), _dev_ptr(w), _dev_ptr(dx),
                                           _dev_ptr(ws), nb, _stream()), "conv2d_transpose_bwd_data")
     return dx
 
@@ -299,7 +325,7 @@ def conv2d_transpose_bwd_data(desc: ConvDesc, dy: torch.Tensor, w: torch.Tensor,
 def conv2d_transpose_bwd_filter(desc: ConvDesc, x: torch.Tensor, dy: torch.Tensor, dw: torch.Tensor | None = None,
                                 workspace: torch.Tensor | None = None) -> torch.Tensor:
     """x: [N,P,Q,K], dy: [N,H,W,C] -> dw: [K,R,S,C]."""
-    P, Q = dl_conv_out_shape(desc)
+    ref, P, Q, need = _plan(desc)
     _expect(x, (desc.N, P, Q, desc.K), "x")
     _expect(dy, (desc.N, desc.H, desc.W, desc.C), "dy")
     if _dtype_code(x) != desc.dtype or dy.dtype != x.dtype:
@@ -309,8 +335,8 @@ def conv2d_transpose_bwd_filter(desc: ConvDesc, x: torch.Tensor, dy: torch.Tenso
         dw = torch.empty((desc.K, desc.R, desc.S, desc.C), device=x.device,
                          dtype=torch.float32 if dwt == DL_F32 else x.dtype)
     _expect(dw, (desc.K, desc.R, desc.S, desc.C), "dw")
-    ws, nb = _workspace(dl_conv_workspace_bytes(desc, PASS_BWD_FILTER), x.device, workspace)
-    _check(_lib.conv2d_transpose_bwd_filter(ctypes.byref(desc.c_struct()), _dev_ptr(x), _dev_ptr(dy), _dev_ptr(dw),
+    ws, nb = _workspace(need[PASS_BWD_FILTER], x.device, workspace)
+    _check(_lib.conv2d_transpose_bwd_filter(ref, _dev_ptr(x), _dev_ptr(dy), _dev_ptr(dw),
                                             _dev_ptr(ws), nb, _stream()), "conv2d_transpose_bwd_filter")
     return dw
 

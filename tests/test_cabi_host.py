@@ -158,6 +158,25 @@ def test_dispatch_does_not_read_the_environment(api):
     assert "getenv" not in syms
 
 
+def test_kept_descriptor_answers_follow_the_values(api):
+    """The wrapper keeps the library's answers by the values of the descriptor: equal values share them, any other value
+    gets its own, refused descriptors are refused every time and the store stays bounded."""
+    base = dict(N=1, H=20, W=33, C=16, K=32, R=3, S=3, stride_h=1, stride_w=1, pad_h=1, pad_w=1, dil_h=1, dil_w=1)
+    for change in ({}, {}, {"H": 40}, {"stride_w": 2}, {"dil_h": 2}, {"K": 8}, {"dtype": api.DL_BF16}, {"dw_dtype": api.DL_F32}):
+        d = api.ConvDesc(**{**base, **change})
+        for _ in range(2):
+            _, P, Q, need = api._plan(d)
+            assert (P, Q) == api.dl_conv_out_shape(d)
+            assert list(need) == [api.dl_conv_workspace_bytes(d, w) for w in range(3)]
+    for _ in range(2):
+        assert _code(api._plan, api.ConvDesc(1, 8, 8, 8, 8, 3, 3, 0)) == 2
+        with pytest.raises((TypeError, ctypes.ArgumentError)):
+            api._plan(api.ConvDesc(**{**base, "N": 1.0}))
+    for n in range(1100):
+        api._plan(api.ConvDesc(1, 8, 8 + n, 8, 8, 1, 1))
+    assert len(api._plans) <= 1024
+
+
 def test_describe_names_the_kernels_of_the_decoder_layers(api):
     """dl_conv_describe runs the entry points' own dispatch with launches logged instead of issued
     (no GPU needed): the layers that carry 87 % of the FLOPs must reach the kernels built for them."""
