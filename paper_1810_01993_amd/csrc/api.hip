@@ -206,7 +206,7 @@ dlk::WgradPlan wgrad_plan(const dl_conv_desc *d, const Geometry &g)
         return dlk::WgradPlan{-3, p3.slices, 0};
     }
     const bool thin = dlk::thin_wgrad_applicable(d->K, d->C, d->R, d->S, d->stride_h, d->stride_w, d->pad_h, d->pad_w);
-    return dlk::wgrad_make_plan((int64_t)d->N * g.P * g.Q, d->K, d->C, d->R * d->S * d->C, thin);
+    return dlk::wgrad_make_plan((int64_t)d->N * g.P * g.Q, g.x_elems, d->K, d->C, d->R * d->S * d->C, thin);
 }
 
 size_t wgrad_workspace(const dl_conv_desc *d, const Geometry &g)

@@ -14,6 +14,7 @@
 //
 // The pixel range is cut into `splits` slices; every slice writes an fp32
 // partial tile and a second kernel adds the slices in a fixed order.
+#include <algorithm>
 #include <cstdlib>
 
 #include "device_common.h"
@@ -232,7 +233,7 @@ static hipError_t launch_cfg(const WgradArgs &a, hipStream_t stream)
     return dlk::launch_status();
 }
 
-WgradPlan wgrad_make_plan(int64_t npix, int K, int C, int RSC, bool thin_ok)
+WgradPlan wgrad_make_plan(int64_t npix, int64_t x_elems, int K, int C, int RSC, bool thin_ok)
 {
     static const int forced = tuning_knob("DLCONV_WGRAD_CFG", -2); // tuning override, unset in normal use
     WgradPlan pl{-1, 1, 32, 0};
@@ -291,7 +292,16 @@ WgradPlan wgrad_make_plan(int64_t npix, int K, int C, int RSC, bool thin_ok)
             const int64_t per_xcd = (splits + 7) / 8;
             const int64_t rounds = spread ? (tiles * splits + 8 * cap - 1) / (8 * cap) : (tiles * per_xcd + cap - 1) / cap;
             const double reduce_us = (splits > 1 ? splits * outputs * 8.0 : outputs * 6.0) / 11.5e6;
-            const double est = 9.0 + rounds * (chunk / 32 + 7) * sh.us_per_step + reduce_us;
+            // Tiles of one slice that run on different XCDs share no L2.  With up to nine taps and operands beyond
+            // what the L2s hold (32 MB together) every operand tile then comes from the last-level cache or HBM, at
+            // about 9 TB/s; where that takes longer than the steps, a slice belongs on one XCD (256 x 9 x 256 filter,
+            // stride 2, 110592 pixels: 14 dealt slices of 128 x 128 tiles, 2 GB, 240 us; 24 slices of 256 x 256 tiles
+            // on their XCDs 152 us; 1.2-1.9x on 21 of 24 such shapes, 0.95-0.97x on three).  Below that size, and with
+            // more taps, whose tiles meet in an XCD's L2, dealt slices were fetched at 10-16 TB/s and stayed ahead.
+            const double steps_us = rounds * (chunk / 32 + 7) * sh.us_per_step;
+            const bool fetch_bound = spread && RSC / C <= 9 && 2 * (x_elems + npix * K) >= 40000000;
+            const double fetch_us = fetch_bound ? 2.0 * tiles * (sh.bm + sh.bn) * (double)npix / 9e6 : 0.0;
+            const double est = 9.0 + std::max(steps_us, fetch_us) + reduce_us;
             if (est < best) {
                 best = est;
                 pl.cfg = cfg;

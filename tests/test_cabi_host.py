@@ -192,6 +192,11 @@ def test_describe_names_the_kernels_of_the_decoder_layers(api):
     assert api.dl_conv_describe(logits, api.PASS_FWD) == "thin_cols_kernel[2048]"
     assert "thin_rows_kernel" in api.dl_conv_describe(logits, api.PASS_BWD_DATA)
     assert "thin_wgrad_kernel" in api.dl_conv_describe(logits, api.PASS_BWD_FILTER)
+    # filter gradient: large operands that every XCD would fetch for itself keep a slice on one XCD, small ones are dealt
+    up = api.ConvDesc(2, 384, 576, 256, 256, 3, 3, 2, 2, 1, 1, 1, 1, api.DL_F16)
+    assert api.dl_conv_describe(up, api.PASS_BWD_FILTER).startswith("wgrad_dma_kernel<256,256>[216]")
+    low = api.ConvDesc(2, 48, 72, 256, 256, 3, 3, 2, 2, 1, 1, 1, 1, api.DL_F16)
+    assert api.dl_conv_describe(low, api.PASS_BWD_FILTER).startswith("wgrad_dma_kernel<128,128>")
     # the query leaves nothing behind: a call after it still validates and reports as before
     assert api._lib.conv2d_fwd(ctypes.byref(dec.c_struct()), None, None, None, None, 0, None) == 1
     assert _code(api.dl_conv_describe, api.ConvDesc(2, 8, 8, 8, 8, 3, 3, 1, 1, 1, 1, 1, 1, api.DL_F16), 5) == 6
