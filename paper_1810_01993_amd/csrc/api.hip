@@ -123,6 +123,21 @@ hipError_t run_igemm(const dlk::IgemmArgs &a, bool bf16, const FilterSrc &fs, ui
     return dlk::launch_igemm(r, bf16, stream);
 }
 
+// ---- channel counts that are not a multiple of 8 -------------------------------
+// The kernels that move 16-byte pieces need C % 8 == 0; the element-wise ones are 2 to 10 times slower.
+// So the activation tensor (and the forward filter) is first copied with its channels padded with zeros, and the
+// layer runs on the copy: 361 x 577 x 6 -> 64, 7x7 stride 2, batch 2: forward 56 -> 28 us, filter gradient 148 -> 35 us,
+// 5 us of either being the copy; 60 x 90 x 100 -> 64, 3x3: 92 -> 14 us and 41 -> 20 us.  Forward reductions of at
+// most 24 elements stay with the element-wise kernel (60 x 90 x 17 -> 64, 1x1: 9.1 us, 9.9 us through the copy).
+// Zero channels meet zero coefficients, so the sums are those of the layer itself.
+inline dl_conv_desc padded_desc(const dl_conv_desc *d)
+{
+    dl_conv_desc e = *d;
+    e.C = (d->C + 7) / 8 * 8;
+    return e;
+}
+inline size_t padded_bytes(const dl_conv_desc *e, int64_t rows) { return align_up((size_t)rows * e->C * sizeof(uint16_t), 256); }
+
 dlk::IgemmArgs fwd_args(const dl_conv_desc *d, const Geometry &g)
 {
     dlk::IgemmArgs a{};
@@ -133,6 +148,20 @@ dlk::IgemmArgs fwd_args(const dl_conv_desc *d, const Geometry &g)
     a.th0 = -d->pad_h; a.dth = d->dil_h; a.tw0 = -d->pad_w; a.dtw = d->dil_w;
     a.FH = g.P; a.FW = g.Q; a.osh = 1; a.osw = 1; a.ooh = 0; a.oow = 0; a.ldd = d->K;
     return a;
+}
+
+// Scratch of a forward pass on the channel-padded copies (0: the layer takes its own tensors): the copies, then what
+// the implicit GEMM on them needs.  Layers that the streaming kernel for few channels takes stay with it.
+size_t fwd_padded_workspace(const dl_conv_desc *d, const Geometry &g, bool resid)
+{
+    if (d->C % 8 == 0 || (int64_t)d->R * d->S * d->C <= 24 || dlk::thin_rows_applicable(fwd_args(d, g))) return 0;
+    const dl_conv_desc e = padded_desc(d);
+    Geometry ge;
+    if (check_desc(&e, &ge) != DL_OK) return 0;              // the copy would exceed the index range
+    dlk::IgemmArgs a = fwd_args(&e, ge);
+    a.resid = resid ? reinterpret_cast<const uint16_t *>(uintptr_t(16)) : nullptr;      // only tested for null
+    return padded_bytes(&e, (int64_t)d->N * d->H * d->W) + padded_bytes(&e, (int64_t)d->K * d->R * d->S) +
+           igemm_scratch_bytes(a);
 }
 
 // The data gradient of one stride-parity class (ca, cb) of the input pixels.
@@ -209,9 +238,26 @@ dlk::WgradPlan wgrad_plan(const dl_conv_desc *d, const Geometry &g)
     return dlk::wgrad_make_plan((int64_t)d->N * g.P * g.Q, g.x_elems, d->K, d->C, d->R * d->S * d->C, thin);
 }
 
-size_t wgrad_workspace(const dl_conv_desc *d, const Geometry &g)
+size_t wgrad_own_workspace(const dl_conv_desc *d, const Geometry &g)
 {
     return (size_t)wgrad_plan(d, g).splits * (size_t)g.w_elems * sizeof(float);
+}
+
+// As fwd_padded_workspace, for the filter gradient: partial sums of the padded filter, then the copy of x.
+size_t wgrad_padded_workspace(const dl_conv_desc *d, const Geometry &g)
+{
+    if (d->C % 8 == 0) return 0;
+    const dl_conv_desc e = padded_desc(d);
+    Geometry ge;
+    if (check_desc(&e, &ge) != DL_OK) return 0;
+    // only where the copy gets a faster kernel, and never instead of the streaming kernel for few output channels
+    if (wgrad_plan(d, g).cfg != -1 || wgrad_plan(&e, ge).cfg == -1) return 0;
+    return align_up(wgrad_own_workspace(&e, ge), 256) + padded_bytes(&e, (int64_t)d->N * d->H * d->W);
+}
+
+size_t wgrad_workspace(const dl_conv_desc *d, const Geometry &g)
+{
+    return std::max(wgrad_own_workspace(d, g), wgrad_padded_workspace(d, g));
 }
 
 dl_status hip_status(hipError_t e) { return e == hipSuccess ? DL_OK : DL_ERR_LAUNCH; }
@@ -301,7 +347,7 @@ dl_status dl_conv_workspace_bytes(const dl_conv_desc *desc, int pass, size_t *by
             dlk::IgemmArgs a = fwd_args(desc, g);
             const size_t plain = igemm_scratch_bytes(a);
             a.resid = reinterpret_cast<const uint16_t *>(uintptr_t(16));     // any non-null value: only tested for null
-            *bytes = std::max(plain, igemm_scratch_bytes(a));
+            *bytes = std::max({plain, igemm_scratch_bytes(a), fwd_padded_workspace(desc, g, false), fwd_padded_workspace(desc, g, true)});
             return DL_OK;
         }
         case DL_PASS_BWD_DATA: *bytes = dgrad_workspace(desc, g); return DL_OK;
@@ -326,6 +372,19 @@ dl_status run_fwd(const dl_conv_desc *d, const void *x, const void *w, const flo
     const size_t need = igemm_scratch_bytes(a);
     if (need > 0 && (!workspace || workspace_bytes < need)) return DL_ERR_WORKSPACE;
     if (need > 0 && !aligned16(workspace)) return DL_ERR_ALIGN;
+    // (a workspace too small for the copies, or none, still runs the layer on its own tensors)
+    const size_t padded = fwd_padded_workspace(d, g, residual != nullptr);
+    if (padded > 0 && workspace && workspace_bytes >= padded && aligned16(workspace)) {
+        const dl_conv_desc e = padded_desc(d);
+        const int64_t xrows = (int64_t)d->N * d->H * d->W, wrows = (int64_t)d->K * d->R * d->S;
+        char *const xp = static_cast<char *>(workspace), *const wp = xp + padded_bytes(&e, xrows);
+        if (dlk::launch_pad_channels(static_cast<const uint16_t *>(x), reinterpret_cast<uint16_t *>(xp), xrows,
+                                     static_cast<const uint16_t *>(w), reinterpret_cast<uint16_t *>(wp), wrows, d->C,
+                                     static_cast<hipStream_t>(hip_stream)) != hipSuccess)
+            return DL_ERR_LAUNCH;
+        const size_t used = padded_bytes(&e, xrows) + padded_bytes(&e, wrows);
+        return run_fwd(&e, xp, wp, bias, residual, relu, y, xp + used, padded - used, hip_stream);
+    }
     a.A = static_cast<const uint16_t *>(x);
     a.B = static_cast<const uint16_t *>(w);
     a.D = static_cast<uint16_t *>(y);
@@ -466,19 +525,12 @@ dl_status conv2d_bwd_data(const dl_conv_desc *d, const void *dy, const void *w, 
     return DL_OK;
 }
 
-dl_status conv2d_bwd_filter(const dl_conv_desc *d, const void *x, const void *dy, void *dw, void *workspace,
-                            size_t workspace_bytes, void *hip_stream)
+namespace {
+// dw_c: channels of dw itself, smaller than d->C where d describes a channel-padded copy
+dl_status run_wgrad(const dl_conv_desc *d, const Geometry &g, const void *x, const void *dy, void *dw, int dw_c, void *workspace,
+                    hipStream_t stream)
 {
-    if (!d || !x || !dy || !dw) return DL_ERR_NULL;
-    Geometry g;
-    const dl_status st = check_desc(d, &g);
-    if (st != DL_OK) return st;
-    if (!aligned16(x) || !aligned16(dy) || !aligned16(dw)) return DL_ERR_ALIGN;
     const dlk::WgradPlan plan = wgrad_plan(d, g);
-    if (!workspace || workspace_bytes < wgrad_workspace(d, g)) return DL_ERR_WORKSPACE;
-    if (!aligned16(workspace)) return DL_ERR_ALIGN;
-    hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-
     dlk::WgradArgs a{};
     a.x = static_cast<const uint16_t *>(x);
     a.dy = static_cast<const uint16_t *>(dy);
@@ -508,9 +560,38 @@ dl_status conv2d_bwd_filter(const dl_conv_desc *d, const void *x, const void *dy
                    : plan.cfg == -2 ? dlk::launch_thin_wgrad(a, d->dtype == DL_BF16, stream)
                                     : dlk::launch_wgrad(a, d->dtype == DL_BF16, stream);
     if (e != hipSuccess) return DL_ERR_LAUNCH;
+    if (dw_c != d->C)
+        return hip_status(dlk::launch_splitk_reduce_padded(a.partial, plan.splits, g.w_elems / d->C, dw_c, d->C, dw, d->dw_dtype, stream));
     e = dlk::launch_splitk_reduce(a.partial, plan.splits, g.w_elems, dw, d->dw_dtype, stream);
     return hip_status(e);
 }
+}  // namespace
+
+dl_status conv2d_bwd_filter(const dl_conv_desc *d, const void *x, const void *dy, void *dw, void *workspace,
+                            size_t workspace_bytes, void *hip_stream)
+{
+    if (!d || !x || !dy || !dw) return DL_ERR_NULL;
+    Geometry g;
+    const dl_status st = check_desc(d, &g);
+    if (st != DL_OK) return st;
+    if (!aligned16(x) || !aligned16(dy) || !aligned16(dw)) return DL_ERR_ALIGN;
+    if (!workspace || workspace_bytes < wgrad_own_workspace(d, g)) return DL_ERR_WORKSPACE;
+    if (!aligned16(workspace)) return DL_ERR_ALIGN;
+    hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+    const size_t padded = wgrad_padded_workspace(d, g);
+    if (padded > 0 && workspace_bytes >= padded) {
+        const dl_conv_desc e = padded_desc(d);
+        Geometry ge;
+        check_desc(&e, &ge);
+        char *const xp = static_cast<char *>(workspace) + align_up(wgrad_own_workspace(&e, ge), 256);
+        if (dlk::launch_pad_channels(static_cast<const uint16_t *>(x), reinterpret_cast<uint16_t *>(xp), (int64_t)d->N * d->H * d->W,
+                                     nullptr, nullptr, 0, d->C, stream) != hipSuccess)
+            return DL_ERR_LAUNCH;
+        return run_wgrad(&e, ge, xp, dy, dw, d->C, workspace, stream);
+    }
+    return run_wgrad(d, g, x, dy, dw, d->C, workspace, stream);
+}
+
 
 dl_status dl_conv_describe(const dl_conv_desc *d, int pass, char *buf, size_t buf_bytes)
 {

@@ -16,7 +16,8 @@
 // the 98 (class, tap, row) products) and reads one filter fragment per tap.
 // The filter rides in the first MFMA operand, so a lane ends up with four
 // consecutive channels of one pixel; the 32 x 32 x 16 tile is assembled in LDS
-// and written out as whole 1 KB rows.
+// and written out as whole 1 KB rows (fewer channels than 16 or 8: as packed rows of 32 pixels, 4 bytes per lane
+// where the channel count is even: 361 x 577 x 6 <- 64, batch 2: 78 us as four GEMMs with 6 of 32 columns -> 22 us).
 #include <cstdlib>
 
 #include "device_common.h"
@@ -129,6 +130,27 @@ __global__ __launch_bounds__(512) void dgrad_stem_kernel(const DgradStemArgs p)
             }
     __syncthreads();
     const int h0 = 2 * p0, w0 = 2 * q0;
+    if (p.C % 8 != 0) {
+        // rows of 32 pixels x C channels, packed: 4 bytes per lane where C is even (every row starts on a multiple of
+        // four bytes then), else element by element
+        const int cols = min(32, p.W - w0) * p.C;
+        for (int row = wave; row < 32 && h0 + row < p.H; row += NW) {
+            uint16_t *dst = p.dx + ((size_t)(img * p.H + h0 + row) * p.W + w0) * p.C;
+            const uint16_t *src = stg + row * 32 * 16;
+            if (p.C % 2 == 0) {
+                for (int e = 2 * lane; e < cols; e += 128) {
+                    const int px = e / p.C, c = e - px * p.C;
+                    *reinterpret_cast<uint32_t *>(dst + e) = *reinterpret_cast<const uint32_t *>(src + px * 16 + c);
+                }
+            } else {
+                for (int e = lane; e < cols; e += 64) {
+                    const int px = e / p.C, c = e - px * p.C;
+                    dst[e] = src[px * 16 + c];
+                }
+            }
+        }
+        return;
+    }
 #pragma unroll
     for (int it = 0; it < 4; ++it) {
         const int row = wave * 4 + it, col = lane >> 1, c8 = (lane & 1) * 8;
@@ -144,7 +166,7 @@ bool dgrad_stem_applicable(int N, int H, int W, int C, int K, int R, int S, int 
     static const int mode = tuning_knob("DLCONV_DGRAD_STEM", 1); // tuning override: 0 = never
     (void)N;
     return mode && R == DS_R && S == DS_R && sh == 2 && sw == 2 && ph == DS_PAD && pw == DS_PAD && dh == 1 && dw == 1 &&
-           (C == 8 || C == 16) && K % 8 == 0 && K <= DS_MAXCH * BK && H >= 2 && W >= 2;
+           C <= 16 && K % 8 == 0 && K <= DS_MAXCH * BK && H >= 2 && W >= 2;
 }
 
 size_t dgrad_stem_filter_bytes(int C, int K) { return (size_t)((K + BK - 1) / BK) * DS_R * DS_R * C * BK * sizeof(uint16_t); }

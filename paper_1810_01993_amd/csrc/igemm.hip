@@ -331,6 +331,39 @@ hipError_t launch_zero_classes(uint16_t *dx, int N, int H, int W, int C, int sh,
     return dlk::launch_status();
 }
 
+// Channel padding for the kernels that move 16-byte pieces: one piece of eight channels per thread, assembled from
+// 2-byte loads (neighbouring threads read neighbouring elements, the cache makes whole lines of them).
+__global__ __launch_bounds__(256) void pad_channels_kernel(const uint16_t *__restrict__ src, uint16_t *__restrict__ dst, int64_t pieces,
+                                                           const uint16_t *__restrict__ src2, uint16_t *__restrict__ dst2,
+                                                           int64_t pieces2, int C)
+{
+    const int C8 = (C + 7) / 8;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < pieces + pieces2; i += (int64_t)gridDim.x * 256) {
+        const bool second = i >= pieces;
+        const int64_t j = second ? i - pieces : i;
+        const int64_t row = j / C8;
+        const int c0 = (int)(j - row * C8) * 8;
+        const uint16_t *from = (second ? src2 : src) + row * C + c0;
+        u32x4_t v;
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+            const uint32_t lo = c0 + 2 * d < C ? from[2 * d] : 0u, hi = c0 + 2 * d + 1 < C ? from[2 * d + 1] : 0u;
+            v[d] = lo | (hi << 16);
+        }
+        *reinterpret_cast<u32x4_t *>((second ? dst2 : dst) + j * 8) = v;
+    }
+}
+
+hipError_t launch_pad_channels(const uint16_t *src, uint16_t *dst, int64_t rows, const uint16_t *src2, uint16_t *dst2,
+                               int64_t rows2, int C, hipStream_t stream)
+{
+    const int64_t C8 = (C + 7) / 8, pieces = rows * C8, pieces2 = rows2 * C8, want = (pieces + pieces2 + 255) / 256;
+    if (want <= 0) return hipSuccess;
+    const dim3 grid((unsigned)(want < 16384 ? want : 16384)), block(256);
+    DLK_LAUNCH("pad_channels_kernel", pad_channels_kernel, grid, block, 0, stream, src, dst, pieces, src2, dst2, pieces2, C);
+    return dlk::launch_status();
+}
+
 hipError_t launch_filter_relayout(const FilterRelayoutArgs &a, hipStream_t stream)
 {
     const int64_t total = (int64_t)a.C * a.TR * a.TS * a.K;

@@ -156,7 +156,7 @@ struct FilterBlockArgs {
 };
 hipError_t launch_filter_block(const FilterBlockArgs &a, hipStream_t stream);
 
-// Data gradient of a 7x7, stride-2, padding-3 convolution with 8 or 16 input channels and at most
+// Data gradient of a 7x7, stride-2, padding-3 convolution with at most 16 input channels and at most
 // 64 output channels (the stem): all four parity classes in one workgroup, operands resident in LDS.
 // wblk: the filter as [chunk of K][tap][c][32] (launch_filter_block with rows = c).
 struct DgradStemArgs {
@@ -181,6 +181,11 @@ hipError_t launch_filter_relayout(const FilterRelayoutArgs &a, hipStream_t strea
 // Clears the pixels of dx[N][H][W][C] (C % 8 == 0, sh * sw <= 64) whose stride-parity class (h % sh) * sw + (w % sw)
 // has its bit set in `mask`.
 hipError_t launch_zero_classes(uint16_t *dx, int N, int H, int W, int C, int sh, int sw, uint64_t mask, hipStream_t stream);
+
+// Rows of C 16-bit elements copied to rows of Cp = C rounded up to a multiple of 8, zeros behind: src[rows][C] ->
+// dst[rows][Cp], and a second such tensor behind it in the same launch (rows2 = 0: none).  dst 16-byte aligned.
+hipError_t launch_pad_channels(const uint16_t *src, uint16_t *dst, int64_t rows, const uint16_t *src2, uint16_t *dst2,
+                               int64_t rows2, int C, hipStream_t stream);
 
 // Filter gradient: partial[z][k][j] = sum over the z-th slice of the N*P*Q
 // pixels of dy[pix][k] * x[pixel(pix, tap(j)), c(j)],  j = (r*S + s)*C + c.
@@ -240,6 +245,9 @@ hipError_t launch_thin_wgrad(const WgradArgs &a, bool is_bf16, hipStream_t strea
 // dw[i] = sum_z partial[z][i] in ascending z, rounded to out_dtype (dl_dtype).
 hipError_t launch_splitk_reduce(const float *partial, int32_t splits, int64_t n, void *out, int out_dtype,
                                 hipStream_t stream);
+// The same for partial sums whose rows of C elements were padded to Cp: out[rows][C] from partial[z][rows][Cp].
+hipError_t launch_splitk_reduce_padded(const float *partial, int32_t splits, int64_t rows, int C, int Cp, void *out,
+                                       int out_dtype, hipStream_t stream);
 // The same with the forward convolution's point-wise tail: element i belongs to column i % ncols.
 hipError_t launch_splitk_reduce_tail(const float *partial, int32_t splits, int64_t n, void *out, int out_dtype,
                                      const float *bias, int32_t relu, int32_t ncols, const uint16_t *resid, hipStream_t stream);

@@ -242,7 +242,7 @@ hipError_t launch_wgrad(const WgradArgs &a, bool is_bf16, hipStream_t stream)
 template <int OUT, int G>   // OUT: 0 f16, 1 bf16, 2 f32
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *__restrict__ partial, int splits, int64_t n,
                                                             void *out, const float *__restrict__ bias, int relu, int ncols,
-                                                            const uint16_t *__restrict__ resid)
+                                                            const uint16_t *__restrict__ resid, int pad_c, int pad_cp)
 {
     constexpr int XW = 256 / G;
     __shared__ float part[G][XW];
@@ -250,7 +250,8 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *__restr
     for (int64_t base = (int64_t)blockIdx.x * XW; base < n; base += (int64_t)gridDim.x * XW) {
         const int64_t i = base + x;
         float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
-        if (i < n) {
+        const bool real = i < n && (pad_cp == 0 || (int)(i % pad_cp) < pad_c);     // not a padding column
+        if (real) {
             int z = g;
             for (; z + 3 * G < splits; z += 4 * G) {
                 s0 += partial[(size_t)z * n + i];
@@ -262,7 +263,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *__restr
         }
         part[g][x] = (s0 + s1) + (s2 + s3);
         __syncthreads();
-        if (g == 0 && i < n) {
+        if (g == 0 && real) {
             float s;
             if constexpr (G == 4) {
                 s = (part[0][x] + part[1][x]) + (part[2][x] + part[3][x]);
@@ -273,9 +274,10 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *__restr
             }
             if (OUT != 2 && resid) s += OUT == 1 ? BF16::to_float(resid[i]) : F16::to_float(resid[i]);   // same layout and type as out
             if (bias || relu) s = apply_tail(s, bias, relu, (int)(i % ncols));
-            if constexpr (OUT == 0) reinterpret_cast<uint16_t *>(out)[i] = F16::from_float(s);
-            else if constexpr (OUT == 1) reinterpret_cast<uint16_t *>(out)[i] = BF16::from_float(s);
-            else reinterpret_cast<float *>(out)[i] = s;
+            const int64_t o = pad_cp == 0 ? i : i / pad_cp * pad_c + i % pad_cp;
+            if constexpr (OUT == 0) reinterpret_cast<uint16_t *>(out)[o] = F16::from_float(s);
+            else if constexpr (OUT == 1) reinterpret_cast<uint16_t *>(out)[o] = BF16::from_float(s);
+            else reinterpret_cast<float *>(out)[o] = s;
         }
         __syncthreads();
     }
@@ -349,17 +351,17 @@ static hipError_t launch_reduce4(const float *partial, int32_t splits, int64_t n
 
 template <int G>
 static hipError_t launch_reduce_g(const float *partial, int32_t splits, int64_t n, void *out, int out_dtype, const float *bias,
-                                  int32_t relu, int32_t ncols, const uint16_t *resid, hipStream_t stream)
+                                  int32_t relu, int32_t ncols, const uint16_t *resid, hipStream_t stream, int pad_c = 0, int pad_cp = 0)
 {
     constexpr int XW = 256 / G;
     const int64_t want = (n + XW - 1) / XW;
     const dim3 grid((unsigned)(want < 16384 ? want : 16384)), block(256);
     if (out_dtype == 0)
-        DLK_LAUNCH(kname("splitk_reduce_kernel", {G}), (splitk_reduce_kernel<0, G>), grid, block, 0, stream, partial, splits, n, out, bias, relu, ncols, resid);
+        DLK_LAUNCH(kname("splitk_reduce_kernel", {G}), (splitk_reduce_kernel<0, G>), grid, block, 0, stream, partial, splits, n, out, bias, relu, ncols, resid, pad_c, pad_cp);
     else if (out_dtype == 1)
-        DLK_LAUNCH(kname("splitk_reduce_kernel", {G}), (splitk_reduce_kernel<1, G>), grid, block, 0, stream, partial, splits, n, out, bias, relu, ncols, resid);
+        DLK_LAUNCH(kname("splitk_reduce_kernel", {G}), (splitk_reduce_kernel<1, G>), grid, block, 0, stream, partial, splits, n, out, bias, relu, ncols, resid, pad_c, pad_cp);
     else
-        DLK_LAUNCH(kname("splitk_reduce_kernel", {G}), (splitk_reduce_kernel<2, G>), grid, block, 0, stream, partial, splits, n, out, bias, relu, ncols, nullptr);
+        DLK_LAUNCH(kname("splitk_reduce_kernel", {G}), (splitk_reduce_kernel<2, G>), grid, block, 0, stream, partial, splits, n, out, bias, relu, ncols, nullptr, pad_c, pad_cp);
     return dlk::launch_status();
 }
 
@@ -381,6 +383,14 @@ hipError_t launch_splitk_reduce(const float *partial, int32_t splits, int64_t n,
                                 hipStream_t stream)
 {
     return launch_splitk_reduce_tail(partial, splits, n, out, out_dtype, nullptr, 0, 1, nullptr, stream);
+}
+
+hipError_t launch_splitk_reduce_padded(const float *partial, int32_t splits, int64_t rows, int C, int Cp, void *out,
+                                       int out_dtype, hipStream_t stream)
+{
+    if (rows <= 0) return hipSuccess;
+    if (C < 1 || Cp < C) return hipErrorInvalidValue;
+    return launch_reduce_g<4>(partial, splits, rows * Cp, out, out_dtype, nullptr, 0, 1, nullptr, stream, C, Cp);
 }
 
 }  // namespace dlk

@@ -217,6 +217,41 @@ def test_stem_data_gradient_kernel(api, layer, dtype):
     check_layer(api, layer, dtype, synth.seed_for(0, 650 + len(layer.name)), x_kind="normal", passes=("dgrad",))
 
 
+# channel counts that are not a multiple of 8: channel-padded copies (forward, filter gradient), packed rows of the
+# stem's data gradient (odd and even counts, ragged patches), and the reductions on either side of the copies' limit
+ODD = [
+    (L("odd.7x7s2.c3", 2, 33, 65, 3, 64, 7, 7, 2, 3, 1), "f16"),
+    (L("odd.7x7s2.c6", 1, 61, 97, 6, 48, 7, 7, 2, 3, 1), "bf16"),
+    (L("odd.7x7s2.c9", 1, 64, 35, 9, 32, 7, 7, 2, 3, 1), "f16"),
+    (L("odd.7x7s2.c14", 2, 17, 34, 14, 64, 7, 7, 2, 3, 1), "bf16"),
+    (L("odd.7x7s2.c1", 1, 40, 31, 1, 32, 7, 7, 2, 3, 1), "f16"),
+    (L("odd.3x3.c13", 2, 19, 23, 13, 64, 3, 3, 1, 1, 1), "f16"),
+    (L("odd.5x5s2.c7", 1, 30, 41, 7, 40, 5, 5, 2, 2, 1), "bf16"),
+    (L("odd.3x3d2.c20", 1, 26, 27, 20, 96, 3, 3, 1, 2, 2), "f16"),
+    (L("odd.1x1.c24", 1, 26, 27, 23, 32, 1, 1, 1, 0, 1), "f16"),
+    (L("odd.1x1.c25", 1, 26, 27, 25, 32, 1, 1, 1, 0, 1), "f16"),
+    (L("odd.1x1.c300", 1, 26, 27, 300, 72, 1, 1, 1, 0, 1), "bf16"),
+    (L("odd.3x3.k12", 1, 26, 27, 12, 12, 3, 3, 1, 1, 1), "f16"),
+]
+
+
+@pytest.mark.parametrize("layer,dtype", ODD, ids=[l.name for l, _ in ODD])
+def test_channel_counts_without_16_byte_pieces(api, layer, dtype):
+    check_layer(api, layer, dtype, synth.seed_for(0, 640 + layer.C), x_kind="normal")
+    check_layer(api, layer, dtype, synth.seed_for(0, 660 + layer.C), x_kind="normal", dw_f32=True, passes=("wgrad",))
+
+
+def test_forward_without_room_for_the_padded_copies(api):
+    """A workspace too small for the copies is as good as it was before there were any."""
+    layer = L("odd.small-workspace", 1, 21, 25, 6, 40, 3, 3, 1, 1, 1)
+    (x32, xb), (w32, wb), _ = U.conv_inputs(layer, "f16", synth.seed_for(0, 690), "normal")
+    desc = api.desc_from_layer(layer, "f16")
+    ref = oracle.conv_fwd(U.shape_of(layer), x32, w32)
+    for ws in (torch.empty(16, dtype=torch.uint8, device="cuda"), None):
+        y = api.conv2d_fwd(desc, U.to_device(xb, "f16"), U.to_device(wb, "f16"), workspace=ws)
+        assert U.rel_err(U.to_host_f64(y), ref) <= U.TOL["f16"]
+
+
 def test_wgrad_3x3_fused_taps(api):
     # large-image 3x3 filter gradient (all taps per workgroup): ragged strip, ragged channel block, ragged k
     check_layer(api, L("wgrad3x3.ragged", 1, 330, 1000, 40, 72, 3, 3, 1, 1, 1), "bf16", synth.seed_for(0, 700),
