@@ -227,6 +227,9 @@ static hipError_t dispatch(const IgemmArgs &a, hipStream_t stream)
                                                  a.relu, a.Nout, a.resid, stream);
             }
         }
+        static const int use_short = tuning_knob("DLCONV_SHORT", 1); // tuning override: 0 = never
+        // whole reduction in one step: before the choice between ring tiles, which all spend four steps on it
+        if (use_short && b.c_outer && forced_cfg() < 0 && igemm_short_applicable(b)) return launch_igemm_short(b, std::is_same<T, BF16>::value, stream);
         // A ragged last column tile of the widest configuration (e.g. 304 = 256 + 48 output
         // channels) would run mostly empty: give the remainder to a narrower tile instead.
         const int rem = a.Nout % 256;

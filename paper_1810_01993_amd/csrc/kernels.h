@@ -127,6 +127,17 @@ hipError_t launch_igemm(const IgemmArgs &a, bool is_bf16, hipStream_t stream);
 // Direct-to-LDS variant of the engine (needs Cin % 8 == 0); cfg selects the tile.
 hipError_t launch_igemm_dma(const IgemmArgs &a, bool is_bf16, int cfg, hipStream_t stream);
 
+// 1x1 layers with 32 or 64 input channels, more than 64 output channels and many pixels: one 64-channel step (igemm_short.hip).
+// launch_igemm chooses it; c_outer must be set.
+bool igemm_short_applicable(const IgemmArgs &a);
+hipError_t launch_igemm_short(const IgemmArgs &a, bool is_bf16, hipStream_t stream);
+// A residual input that can be fetched 16 bytes per lane like the output is written.
+inline bool resid_prefetchable(const IgemmArgs &a)
+{
+    return a.resid != nullptr && a.ldd % 8 == 0 && a.Nout % 8 == 0 &&
+           ((reinterpret_cast<uintptr_t>(a.D) | reinterpret_cast<uintptr_t>(a.resid)) & 15) == 0;
+}
+
 // Halo-tile variant for stride-1 multi-tap filters.  a.B must point at the
 // blocked filter copy [chunk][tap][a.Nout][32] made by launch_filter_block.
 int igemm_halo_columns(const IgemmArgs &a);

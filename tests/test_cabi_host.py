@@ -195,6 +195,9 @@ def test_describe_names_the_kernels_of_the_decoder_layers(api):
     # filter gradient: large operands that every XCD would fetch for itself keep a slice on one XCD, small ones are dealt
     up = api.ConvDesc(2, 384, 576, 256, 256, 3, 3, 2, 2, 1, 1, 1, 1, api.DL_F16)
     assert api.dl_conv_describe(up, api.PASS_BWD_FILTER).startswith("wgrad_dma_kernel<256,256>[216]")
+    # one-step reductions take their own kernel from 512 tiles of 128 x 128 on
+    for H, name in ((256, "igemm_short_kernel["), (255, "igemm_dma_kernel")):
+        assert api.dl_conv_describe(api.ConvDesc(1, H, 128, 64, 200, 1, 1), api.PASS_FWD).startswith(name)
     low = api.ConvDesc(2, 48, 72, 256, 256, 3, 3, 2, 2, 1, 1, 1, 1, api.DL_F16)
     assert api.dl_conv_describe(low, api.PASS_BWD_FILTER).startswith("wgrad_dma_kernel<128,128>")
     # the query leaves nothing behind: a call after it still validates and reports as before

@@ -217,6 +217,24 @@ def test_stem_data_gradient_kernel(api, layer, dtype):
     check_layer(api, layer, dtype, synth.seed_for(0, 650 + len(layer.name)), x_kind="normal", passes=("dgrad",))
 
 
+# reductions of one step (igemm_short_kernel): from 512 tiles of 128 x 128 on, ragged rows and columns, half a step of
+# channels, strided input pixels (forward) and strided output rows (data gradient)
+SHORT = [
+    (L("short.64-256", 1, 181, 185, 64, 256, 1, 1, 1, 0, 1), "f16", ("fwd",)),
+    (L("short.32-104", 1, 256, 257, 32, 104, 1, 1, 1, 0, 1), "bf16", ("fwd",)),
+    (L("short.64-72s2", 2, 364, 361, 64, 72, 1, 1, 2, 0, 1), "f16", ("fwd",)),
+    (L("short.dgrad.136-64", 1, 181, 185, 136, 64, 1, 1, 1, 0, 1), "f16", ("dgrad",)),
+    (L("short.dgrad.256-32s2", 2, 260, 257, 256, 32, 1, 1, 2, 0, 1), "bf16", ("dgrad",)),
+]
+
+
+@pytest.mark.parametrize("layer,dtype,passes", SHORT, ids=[l.name for l, _, _ in SHORT])
+def test_reductions_of_one_step(api, layer, dtype, passes):
+    which = {"fwd": api.PASS_FWD, "dgrad": api.PASS_BWD_DATA}[passes[0]]
+    assert "igemm_short_kernel" in api.dl_conv_describe(api.desc_from_layer(layer, dtype), which)
+    check_layer(api, layer, dtype, synth.seed_for(0, 700 + layer.C), x_kind="normal", passes=passes)
+
+
 # channel counts that are not a multiple of 8: channel-padded copies (forward, filter gradient), packed rows of the
 # stem's data gradient (odd and even counts, ragged patches), and the reductions on either side of the copies' limit
 ODD = [

@@ -156,6 +156,13 @@ RESIDUAL_CASES = [
     (L("r.would-be-halo3x3.k256", 1, 200, 230, 40, 256, 3, 3, 1, 1, 1), "f16"),
     (L("r.would-be-narrow5x5.k32", 4, 75, 200, 16, 32, 5, 5, 1, 2, 1), "f16"),
     (L("r.would-be-wide5x5.c32.k80", 3, 100, 230, 32, 80, 5, 5, 1, 2, 1), "bf16"),
+    (L("r.dma.k304.c96.remainder", 2, 150, 200, 96, 304, 1, 1, 1, 0, 1), "f16"),
+    # residual fetched ahead of the reduction: ragged rows and columns of each tile shape, and the one-step kernel
+    (L("r.128x128.ragged", 1, 90, 101, 160, 264, 1, 1, 1, 0, 1), "bf16"),
+    (L("r.128x64.ragged", 1, 90, 101, 96, 136, 1, 1, 1, 0, 1), "f16"),
+    (L("r.64x64.ragged", 1, 23, 29, 256, 72, 1, 1, 1, 0, 1), "f16"),
+    (L("r.short.ragged", 1, 181, 185, 64, 200, 1, 1, 1, 0, 1), "f16"),
+    (L("r.short.32.s2", 1, 511, 514, 32, 72, 1, 1, 2, 0, 1), "bf16"),
 ]
 
 
