@@ -200,9 +200,11 @@ bool use_dgrad_stem(const dl_conv_desc *d)
                                       d->dil_h, d->dil_w);
 }
 
-size_t dgrad_workspace(const dl_conv_desc *d, const Geometry &g)
+size_t dgrad_stem_workspace(const dl_conv_desc *d) { return align_up(dlk::dgrad_stem_filter_bytes(d->C, d->K), 256); }
+
+size_t dgrad_workspace(const dl_conv_desc *d, const Geometry &g, bool stem)
 {
-    if (use_dgrad_stem(d)) return align_up(dlk::dgrad_stem_filter_bytes(d->C, d->K), 256);
+    if (stem) return dgrad_stem_workspace(d);
     size_t total = 0;
     for (int ca = 0; ca < d->stride_h; ++ca)
         for (int cb = 0; cb < d->stride_w; ++cb) {
@@ -224,7 +226,9 @@ bool use_wgrad5x5(const dl_conv_desc *d)
                                     d->dil_h, d->dil_w);
 }
 
-dlk::WgradPlan wgrad_plan(const dl_conv_desc *d, const Geometry &g)
+// room: bytes of workspace the plan may use.  A caller that brings fewer bytes than the preferred plan takes (say, the size
+// that an earlier version of the library asked for) gets the plan without the fetch term, whose slices were as few.
+dlk::WgradPlan wgrad_plan(const dl_conv_desc *d, const Geometry &g, size_t room = SIZE_MAX)
 {
     if (use_wgrad5x5(d)) {
         const dlk::WgradStripPlan p5 = dlk::wgrad5x5_make_plan(d->N, d->H, d->W, d->C, d->K);
@@ -235,12 +239,16 @@ dlk::WgradPlan wgrad_plan(const dl_conv_desc *d, const Geometry &g)
         return dlk::WgradPlan{-3, p3.slices, 0};
     }
     const bool thin = dlk::thin_wgrad_applicable(d->K, d->C, d->R, d->S, d->stride_h, d->stride_w, d->pad_h, d->pad_w);
-    return dlk::wgrad_make_plan((int64_t)d->N * g.P * g.Q, g.x_elems, d->K, d->C, d->R * d->S * d->C, thin);
+    const auto plan = [&](bool fetch_term) {
+        return dlk::wgrad_make_plan((int64_t)d->N * g.P * g.Q, g.x_elems, d->K, d->C, d->R * d->S * d->C, thin, fetch_term);
+    };
+    const dlk::WgradPlan best = plan(true);
+    return (size_t)best.splits * (size_t)g.w_elems * sizeof(float) <= room ? best : plan(false);
 }
 
-size_t wgrad_own_workspace(const dl_conv_desc *d, const Geometry &g)
+size_t wgrad_own_workspace(const dl_conv_desc *d, const Geometry &g, size_t room = SIZE_MAX)
 {
-    return (size_t)wgrad_plan(d, g).splits * (size_t)g.w_elems * sizeof(float);
+    return (size_t)wgrad_plan(d, g, room).splits * (size_t)g.w_elems * sizeof(float);
 }
 
 // As fwd_padded_workspace, for the filter gradient: partial sums of the padded filter, then the copy of x.
@@ -350,7 +358,7 @@ dl_status dl_conv_workspace_bytes(const dl_conv_desc *desc, int pass, size_t *by
             *bytes = std::max({plain, igemm_scratch_bytes(a), fwd_padded_workspace(desc, g, false), fwd_padded_workspace(desc, g, true)});
             return DL_OK;
         }
-        case DL_PASS_BWD_DATA: *bytes = dgrad_workspace(desc, g); return DL_OK;
+        case DL_PASS_BWD_DATA: *bytes = dgrad_workspace(desc, g, use_dgrad_stem(desc)); return DL_OK;
         case DL_PASS_BWD_FILTER: *bytes = wgrad_workspace(desc, g); return DL_OK;
     }
     return DL_ERR_UNSUPPORTED;
@@ -423,13 +431,16 @@ dl_status conv2d_bwd_data(const dl_conv_desc *d, const void *dy, const void *w, 
     const dl_status st = check_desc(d, &g);
     if (st != DL_OK) return st;
     if (!aligned16(dy) || !aligned16(w) || !aligned16(dx)) return DL_ERR_ALIGN;
-    const size_t need = dgrad_workspace(d, g);
+    // the stem kernel's filter copy is rounded up to 32 output channels: for channel counts that the general path served
+    // from fewer bytes, those bytes are still enough
+    const bool stem = use_dgrad_stem(d) && (d->C % 8 == 0 || (workspace && workspace_bytes >= dgrad_stem_workspace(d)));
+    const size_t need = dgrad_workspace(d, g, stem);
     if (need > 0 && (!workspace || workspace_bytes < need)) return DL_ERR_WORKSPACE;
     if (need > 0 && !aligned16(workspace)) return DL_ERR_ALIGN;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     const bool bf16 = d->dtype == DL_BF16;
 
-    if (use_dgrad_stem(d)) {
+    if (stem) {
         // few input channels, 7x7 stride 2: all parity classes in one workgroup, operands resident in LDS
         dlk::FilterBlockArgs f{};
         f.src = static_cast<const uint16_t *>(w);
@@ -528,9 +539,9 @@ dl_status conv2d_bwd_data(const dl_conv_desc *d, const void *dy, const void *w, 
 namespace {
 // dw_c: channels of dw itself, smaller than d->C where d describes a channel-padded copy
 dl_status run_wgrad(const dl_conv_desc *d, const Geometry &g, const void *x, const void *dy, void *dw, int dw_c, void *workspace,
-                    hipStream_t stream)
+                    size_t room, hipStream_t stream)
 {
-    const dlk::WgradPlan plan = wgrad_plan(d, g);
+    const dlk::WgradPlan plan = wgrad_plan(d, g, room);
     dlk::WgradArgs a{};
     a.x = static_cast<const uint16_t *>(x);
     a.dy = static_cast<const uint16_t *>(dy);
@@ -575,7 +586,7 @@ dl_status conv2d_bwd_filter(const dl_conv_desc *d, const void *x, const void *dy
     const dl_status st = check_desc(d, &g);
     if (st != DL_OK) return st;
     if (!aligned16(x) || !aligned16(dy) || !aligned16(dw)) return DL_ERR_ALIGN;
-    if (!workspace || workspace_bytes < wgrad_own_workspace(d, g)) return DL_ERR_WORKSPACE;
+    if (!workspace || workspace_bytes < wgrad_own_workspace(d, g, workspace_bytes)) return DL_ERR_WORKSPACE;
     if (!aligned16(workspace)) return DL_ERR_ALIGN;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     const size_t padded = wgrad_padded_workspace(d, g);
@@ -587,9 +598,9 @@ dl_status conv2d_bwd_filter(const dl_conv_desc *d, const void *x, const void *dy
         if (dlk::launch_pad_channels(static_cast<const uint16_t *>(x), reinterpret_cast<uint16_t *>(xp), (int64_t)d->N * d->H * d->W,
                                      nullptr, nullptr, 0, d->C, stream) != hipSuccess)
             return DL_ERR_LAUNCH;
-        return run_wgrad(&e, ge, xp, dy, dw, d->C, workspace, stream);
+        return run_wgrad(&e, ge, xp, dy, dw, d->C, workspace, SIZE_MAX, stream);
     }
-    return run_wgrad(d, g, x, dy, dw, d->C, workspace, stream);
+    return run_wgrad(d, g, x, dy, dw, d->C, workspace, workspace_bytes, stream);
 }
 
 

@@ -233,7 +233,7 @@ static hipError_t launch_cfg(const WgradArgs &a, hipStream_t stream)
     return dlk::launch_status();
 }
 
-WgradPlan wgrad_make_plan(int64_t npix, int64_t x_elems, int K, int C, int RSC, bool thin_ok)
+WgradPlan wgrad_make_plan(int64_t npix, int64_t x_elems, int K, int C, int RSC, bool thin_ok, bool fetch_term)
 {
     static const int forced = tuning_knob("DLCONV_WGRAD_CFG", -2); // tuning override, unset in normal use
     WgradPlan pl{-1, 1, 32, 0};
@@ -299,7 +299,7 @@ WgradPlan wgrad_make_plan(int64_t npix, int64_t x_elems, int K, int C, int RSC, 
             // on their XCDs 152 us; 1.2-1.9x on 21 of 24 such shapes, 0.95-0.97x on three).  Below that size, and with
             // more taps, whose tiles meet in an XCD's L2, dealt slices were fetched at 10-16 TB/s and stayed ahead.
             const double steps_us = rounds * (chunk / 32 + 7) * sh.us_per_step;
-            const bool fetch_bound = spread && RSC / C <= 9 && 2 * (x_elems + npix * K) >= 40000000;
+            const bool fetch_bound = fetch_term && spread && RSC / C <= 9 && 2 * (x_elems + npix * K) >= 40000000;
             const double fetch_us = fetch_bound ? 2.0 * tiles * (sh.bm + sh.bn) * (double)npix / 9e6 : 0.0;
             const double est = 9.0 + std::max(steps_us, fetch_us) + reduce_us;
             if (est < best) {

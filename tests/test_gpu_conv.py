@@ -270,6 +270,33 @@ def test_forward_without_room_for_the_padded_copies(api):
         assert U.rel_err(U.to_host_f64(y), ref) <= U.TOL["f16"]
 
 
+def test_gradients_in_a_smaller_workspace(api):
+    """A filter gradient whose preferred plan takes many slices runs in the room of fewer, a stem's data gradient with an odd
+    channel count in that of the general path; less than that is refused."""
+    # 15 slices at most where the tiles are dealt, 24 in the preferred plan
+    desc = api.ConvDesc(2, 384, 576, 256, 256, 3, 3, 2, 2, 1, 1, 1, 1, api.DL_F16)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(7)
+    x = torch.randn((2, 384, 576, 256), generator=g, device="cuda").half()
+    dy = torch.randn((2, 192, 288, 256), generator=g, device="cuda").half()
+    one = 256 * 9 * 256 * 4
+    assert api.dl_conv_workspace_bytes(desc, api.PASS_BWD_FILTER) > 15 * one
+    full = api.conv2d_bwd_filter(desc, x, dy).float()
+    part = api.conv2d_bwd_filter(desc, x, dy, workspace=torch.empty(15 * one, dtype=torch.uint8, device="cuda")).float()
+    # both are sums of the same products rounded once to fp16 (2^-11 of a value each)
+    assert float((full - part).norm() / full.norm()) <= 2 ** -10
+    with pytest.raises(RuntimeError):
+        api.conv2d_bwd_filter(desc, x, dy, workspace=torch.empty(one, dtype=torch.uint8, device="cuda"))
+    layer = L("stem.c6.k40.small-workspace", 1, 33, 45, 6, 40, 7, 7, 2, 3, 1)
+    _, (w32, wb), (dy32, dyb) = U.conv_inputs(layer, "f16", synth.seed_for(0, 695), "normal")
+    ref = oracle.conv_bwd_data(U.shape_of(layer), dy32, w32)
+    desc = api.desc_from_layer(layer, "f16")
+    for size in (api.dl_conv_workspace_bytes(desc, api.PASS_BWD_DATA), 6 * 49 * 40 * 2 + 4 * 256):
+        ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+        dx = api.conv2d_bwd_data(desc, U.to_device(dyb, "f16"), U.to_device(wb, "f16"), workspace=ws)
+        assert U.rel_err(U.to_host_f64(dx), ref) <= U.TOL["f16"]
+
+
 def test_wgrad_3x3_fused_taps(api):
     # large-image 3x3 filter gradient (all taps per workgroup): ragged strip, ragged channel block, ragged k
     check_layer(api, L("wgrad3x3.ragged", 1, 330, 1000, 40, 72, 3, 3, 1, 1, 1), "bf16", synth.seed_for(0, 700),
