@@ -671,10 +671,12 @@ dl_status bias_relu_bwd(const void *dy, const void *y, int32_t dtype, int64_t n_
     if (n_pixels > 0 && (!dy || (relu && (!y || !dz)))) return DL_ERR_NULL;
     if (dtype != DL_F16 && dtype != DL_BF16) return DL_ERR_DTYPE;
     if (!aligned16(dy) || !aligned16(y) || !aligned16(dz) || (reinterpret_cast<uintptr_t>(dbias) & 3u)) return DL_ERR_ALIGN;
-    const size_t need = (size_t)dlk::tail_bwd_blocks(n_pixels, K) * K * sizeof(float);
-    if (!workspace || workspace_bytes < need) return DL_ERR_WORKSPACE;
+    // a smaller workspace than the query asks for gives longer slabs, down to a least number of them
+    const size_t row = (size_t)K * sizeof(float);
+    if (!workspace || workspace_bytes < dlk::tail_bwd_least_blocks(n_pixels, K) * row) return DL_ERR_WORKSPACE;
     if (!aligned16(workspace)) return DL_ERR_ALIGN;
     dlk::TailBwdArgs a{};
+    a.rows = (int32_t)std::min<size_t>(dlk::tail_bwd_blocks(n_pixels, K), workspace_bytes / row);
     a.dy = static_cast<const uint16_t *>(dy);
     a.y = static_cast<const uint16_t *>(y);
     a.dz = static_cast<uint16_t *>(dz);

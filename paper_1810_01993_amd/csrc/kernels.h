@@ -264,15 +264,17 @@ hipError_t launch_splitk_reduce_tail(const float *partial, int32_t splits, int64
                                      const float *bias, int32_t relu, int32_t ncols, const uint16_t *resid, hipStream_t stream);
 
 // Backward of the point-wise tail y = max(s + bias, 0): dz = dy masked by y > 0 (relu != 0;
-// otherwise dz and y are not touched), dbias = column sums of dz.  partial: blocks x K floats.
+// otherwise dz and y are not touched), dbias = column sums of dz.  partial: rows x K floats, rows between
+// tail_bwd_least_blocks and tail_bwd_blocks (preferred).
 struct TailBwdArgs {
     const uint16_t *dy, *y;     // [npix][K]
     uint16_t *dz;
     float *partial, *dbias;
     int64_t npix, chunk;        // chunk: pixels per workgroup (set by the launcher)
-    int32_t K, relu;
+    int32_t K, relu, rows;
 };
 int tail_bwd_blocks(int64_t npix, int K);
+int tail_bwd_least_blocks(int64_t npix, int K);
 hipError_t launch_tail_bwd(const TailBwdArgs &a, bool is_bf16, hipStream_t stream);
 
 // LARC update of up to LARC_MAX tensors (see larc.hip).  partial: 2 * LARC_SLICES floats per tensor

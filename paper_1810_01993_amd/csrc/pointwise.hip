@@ -138,10 +138,21 @@ int tail_bwd_blocks(int64_t npix, int K)
     return (int)(b > 1024 ? 1024 : b);
 }
 
+// The fewest rows the entry point takes a workspace for: about 32 pixels per thread of workgroups that hold up to
+// 2048 channels (256 without 16-byte pieces), which is what a workspace query answered before slabs became shorter.
+int tail_bwd_least_blocks(int64_t npix, int K)
+{
+    const int blocks = tail_bwd_blocks(npix, K), vec = K % 8 == 0 ? 8 : 1;
+    const int64_t groups = (K + vec - 1) / vec, slab = TB_THREADS / (groups < TB_THREADS ? groups : TB_THREADS) * 32;
+    const int64_t b = (npix + slab - 1) / slab;
+    return b < 1 ? 1 : b < blocks ? (int)b : blocks;
+}
+
 hipError_t launch_tail_bwd(const TailBwdArgs &a0, bool is_bf16, hipStream_t stream)
 {
     TailBwdArgs a = a0;
-    const int blocks = tail_bwd_blocks(a.npix, a.K);
+    const int blocks = a.rows;
+    if (blocks < 1) return hipErrorInvalidValue;
     a.chunk = (a.npix + blocks - 1) / blocks;
     if (a.chunk < 1) a.chunk = 1;
     const int vec = a.K % 8 == 0 ? 8 : 1;

@@ -21,14 +21,15 @@ def api():
     return _api
 
 
-def _run(api, n, K, dtype, seed, relu=True, alias=False):
+def _run(api, n, K, dtype, seed, relu=True, alias=False, workspace=None):
     print(f"[case] bias_relu_bwd n={n} K={K} {dtype} relu={relu} alias={alias} seed={seed}", flush=True)
     sys.stdout.flush()
     dy32, dyb = synth.quantize(synth.normal(seed, (n, K)), dtype)
     # a forward output: about half of it cut to exactly zero (also -0 never appears after a ReLU)
     y32, yb = synth.quantize(np.maximum(synth.normal(seed + 1, (n, K)), 0.0), dtype)
     dyd, yd = U.to_device(dyb, dtype), U.to_device(yb, dtype)
-    dz, db = api.bias_relu_bwd(dyd, yd if relu else None, relu, dz=dyd if (alias and relu) else None)
+    dz, db = api.bias_relu_bwd(dyd, yd if relu else None, relu, dz=dyd if (alias and relu) else None,
+                               workspace=workspace)
     torch.cuda.synchronize()
     ref_dz, ref_db = E.bias_relu_bwd(dy32, y32, relu)
     got_dz = U.to_host_f64(dz)
@@ -65,6 +66,20 @@ def test_without_relu_in_place_and_repeatable(api):
     a = _run(api, 3001, 72, "bf16", synth.seed_for(0, 1591), alias=True)
     b = _run(api, 3001, 72, "bf16", synth.seed_for(0, 1591), alias=True)
     assert torch.equal(a, b)
+
+
+# (pixels, channels, partial rows): workspaces of the sizes that the query answered before slabs became shorter
+SMALL_WORKSPACES = [(6912, 256, 27), (6912, 1024, 108), (3015, 256, 12), (11059, 64, 11), (5000, 12, 8), (2048, 264, 10)]
+
+
+@pytest.mark.parametrize("n,K,rows", SMALL_WORKSPACES, ids=[f"{n}x{K}" for n, K, _ in SMALL_WORKSPACES])
+def test_smaller_workspace(api, n, K, rows):
+    """Fewer partial rows than the preferred number give the same sums, in nothing beyond the bytes given; less is refused."""
+    buf, ws = U.guarded_workspace(rows * K * 4)
+    _run(api, n, K, "bf16", synth.seed_for(0, 1580 + rows % 7), workspace=ws)
+    assert U.workspace_guards_intact(buf, rows * K * 4)
+    with pytest.raises(RuntimeError):
+        _run(api, n, K, "bf16", synth.seed_for(0, 1580 + rows % 7), workspace=ws[:-16])
 
 
 def test_decoder_sized_tensor(api):
