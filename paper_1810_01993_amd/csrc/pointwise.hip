@@ -17,6 +17,8 @@
 // pixels to itself, which put 27 workgroups on the smallest of these): 6912 x 1024 32.0 -> 11.6 us (3.7 TB/s),
 // 6912 x 256 21.2 -> 5.3 us, 110592 x 256 48.3 -> 32.3 us (5.3 TB/s), 110592 x 64 25.8 -> 13.7 us.
 // dz is stored without the non-temporal hint of the loads: the convolution gradients read it next.
+#include <type_traits>
+
 #include "device_common.h"
 #include "kernels.h"
 
@@ -24,15 +26,27 @@ namespace dlk {
 
 constexpr int TB_THREADS = 256;
 
-// How the [npix][K] tensor is dealt to workgroups: gpb channel groups x lanes pixel lanes per workgroup.
-struct TailBwdShape { int groups, gpb, lanes; };
-static __host__ __device__ __forceinline__ TailBwdShape tail_bwd_shape(int K, int vec)
+// How the [npix][K] tensor is dealt to workgroups: columns of workgroups side by side, gpb channel groups x lanes
+// pixel lanes in each.
+struct TailBwdShape { int groups, columns, gpb, lanes; };
+static TailBwdShape tail_bwd_split(int K, int vec, int cap, bool even)
 {
     TailBwdShape s;
     s.groups = (K + vec - 1) / vec;
-    s.gpb = s.groups < TB_THREADS / vec ? s.groups : TB_THREADS / vec;
+    s.columns = (s.groups + cap - 1) / cap;
+    s.gpb = even ? (s.groups + s.columns - 1) / s.columns : s.groups < cap ? s.groups : cap;
     s.lanes = TB_THREADS / s.gpb;
     return s;
+}
+
+// Without 16-byte pieces a workgroup of 256 channels has one pixel lane: from 4 M elements on it covers at most 64
+// (four and more lanes), and consecutive workgroups of an XCD take the columns of one slab side by side, so that the
+// pieces of a 128-byte line that two of them write meet in its L2.  Measured (ReLU, against 256 channels):
+// 442368 x 257 559 -> 330 us, 1000000 x 100 357 -> 199 us; below the line 3015 x 257 8.8 us, 9.4 with 64.
+static TailBwdShape tail_bwd_shape(int64_t npix, int K)
+{
+    if (K % 8 == 0) return tail_bwd_split(K, 8, TB_THREADS / 8, false);
+    return npix * K < (1 << 22) ? tail_bwd_split(K, 1, TB_THREADS, false) : tail_bwd_split(K, 1, 64, true);
 }
 
 template <class T, int VEC>
@@ -40,18 +54,32 @@ __global__ __launch_bounds__(TB_THREADS) void tail_bwd_kernel(const TailBwdArgs 
 {
     __shared__ __align__(16) float red[TB_THREADS * VEC];
     __shared__ float part[TB_THREADS];
-    const TailBwdShape sh = tail_bwd_shape(p.K, VEC);
-    const int gl = threadIdx.x % sh.gpb, pl = threadIdx.x / sh.gpb;
-    const int g = blockIdx.y * sh.gpb + gl;
-    const bool active = pl < sh.lanes && g < sh.groups;
+    int slab = blockIdx.x, column = blockIdx.y;
+    if (p.interleave) {                                             // one row of the grid: see tail_bwd_shape
+        const int slot = blockIdx.x / 8;
+        column = slot % p.columns;
+        slab = slot / p.columns * 8 + blockIdx.x % 8;
+        if (slab >= p.rows) return;                                 // the whole workgroup
+    }
+    const int gl = threadIdx.x % p.gpb, pl = threadIdx.x / p.gpb;
+    const int g = column * p.gpb + gl;
+    const bool active = pl < p.lanes && g < p.groups;
     const int k0 = g * VEC;
-    const int64_t begin = (int64_t)blockIdx.x * p.chunk, end = min(p.npix, begin + p.chunk);
+    const int64_t begin = (int64_t)slab * p.chunk, end = min(p.npix, begin + p.chunk);
     float sum[VEC];
 #pragma unroll
     for (int e = 0; e < VEC; ++e) sum[e] = 0.f;
     if (active) {
-        if constexpr (VEC == 8) {
-            auto one = [&](u32x4_t gv, u32x4_t yv, size_t off) {
+        using Piece = std::conditional_t<VEC == 8, u32x4_t, uint16_t>;
+        // (an element's line is read by many threads, at different times: the hint that it is not needed again is for
+        // whole pieces only)
+        auto load = [&](const uint16_t *src, size_t off) {
+            const Piece *q = reinterpret_cast<const Piece *>(src + off);
+            if constexpr (VEC == 8) return __builtin_nontemporal_load(q);
+            else return *q;
+        };
+        auto one = [&](Piece gv, Piece yv, size_t off) {
+            if constexpr (VEC == 8) {
                 if (p.relu) {
 #pragma unroll
                     for (int d = 0; d < 4; ++d) {
@@ -59,82 +87,76 @@ __global__ __launch_bounds__(TB_THREADS) void tail_bwd_kernel(const TailBwdArgs 
                         const uint32_t hi = T::to_float((uint16_t)(yv[d] >> 16)) > 0.f ? 0xffff0000u : 0u;
                         gv[d] &= lo | hi;
                     }
-                    *reinterpret_cast<u32x4_t *>(p.dz + off) = gv;
+                    *reinterpret_cast<Piece *>(p.dz + off) = gv;
                 }
 #pragma unroll
                 for (int d = 0; d < 4; ++d) {
                     sum[2 * d] += T::to_float((uint16_t)(gv[d] & 0xffffu));
                     sum[2 * d + 1] += T::to_float((uint16_t)(gv[d] >> 16));
                 }
-            };
-            auto load = [&](const uint16_t *src, size_t off) {
-                return __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(src + off));
-            };
-            const size_t step = (size_t)sh.lanes * p.K;
-            size_t off = (size_t)(begin + pl) * p.K + k0;
-            int64_t i = begin + pl;
-            for (; i + 3 * sh.lanes < end; i += 4 * sh.lanes, off += 4 * step) {
-                u32x4_t gv[4], yv[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) gv[u] = load(p.dy, off + u * step);
+            } else {
                 if (p.relu) {
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) yv[u] = load(p.y, off + u * step);
-                } else {
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) yv[u] = u32x4_t{0, 0, 0, 0};
+                    if (!(T::to_float(yv) > 0.f)) gv = 0;
+                    p.dz[off] = gv;
                 }
+                sum[0] += T::to_float(gv);
+            }
+        };
+        const size_t step = (size_t)p.lanes * p.K;
+        size_t off = (size_t)(begin + pl) * p.K + k0;
+        int64_t i = begin + pl;
+        for (; i + 3 * p.lanes < end; i += 4 * p.lanes, off += 4 * step) {
+            Piece gv[4], yv[4];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) one(gv[u], yv[u], off + u * step);
+            for (int u = 0; u < 4; ++u) gv[u] = load(p.dy, off + u * step);
+            if (p.relu) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) yv[u] = load(p.y, off + u * step);
+            } else {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) yv[u] = Piece{};
             }
-            for (; i < end; i += sh.lanes, off += step) {
-                const u32x4_t gv = load(p.dy, off);
-                one(gv, p.relu ? load(p.y, off) : u32x4_t{0, 0, 0, 0}, off);
-            }
-        } else {
-            for (int64_t i = begin + pl; i < end; i += sh.lanes) {
-                const size_t off = (size_t)i * p.K + k0;
-                uint16_t v = p.dy[off];
-                if (p.relu) {
-                    if (!(T::to_float(p.y[off]) > 0.f)) v = 0;
-                    p.dz[off] = v;
-                }
-                sum[0] += T::to_float(v);
-            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) one(gv[u], yv[u], off + u * step);
+        }
+        for (; i < end; i += p.lanes, off += step) {
+            const Piece gv = load(p.dy, off);
+            one(gv, p.relu ? load(p.y, off) : Piece{}, off);
         }
     }
-    // Pixel lanes of a column, added in a fixed order: the columns of the workgroup are dealt to the threads,
-    // `parts` threads per column with a contiguous range of pixel lanes each, then the parts in ascending order.
-    const int cols = sh.gpb * VEC;                                  // <= TB_THREADS
-    if (pl < sh.lanes) {
+    // Pixel lanes of a channel, added in a fixed order: the channels of the workgroup are dealt to the threads,
+    // up to 16 threads per channel with a contiguous range of pixel lanes each, then those parts in ascending order.
+    const int cols = p.gpb * VEC;                                   // <= TB_THREADS
+    if (pl < p.lanes) {
 #pragma unroll
         for (int e = 0; e < VEC; ++e) red[threadIdx.x * VEC + e] = sum[e];      // row pl, column gl * VEC + e
     }
     __syncthreads();
-    const int parts = TB_THREADS / cols, per = (sh.lanes + parts - 1) / parts;
+    const int parts = min(16, TB_THREADS / cols), per = (p.lanes + parts - 1) / parts;
     const int col = threadIdx.x % cols, q = threadIdx.x / cols;
     float s = 0.f;
     if (q < parts)
-        for (int l = q * per; l < min(sh.lanes, (q + 1) * per); ++l) s += red[l * cols + col];
+        for (int l = q * per; l < min(p.lanes, (q + 1) * per); ++l) s += red[l * cols + col];
     part[threadIdx.x] = s;
     __syncthreads();
-    const int k = blockIdx.y * cols + col;
+    const int k = column * cols + col;
     if (q == 0 && k < p.K) {
         for (int r = 1; r < parts; ++r) s += part[r * cols + col];
-        p.partial[(size_t)blockIdx.x * p.K + k] = s;
+        p.partial[(size_t)slab * p.K + k] = s;
     }
 }
 
-// Partial rows (workgroups along the pixels): four pixels per thread while that gives no more than about 1024
-// workgroups, then longer slabs, and at most 1024 rows for the reduce kernel.
+// Partial rows (workgroups along the pixels): four pixels per thread of workgroups that cover at most 256 channels
+// while that gives no more than about 1024 workgroups, then longer slabs, and at most 1024 rows for the reduce kernel.
 int tail_bwd_blocks(int64_t npix, int K)
 {
     if (npix <= 0) return 1;
-    const TailBwdShape s = tail_bwd_shape(K, K % 8 == 0 ? 8 : 1);
-    const int64_t columns = (s.groups + s.gpb - 1) / s.gpb;
-    int64_t per = npix * columns / ((int64_t)s.lanes * 1024);        // pixels per thread
+    const int vec = K % 8 == 0 ? 8 : 1, groups = (K + vec - 1) / vec;
+    const int gpb = groups < TB_THREADS / vec ? groups : TB_THREADS / vec, lanes = TB_THREADS / gpb;
+    const int64_t columns = (groups + gpb - 1) / gpb;
+    int64_t per = npix * columns / ((int64_t)lanes * 1024);          // pixels per thread
     per = per < 4 ? 4 : (per + 3) / 4 * 4;
-    const int64_t b = (npix + s.lanes * per - 1) / (s.lanes * per);
+    const int64_t b = (npix + lanes * per - 1) / (lanes * per);
     return (int)(b > 1024 ? 1024 : b);
 }
 
@@ -155,10 +177,16 @@ hipError_t launch_tail_bwd(const TailBwdArgs &a0, bool is_bf16, hipStream_t stre
     if (blocks < 1) return hipErrorInvalidValue;
     a.chunk = (a.npix + blocks - 1) / blocks;
     if (a.chunk < 1) a.chunk = 1;
-    const int vec = a.K % 8 == 0 ? 8 : 1;
-    const TailBwdShape s = tail_bwd_shape(a.K, vec);
-    const dim3 grid((unsigned)blocks, (unsigned)((s.groups + s.gpb - 1) / s.gpb)), block(TB_THREADS);
-    if (vec == 8) {
+    const TailBwdShape s = tail_bwd_shape(a.npix, a.K);
+    a.groups = s.groups;
+    a.columns = s.columns;
+    a.gpb = s.gpb;
+    a.lanes = s.lanes;
+    a.interleave = s.columns > 1 && a.K % 8 != 0 && a.npix * a.K >= 1 << 22;
+    const int64_t wgs = a.interleave ? (int64_t)(blocks + 7) / 8 * 8 * s.columns : blocks;
+    if (wgs > 0x7fffffff) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)wgs, a.interleave ? 1u : (unsigned)s.columns), block(TB_THREADS);
+    if (a.K % 8 == 0) {
         if (is_bf16) DLK_LAUNCH("tail_bwd_kernel", (tail_bwd_kernel<BF16, 8>), grid, block, 0, stream, a);
         else DLK_LAUNCH("tail_bwd_kernel", (tail_bwd_kernel<F16, 8>), grid, block, 0, stream, a);
     } else {

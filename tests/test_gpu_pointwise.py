@@ -61,6 +61,16 @@ def test_column_blocks_and_slab_edges(api, n, K):
     _run(api, n, K, "f16", synth.seed_for(0, 1540 + (n + K) % 37))
 
 
+# element-wise channel counts: workgroups of up to 256 channels below 4 M elements, interleaved columns of at most 64 from
+# there on (last slab group short of eight, last column short), and a few channels with many pixel lanes
+ELEMENTS = [(1, 1), (4097, 1), (9001, 2), (16383, 257), (16385, 257), (70001, 60), (33011, 129), (2800, 1501), (3, 300)]
+
+
+@pytest.mark.parametrize("n,K", ELEMENTS, ids=[f"{n}x{K}" for n, K in ELEMENTS])
+def test_element_wise_columns(api, n, K):
+    _run(api, n, K, "f16" if n % 2 else "bf16", synth.seed_for(0, 1560 + (n + K) % 17))
+
+
 def test_without_relu_in_place_and_repeatable(api):
     _run(api, 3001, 72, "f16", synth.seed_for(0, 1590), relu=False)
     a = _run(api, 3001, 72, "bf16", synth.seed_for(0, 1591), alias=True)
