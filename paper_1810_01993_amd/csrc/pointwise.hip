@@ -10,9 +10,8 @@
 // in a fixed order through LDS, every workgroup writes one fp32 partial row, and the ordered
 // reduce kernel adds the rows: the result does not depend on timing.
 //
-// Bound by memory once enough loads are in flight: a workgroup covers at most 256 channels
-// (so it has at least eight pixel lanes of 16-byte pieces; wider tensors are cut into column blocks,
-// grid.y), a thread has four pixels' loads in flight, and on small maps it gets no more than those four
+// Bound by memory once enough loads are in flight: a workgroup covers at most 256 channels where they are
+// whole 128-byte lines (so it has at least eight pixel lanes of 16-byte pieces; see tail_bwd_shape), a thread has four pixels' loads in flight, and on small maps it gets no more than those four
 // pixels.  Measured (fp16 / bf16, before -> after; before, a thread had two pixels in flight and at least 32
 // pixels to itself, which put 27 workgroups on the smallest of these): 6912 x 1024 32.0 -> 11.6 us (3.7 TB/s),
 // 6912 x 256 21.2 -> 5.3 us, 110592 x 256 48.3 -> 32.3 us (5.3 TB/s), 110592 x 64 25.8 -> 13.7 us.
@@ -43,9 +42,16 @@ static TailBwdShape tail_bwd_split(int K, int vec, int cap, bool even)
 // (four and more lanes), and consecutive workgroups of an XCD take the columns of one slab side by side, so that the
 // pieces of a 128-byte line that two of them write meet in its L2.  Measured (ReLU, against 256 channels):
 // 442368 x 257 559 -> 330 us, 1000000 x 100 357 -> 199 us; below the line 3015 x 257 8.8 us, 9.4 with 64.
+//
+// With 16-byte pieces a column is 256 channels wide where they are whole 128-byte lines (K % 64 == 0), and on tensors of
+// less than 16 M elements.  Other rows share lines with their neighbours wherever they are cut: up to 512 channels they
+// are not cut, wider ones into columns of at most 512 channels, interleaved as above.  Measured (fp16, ReLU; columns of
+// 256 channels -> now): 884736 x 304 481 -> 330 us (4.9 TB/s), 442368 x 520 430 -> 345 us, 110592 x 520 89 -> 74 us,
+// 442368 x 1160 936 -> 789 us; below the line 3015 x 304 8.7 us, 9.3 with one column.
 static TailBwdShape tail_bwd_shape(int64_t npix, int K)
 {
-    if (K % 8 == 0) return tail_bwd_split(K, 8, TB_THREADS / 8, false);
+    if (K % 64 == 0 || (K % 8 == 0 && npix * K < (1 << 24))) return tail_bwd_split(K, 8, TB_THREADS / 8, false);
+    if (K % 8 == 0) return tail_bwd_split(K, 8, 64, true);
     return npix * K < (1 << 22) ? tail_bwd_split(K, 1, TB_THREADS, false) : tail_bwd_split(K, 1, 64, true);
 }
 
@@ -126,12 +132,21 @@ __global__ __launch_bounds__(TB_THREADS) void tail_bwd_kernel(const TailBwdArgs 
     }
     // Pixel lanes of a channel, added in a fixed order: the channels of the workgroup are dealt to the threads,
     // up to 16 threads per channel with a contiguous range of pixel lanes each, then those parts in ascending order.
-    const int cols = p.gpb * VEC;                                   // <= TB_THREADS
+    const int cols = p.gpb * VEC;
     if (pl < p.lanes) {
 #pragma unroll
         for (int e = 0; e < VEC; ++e) red[threadIdx.x * VEC + e] = sum[e];      // row pl, column gl * VEC + e
     }
     __syncthreads();
+    if (cols > TB_THREADS) {                                        // up to seven pixel lanes: a thread adds whole channels
+        for (int col = threadIdx.x; col < cols; col += TB_THREADS) {
+            const int k = column * cols + col;
+            float s = 0.f;
+            for (int l = 0; l < p.lanes; ++l) s += red[l * cols + col];
+            if (k < p.K) p.partial[(size_t)slab * p.K + k] = s;
+        }
+        return;
+    }
     const int parts = min(16, TB_THREADS / cols), per = (p.lanes + parts - 1) / parts;
     const int col = threadIdx.x % cols, q = threadIdx.x / cols;
     float s = 0.f;
@@ -182,7 +197,7 @@ hipError_t launch_tail_bwd(const TailBwdArgs &a0, bool is_bf16, hipStream_t stre
     a.columns = s.columns;
     a.gpb = s.gpb;
     a.lanes = s.lanes;
-    a.interleave = s.columns > 1 && a.K % 8 != 0 && a.npix * a.K >= 1 << 22;
+    a.interleave = s.columns > 1 && a.K % 64 != 0 && a.npix * a.K >= (a.K % 8 == 0 ? 1 << 24 : 1 << 22);
     const int64_t wgs = a.interleave ? (int64_t)(blocks + 7) / 8 * 8 * s.columns : blocks;
     if (wgs > 0x7fffffff) return hipErrorInvalidValue;
     const dim3 grid((unsigned)wgs, a.interleave ? 1u : (unsigned)s.columns), block(TB_THREADS);

@@ -71,6 +71,16 @@ def test_element_wise_columns(api, n, K):
     _run(api, n, K, "f16" if n % 2 else "bf16", synth.seed_for(0, 1560 + (n + K) % 17))
 
 
+# rows that are not whole 128-byte lines, from 16 M elements on: up to 512 channels in one column, wider ones interleaved
+# (last slab group short of eight, last column short); below that and with whole lines columns of 256 channels
+PIECES = [(33289, 504), (55190, 304), (32300, 520), (14503, 1160), (16289, 1032), (4100, 4104), (77, 328), (1000, 576)]
+
+
+@pytest.mark.parametrize("n,K", PIECES, ids=[f"{n}x{K}" for n, K in PIECES])
+def test_columns_of_16_byte_pieces(api, n, K):
+    _run(api, n, K, "bf16" if n % 2 else "f16", synth.seed_for(0, 1570 + (n + K) % 17), relu=n != 16289)
+
+
 def test_without_relu_in_place_and_repeatable(api):
     _run(api, 3001, 72, "f16", synth.seed_for(0, 1590), relu=False)
     a = _run(api, 3001, 72, "bf16", synth.seed_for(0, 1591), alias=True)
