@@ -15,7 +15,9 @@
 // pixels.  Measured (fp16 / bf16, before -> after; before, a thread had two pixels in flight and at least 32
 // pixels to itself, which put 27 workgroups on the smallest of these): 6912 x 1024 32.0 -> 11.6 us (3.7 TB/s),
 // 6912 x 256 21.2 -> 5.3 us, 110592 x 256 48.3 -> 32.3 us (5.3 TB/s), 110592 x 64 25.8 -> 13.7 us.
-// dz is stored without the non-temporal hint of the loads: the convolution gradients read it next.
+// dz is stored without the non-temporal hint of the loads, since the convolution gradients read it next, unless it
+// exceeds what the last-level cache (256 MB) could keep of it: 884736 x 256 (453 MB) 273 us without, 263 with;
+// 442368 x 256 (226 MB) 119 and 135.
 #include <type_traits>
 
 #include "device_common.h"
@@ -55,7 +57,7 @@ static TailBwdShape tail_bwd_shape(int64_t npix, int K)
     return npix * K < (1 << 22) ? tail_bwd_split(K, 1, TB_THREADS, false) : tail_bwd_split(K, 1, 64, true);
 }
 
-template <class T, int VEC>
+template <class T, int VEC, bool STREAM>
 __global__ __launch_bounds__(TB_THREADS) void tail_bwd_kernel(const TailBwdArgs p)
 {
     __shared__ __align__(16) float red[TB_THREADS * VEC];
@@ -93,7 +95,8 @@ __global__ __launch_bounds__(TB_THREADS) void tail_bwd_kernel(const TailBwdArgs 
                         const uint32_t hi = T::to_float((uint16_t)(yv[d] >> 16)) > 0.f ? 0xffff0000u : 0u;
                         gv[d] &= lo | hi;
                     }
-                    *reinterpret_cast<Piece *>(p.dz + off) = gv;
+                    if constexpr (STREAM) __builtin_nontemporal_store(gv, reinterpret_cast<Piece *>(p.dz + off));
+                    else *reinterpret_cast<Piece *>(p.dz + off) = gv;
                 }
 #pragma unroll
                 for (int d = 0; d < 4; ++d) {
@@ -201,12 +204,16 @@ hipError_t launch_tail_bwd(const TailBwdArgs &a0, bool is_bf16, hipStream_t stre
     const int64_t wgs = a.interleave ? (int64_t)(blocks + 7) / 8 * 8 * s.columns : blocks;
     if (wgs > 0x7fffffff) return hipErrorInvalidValue;
     const dim3 grid((unsigned)wgs, a.interleave ? 1u : (unsigned)s.columns), block(TB_THREADS);
-    if (a.K % 8 == 0) {
-        if (is_bf16) DLK_LAUNCH("tail_bwd_kernel", (tail_bwd_kernel<BF16, 8>), grid, block, 0, stream, a);
-        else DLK_LAUNCH("tail_bwd_kernel", (tail_bwd_kernel<F16, 8>), grid, block, 0, stream, a);
+    const bool stream_dz = a.npix * a.K * 2 > 300000000 && !a.interleave;     // (cut lines have to meet in the L2)
+    if (a.K % 8 == 0 && stream_dz) {
+        if (is_bf16) DLK_LAUNCH("tail_bwd_kernel", (tail_bwd_kernel<BF16, 8, true>), grid, block, 0, stream, a);
+        else DLK_LAUNCH("tail_bwd_kernel", (tail_bwd_kernel<F16, 8, true>), grid, block, 0, stream, a);
+    } else if (a.K % 8 == 0) {
+        if (is_bf16) DLK_LAUNCH("tail_bwd_kernel", (tail_bwd_kernel<BF16, 8, false>), grid, block, 0, stream, a);
+        else DLK_LAUNCH("tail_bwd_kernel", (tail_bwd_kernel<F16, 8, false>), grid, block, 0, stream, a);
     } else {
-        if (is_bf16) DLK_LAUNCH("tail_bwd_kernel", (tail_bwd_kernel<BF16, 1>), grid, block, 0, stream, a);
-        else DLK_LAUNCH("tail_bwd_kernel", (tail_bwd_kernel<F16, 1>), grid, block, 0, stream, a);
+        if (is_bf16) DLK_LAUNCH("tail_bwd_kernel", (tail_bwd_kernel<BF16, 1, false>), grid, block, 0, stream, a);
+        else DLK_LAUNCH("tail_bwd_kernel", (tail_bwd_kernel<F16, 1, false>), grid, block, 0, stream, a);
     }
     hipError_t e = dlk::launch_status();
     if (e != hipSuccess) return e;

@@ -107,6 +107,11 @@ def test_decoder_sized_tensor(api):
     _run(api, 768 * 1152, 256, "f16", synth.seed_for(0, 1595))
 
 
+def test_tensor_beyond_the_last_level_cache(api):
+    # 301 MB of dz: stored past the caches (299 MB, the other side of the line, is as test_decoder_sized_tensor)
+    _run(api, 294001, 512, "bf16", synth.seed_for(0, 1596))
+
+
 def test_empty(api):
     dy = torch.empty((0, 16), dtype=torch.float16, device="cuda")
     dz, db = api.bias_relu_bwd(dy, dy.clone(), True)
