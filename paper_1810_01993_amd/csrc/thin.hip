@@ -344,13 +344,29 @@ __global__ __launch_bounds__(256) void thin_wgrad_kernel(const WgradArgs p)
         }
     }
     float *out = p.partial + (size_t)blockIdx.x * KK * p.C;
+    // Pixel lanes of a channel, added in a fixed order.  Up to 256 channels: up to 16 threads per channel, each adding a
+    // contiguous range of the lanes, then those parts in ascending order (with one thread per channel a filter of
+    // 3 x 8 channels, 256 lanes, spent 70 us here; layers of a few channels come this way on channel-padded copies:
+    // 2 x 176 x 189 x 1 -> 2 65 -> 10 us in all).
+    const int cols = 8 * groups, parts = cols <= 256 ? min(16, 256 / cols) : 1, per = (lanes + parts - 1) / parts;
+    const int col = threadIdx.x % cols, q = threadIdx.x / cols;
 #pragma unroll
     for (int k = 0; k < KK; ++k) {
         __syncthreads();
 #pragma unroll
         for (int e = 0; e < 8; ++e) red[threadIdx.x * 8 + e] = (pl < lanes) ? acc[k][e] : 0.f;
         __syncthreads();
-        if (pl == 0) {
+        if (cols <= 256) {                                // uniform
+            float s = 0.f;
+            if (q < parts)
+                for (int l = q * per; l < min(lanes, (q + 1) * per); ++l) s += red[l * cols + col];
+            sdy[threadIdx.x] = s;                        // dy is no longer needed; the barrier of the next k guards it
+            __syncthreads();
+            if (q == 0) {
+                for (int r = 1; r < parts; ++r) s += sdy[r * cols + col];
+                out[(size_t)k * p.C + col] = s;
+            }
+        } else if (pl == 0) {
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 float s = 0.f;

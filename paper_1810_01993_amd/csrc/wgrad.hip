@@ -390,6 +390,9 @@ hipError_t launch_splitk_reduce_padded(const float *partial, int32_t splits, int
 {
     if (rows <= 0) return hipSuccess;
     if (C < 1 || Cp < C) return hipErrorInvalidValue;
+    // few outputs of many slices: as in launch_splitk_reduce_tail, where each of 4 groups would add hundreds of slices in turn
+    if (splits >= 128 && rows * Cp <= 8192)
+        return launch_reduce_g<32>(partial, splits, rows * Cp, out, out_dtype, nullptr, 0, 1, nullptr, stream, C, Cp);
     return launch_reduce_g<4>(partial, splits, rows * Cp, out, out_dtype, nullptr, 0, 1, nullptr, stream, C, Cp);
 }
 

@@ -259,6 +259,27 @@ def test_channel_counts_without_16_byte_pieces(api, layer, dtype):
     check_layer(api, layer, dtype, synth.seed_for(0, 660 + layer.C), x_kind="normal", dw_f32=True, passes=("wgrad",))
 
 
+# 1x1 layers with 1..4 output channels: the streaming filter gradient with few channel groups, i.e. many pixel lanes (16 parts
+# of them, one part, no parts), on the channel-padded copy and on x itself; from 128 slices on the reduce kernel of 32 groups
+THIN_FILTERS = [
+    (L("thin.c1.k3", 2, 61, 43, 1, 3, 1, 1, 1, 0, 1), "f16", "pad_channels_kernel"),
+    (L("thin.c6.k1", 1, 260, 170, 6, 1, 1, 1, 1, 0, 1), "bf16", "splitk_reduce_kernel<32>"),
+    (L("thin.c12.k4", 1, 19, 23, 12, 4, 1, 1, 1, 0, 1), "f16", "pad_channels_kernel"),
+    (L("thin.c60.k2", 1, 100, 81, 60, 2, 1, 1, 1, 0, 1), "bf16", "pad_channels_kernel"),
+    (L("thin.c250.k3", 2, 130, 140, 250, 3, 1, 1, 1, 0, 1), "f16", "splitk_reduce_kernel<32>"),
+    (L("thin.c8.k3", 1, 50, 77, 8, 3, 1, 1, 1, 0, 1), "bf16", "thin_wgrad_kernel"),
+    (L("thin.c264.k3", 1, 30, 41, 264, 3, 1, 1, 1, 0, 1), "f16", "thin_wgrad_kernel"),
+]
+
+
+@pytest.mark.parametrize("layer,dtype,kernel", THIN_FILTERS, ids=[l.name for l, _, _ in THIN_FILTERS])
+def test_filter_gradient_of_few_outputs(api, layer, dtype, kernel):
+    text = api.dl_conv_describe(api.desc_from_layer(layer, dtype), api.PASS_BWD_FILTER)
+    assert kernel in text and "thin_wgrad_kernel" in text
+    check_layer(api, layer, dtype, synth.seed_for(0, 670 + layer.C), x_kind="normal", passes=("wgrad",))
+    check_layer(api, layer, dtype, synth.seed_for(0, 675 + layer.C), x_kind="normal", dw_f32=True, passes=("wgrad",))
+
+
 def test_forward_without_room_for_the_padded_copies(api):
     """A workspace too small for the copies is as good as it was before there were any."""
     layer = L("odd.small-workspace", 1, 21, 25, 6, 40, 3, 3, 1, 1, 1)
