@@ -390,8 +390,9 @@ hipError_t launch_splitk_reduce_padded(const float *partial, int32_t splits, int
 {
     if (rows <= 0) return hipSuccess;
     if (C < 1 || Cp < C) return hipErrorInvalidValue;
-    // few outputs of many slices: as in launch_splitk_reduce_tail, where each of 4 groups would add hundreds of slices in turn
-    if (splits >= 128 && rows * Cp <= 8192)
+    // few outputs of many slices, each of 4 groups of which would add hundreds in turn (8192 outputs of 128 slices are 1-2 us
+    // faster with 4)
+    if (splits >= (rows * Cp <= 2048 ? 128 : 1024) && rows * Cp <= 8192)
         return launch_reduce_g<32>(partial, splits, rows * Cp, out, out_dtype, nullptr, 0, 1, nullptr, stream, C, Cp);
     return launch_reduce_g<4>(partial, splits, rows * Cp, out, out_dtype, nullptr, 0, 1, nullptr, stream, C, Cp);
 }
