@@ -2,6 +2,7 @@
 // three convolution passes and the loss onto the gfx950 kernels.  Everything
 // here runs on the host; validation happens before any launch.
 #include <algorithm>
+#include <cmath>
 #include <hip/hip_runtime.h>
 
 #include "../../include/dlconv.h"
@@ -124,12 +125,11 @@ hipError_t run_igemm(const dlk::IgemmArgs &a, bool bf16, const FilterSrc &fs, ui
 }
 
 // ---- channel counts that are not a multiple of 8 -------------------------------
-// The kernels that move 16-byte pieces need C % 8 == 0; the element-wise ones are 2 to 10 times slower.
-// So the activation tensor (and the forward filter) is first copied with its channels padded with zeros, and the
+// The kernels that move 16-byte pieces need C % 8 == 0; the element-wise ones are up to 10 times slower.
+// So the activation tensor (and the forward filter) may first be copied with its channels padded with zeros, and the
 // layer runs on the copy: 361 x 577 x 6 -> 64, 7x7 stride 2, batch 2: forward 56 -> 28 us, filter gradient 148 -> 35 us,
-// 5 us of either being the copy; 60 x 90 x 100 -> 64, 3x3: 92 -> 14 us and 41 -> 20 us.  Forward reductions of at
-// most 24 elements stay with the element-wise kernel (60 x 90 x 17 -> 64, 1x1: 9.1 us, 9.9 us through the copy).
-// Zero channels meet zero coefficients, so the sums are those of the layer itself.
+// 5 us of either being the copy; 60 x 90 x 100 -> 64, 3x3: 92 -> 14 us and 41 -> 20 us.  Which layers gain from it:
+// fwd_copies_pay.  Zero channels meet zero coefficients, so the sums are those of the layer itself.
 inline dl_conv_desc padded_desc(const dl_conv_desc *d)
 {
     dl_conv_desc e = *d;
@@ -150,16 +150,55 @@ dlk::IgemmArgs fwd_args(const dl_conv_desc *d, const Geometry &g)
     return a;
 }
 
+// Whether the forward pass of d gains from the channel-padded copies, on which it is the GEMM a of the layer e.  The lines
+// come from 9000 random layers timed both ways (fp16, C 1..400, 1..256 outputs, maps of 8 x 8 to 768 x 1500).
+bool fwd_copies_pay(const dl_conv_desc *d, const dl_conv_desc *e, const dlk::IgemmArgs &a)
+{
+    const int64_t taps = (int64_t)d->R * d->S, red = taps * d->C;
+    if (red <= 24) return false;                         // 60 x 90 x 17 -> 64, 1x1: 9.1 us, 9.9 through the copy
+    const int64_t steps = (red + 31) / 32;               // of the element-wise kernel
+    const int64_t strides = (int64_t)d->stride_h * d->stride_w;
+    // estimated times in us; the copy reads and writes all of x, also the pixels that a stride leaves out
+    const double m = (double)a.NB * a.OH * a.OW, pix = (double)d->N * d->H * d->W, tiles = std::ceil(m / 128) * std::ceil(d->K / 64.0);
+    const double copy = 2.0 * pix * (d->C + e->C) / 4.3e6;
+    const double filled = d->K / (64.0 * std::ceil(d->K / 64.0));
+    const double fetched = taps > 1 || strides == 1 ? 2.0 * pix * d->C : std::min(2.0 * pix * d->C, m * std::ceil(d->C / 32.0 + 1) * 64);
+    const double own = 5.0 + 2.6 * steps + std::max(0.0, tiles - 155) * steps * (5.1e-3 + 2.1e-3 * filled) * (1 + 0.36 * std::min(1.0, fetched / 3e8));
+    if (taps == 1) {
+        // the one-step kernel: 1.2-2.2x with stride 1; with stride 2 0.8x on 27 channels and 96 or 128 outputs, 1.2-1.8x on 256
+        if (dlk::igemm_short_applicable(a)) return strides == 1 || d->K >= 192;
+        // else by the estimates (8-9 % off): 506 x 512 x 299 -> 1, stride 2, batch 2: 74 us without the copy, 197 with it
+        const double cols = d->K <= 32 ? 32 : std::ceil(d->K / 64.0) * 64;
+        const double lines = std::min(2.0 * pix * e->C, m * std::ceil(e->C / 64.0) * 128);
+        const double padded = 5.9 + copy + 0.14 * std::ceil(e->C / 32.0) + std::max(m * cols * e->C * 6.4e-9, (2.0 * m * d->K + lines) / 3.4e6);
+        return own > 1.03 * padded;
+    }
+    // More taps: the copy has to be small beside the element-wise kernel's work (786 x 475 x 9 -> 12, 2x2 stride 2, batch 2:
+    // 21 us without, 28 with it), and the padded reduction may not have too many steps of 32 against that kernel's;
+    // a halo kernel takes whole 32-channel chunks of every tap.
+    if (copy > 1.0 && own < (steps == 1 ? 6 : steps <= 3 ? 4 : 2) * copy) return false;
+    if (!halo_columns(a)) return 2 * ((taps * e->C + 31) / 32) <= 7 * steps;
+    // 3x3, measured with 3..13 channels: 64 outputs 0.7-1.0x up to 5 channels, 1.0-1.1x with 6 and 7; at most 16 outputs
+    // 0.6-0.97x up to 10 channels, 1.0-1.2x with 11; above 64 outputs 0.98x and more from 4 channels on (dilated 0.6-0.8x
+    // with 6 and 7)
+    const bool dense3 = d->R == 3 && d->S == 3 && d->dil_h == 1 && d->dil_w == 1;
+    if (taps <= 9) return red >= (!dense3 ? 90 : d->K > 64 ? 36 : d->K > 16 ? 54 : 99);
+    // 5x5: 0.5-0.9x with one channel; up to 32 outputs 1.1-1.4x with two; above that 0.8-1.2x with two, 0.9-1.3x with three;
+    // 7x7: 0.43x with one, 0.74x with three, 1.3x with five
+    return taps * ((e->C + 31) / 32) <= (d->K > 32 ? 9 : 13) * steps;
+}
+
 // Scratch of a forward pass on the channel-padded copies (0: the layer takes its own tensors): the copies, then what
 // the implicit GEMM on them needs.  Layers that the streaming kernel for few channels takes stay with it.
 size_t fwd_padded_workspace(const dl_conv_desc *d, const Geometry &g, bool resid)
 {
-    if (d->C % 8 == 0 || (int64_t)d->R * d->S * d->C <= 24 || dlk::thin_rows_applicable(fwd_args(d, g))) return 0;
+    if (d->C % 8 == 0 || dlk::thin_rows_applicable(fwd_args(d, g))) return 0;
     const dl_conv_desc e = padded_desc(d);
     Geometry ge;
     if (check_desc(&e, &ge) != DL_OK) return 0;              // the copy would exceed the index range
     dlk::IgemmArgs a = fwd_args(&e, ge);
     a.resid = resid ? reinterpret_cast<const uint16_t *>(uintptr_t(16)) : nullptr;      // only tested for null
+    if (!fwd_copies_pay(d, &e, a)) return 0;
     return padded_bytes(&e, (int64_t)d->N * d->H * d->W) + padded_bytes(&e, (int64_t)d->K * d->R * d->S) +
            igemm_scratch_bytes(a);
 }

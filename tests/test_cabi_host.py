@@ -177,6 +177,34 @@ def test_kept_descriptor_answers_follow_the_values(api):
     assert len(api._plans) <= 1024
 
 
+# (N, H, W, C, K, R, stride, forward on channel-padded copies): timed both ways, us without / with the copies
+PADDED_FORWARD = [
+    ((2, 506, 512, 299, 1, 1, 2), False),       # 74 / 197: the copy moves four times the pixels that the layer reads
+    ((2, 759, 884, 204, 12, 1, 2), False),      # 138 / 354
+    ((1, 600, 900, 58, 96, 1, 2), False),
+    ((1, 535, 1022, 58, 256, 1, 2), True),      # 85 / 46: the one-step kernel with enough columns
+    ((2, 648, 1148, 189, 5, 1, 1), True),       # 596 / 456
+    ((2, 224, 394, 27, 1, 1, 1), False),        # 16.2 / 20.8
+    ((1, 60, 90, 17, 64, 1, 1), False),         # 9.1 / 9.9
+    ((2, 730, 734, 1, 256, 7, 1), False),       # 372 / 856: seven of eight padded channels are zeros
+    ((1, 328, 392, 1, 128, 5, 1), False),       # 24 / 49
+    ((1, 304, 425, 6, 8, 3, 1), False),         # 16 / 24: a 32-channel chunk of the halo kernel for 8 outputs
+    ((1, 397, 592, 7, 48, 3, 1), True),         # 32 / 29
+    ((2, 402, 549, 5, 96, 3, 1), True),         # 83 / 58
+    ((2, 475, 786, 9, 12, 2, 2), False),        # 21 / 28
+    ((2, 361, 577, 6, 64, 7, 2), True),         # 56 / 28
+    ((1, 60, 90, 100, 64, 3, 1), True),         # 92 / 14
+]
+
+
+@pytest.mark.parametrize("shape,padded", PADDED_FORWARD, ids=["x".join(map(str, s)) for s, _ in PADDED_FORWARD])
+def test_forward_on_padded_copies_where_they_pay(api, shape, padded):
+    N, H, W, C, K, R, st = shape
+    d = api.ConvDesc(N, H, W, C, K, R, R, st, st, R // 2, R // 2, 1, 1, api.DL_F16)
+    text = api.dl_conv_describe(d, api.PASS_FWD)
+    assert text.startswith("pad_channels_kernel" if padded else "igemm_scalar_kernel"), text
+
+
 def test_describe_names_the_kernels_of_the_decoder_layers(api):
     """dl_conv_describe runs the entry points' own dispatch with launches logged instead of issued
     (no GPU needed): the layers that carry 87 % of the FLOPs must reach the kernels built for them."""
