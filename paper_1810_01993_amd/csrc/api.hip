@@ -129,7 +129,7 @@ hipError_t run_igemm(const dlk::IgemmArgs &a, bool bf16, const FilterSrc &fs, ui
 // So the activation tensor (and the forward filter) may first be copied with its channels padded with zeros, and the
 // layer runs on the copy: 361 x 577 x 6 -> 64, 7x7 stride 2, batch 2: forward 56 -> 28 us, filter gradient 148 -> 35 us,
 // 5 us of either being the copy; 60 x 90 x 100 -> 64, 3x3: 92 -> 14 us and 41 -> 20 us.  Which layers gain from it:
-// fwd_copies_pay.  Zero channels meet zero coefficients, so the sums are those of the layer itself.
+// fwd_copies_pay, wgrad_padded_workspace.  Zero channels meet zero coefficients, so the sums are those of the layer itself.
 inline dl_conv_desc padded_desc(const dl_conv_desc *d)
 {
     dl_conv_desc e = *d;
@@ -299,6 +299,14 @@ size_t wgrad_padded_workspace(const dl_conv_desc *d, const Geometry &g)
     if (check_desc(&e, &ge) != DL_OK) return 0;
     // only where the copy gets a faster kernel, and never instead of the streaming kernel for few output channels
     if (wgrad_plan(d, g).cfg != -1 || wgrad_plan(&e, ge).cfg == -1) return 0;
+    // A 1x1 layer with a stride has all of x copied and reads a part of it: the copy (4.3 TB/s) has to take less than seven
+    // tenths of what the element-wise kernel's tiles take (5e-4 us per pixel of a 128 x 128 tile).  501 x 962 x 242 -> 64,
+    // stride 2, batch 2: 244 us without, 325 with it; 659 x 1209 x 141 -> 48: 389 and 312 us.
+    if (d->R * d->S == 1 && d->stride_h * d->stride_w > 1) {
+        const double copy = 2.0 * d->N * d->H * d->W * (d->C + e.C) / 4.3e6;
+        const double tiles = 5e-4 * ((d->K + 127) / 128) * ((d->C + 127) / 128) * d->N * g.P * g.Q;
+        if (copy > 3.0 + 0.7 * tiles) return 0;
+    }
     return align_up(wgrad_own_workspace(&e, ge), 256) + padded_bytes(&e, (int64_t)d->N * d->H * d->W);
 }
 

@@ -205,6 +205,15 @@ def test_forward_on_padded_copies_where_they_pay(api, shape, padded):
     assert text.startswith("pad_channels_kernel" if padded else "igemm_scalar_kernel"), text
 
 
+def test_filter_gradient_on_padded_copies_where_they_pay(api):
+    # (timed both ways, us without / with the copies: 244 / 325, 144 / 189, 389 / 312, 148 / 35)
+    for (N, H, W, C, K, R, st), padded in (((2, 501, 962, 242, 64, 1, 2), False), ((1, 463, 801, 378, 32, 1, 2), False),
+                                           ((2, 659, 1209, 141, 48, 1, 2), True), ((2, 361, 577, 6, 64, 7, 2), True)):
+        d = api.ConvDesc(N, H, W, C, K, R, R, st, st, R // 2, R // 2, 1, 1, api.DL_F16)
+        text = api.dl_conv_describe(d, api.PASS_BWD_FILTER)
+        assert text.startswith("pad_channels_kernel" if padded else "wgrad_kernel"), text
+
+
 def test_describe_names_the_kernels_of_the_decoder_layers(api):
     """dl_conv_describe runs the entry points' own dispatch with launches logged instead of issued
     (no GPU needed): the layers that carry 87 % of the FLOPs must reach the kernels built for them."""
