@@ -63,8 +63,15 @@ typedef struct {
  * Q likewise along W.  DL_ERR_SHAPE if the descriptor is invalid or P, Q < 1. */
 dl_status dl_conv_out_shape(const dl_conv_desc *desc, int32_t *P, int32_t *Q);
 
-/* Bytes of device scratch the given pass (DL_PASS_*) needs; may be 0. */
+/* Bytes of device scratch with which the given pass (DL_PASS_*) runs fastest; may be 0.
+ * Where C is not a multiple of 8 this can include a copy of x with its channels padded to
+ * one (forward pass and filter gradient): 2 * N*H*W * (C rounded up to a multiple of 8) bytes. */
 dl_status dl_conv_workspace_bytes(const dl_conv_desc *desc, int pass, size_t *bytes);
+
+/* The fewest bytes with which the given pass runs at all; may be 0.  Any workspace from
+ * this size on is accepted; below dl_conv_workspace_bytes the pass may take slower kernels
+ * (no padded copies, fewer slices of a filter gradient), whose sums are added in another order. */
+dl_status dl_conv_least_workspace_bytes(const dl_conv_desc *desc, int pass, size_t *bytes);
 
 /* Which kernels the given pass of this convolution launches, in order, each with
  * its grid, as text ("name<tile>[workgroups]; ..."), NUL-terminated and cut to
@@ -167,7 +174,8 @@ dl_status conv2d_transpose_bwd_filter(const dl_conv_desc *desc, const void *x, c
  *              convolution's data- and filter-gradient entry points take as dy)
  *   dbias[k] = sum_i dz[i,k]                      (device float[K], fp32 sums in a fixed order)
  * With relu == 0 only dbias is computed (dz = dy; y and dz may be NULL).  dz may
- * alias dy.  Workspace: dl_bias_relu_bwd_workspace_bytes(n_pixels, K). */
+ * alias dy.  Workspace: dl_bias_relu_bwd_workspace_bytes(n_pixels, K); down to a few times
+ * fewer bytes are accepted (fewer workgroups, slower). */
 dl_status dl_bias_relu_bwd_workspace_bytes(int64_t n_pixels, int32_t K, size_t *bytes);
 dl_status bias_relu_bwd(const void *dy, const void *y, int32_t dtype, int64_t n_pixels, int32_t K, int32_t relu,
                         void *dz, float *dbias, void *workspace, size_t workspace_bytes, void *hip_stream);

@@ -19,7 +19,7 @@ LIB_PATH = os.path.join(_HERE, "libdlconv.so")
 DL_F16, DL_BF16, DL_F32 = 0, 1, 2
 PASS_FWD, PASS_BWD_DATA, PASS_BWD_FILTER = 0, 1, 2
 
-EXPORTS = ("dl_conv_out_shape", "dl_conv_workspace_bytes", "dl_conv_describe", "conv2d_fwd", "conv2d_fwd_bias_relu", "conv2d_fwd_bias_add_relu", "conv2d_bwd_data",
+EXPORTS = ("dl_conv_out_shape", "dl_conv_workspace_bytes", "dl_conv_least_workspace_bytes", "dl_conv_describe", "conv2d_fwd", "conv2d_fwd_bias_relu", "conv2d_fwd_bias_add_relu", "conv2d_bwd_data",
            "conv2d_bwd_filter", "conv2d_transpose_fwd", "conv2d_transpose_bwd_data", "conv2d_transpose_bwd_filter",
            "dl_bias_relu_bwd_workspace_bytes", "bias_relu_bwd", "dl_larc_workspace_bytes", "larc_sgd_step", "dl_ce_workspace_bytes", "weighted_pixel_ce_fwd_bwd", "weighted_pixel_ce_fwd_bwd_static",
            "weighted_pixel_ce_map_fwd_bwd",
@@ -75,7 +75,7 @@ def _load() -> ctypes.CDLL:
     dp = ctypes.POINTER(_Desc)
     vp, sz = ctypes.c_void_p, ctypes.c_size_t
     lib.dl_conv_out_shape.argtypes = [dp, ctypes.POINTER(ctypes.c_int32), ctypes.POINTER(ctypes.c_int32)]
-    lib.dl_conv_workspace_bytes.argtypes = [dp, ctypes.c_int, ctypes.POINTER(sz)]
+    lib.dl_conv_workspace_bytes.argtypes = lib.dl_conv_least_workspace_bytes.argtypes = [dp, ctypes.c_int, ctypes.POINTER(sz)]
     lib.dl_conv_describe.argtypes = [dp, ctypes.c_int, ctypes.c_char_p, sz]
     for name in ("conv2d_fwd", "conv2d_bwd_data", "conv2d_bwd_filter", "conv2d_transpose_fwd",
                  "conv2d_transpose_bwd_data", "conv2d_transpose_bwd_filter"):
@@ -144,6 +144,13 @@ def dl_conv_workspace_bytes(desc: ConvDesc, which: int) -> int:
     return n.value
 
 
+def dl_conv_least_workspace_bytes(desc: ConvDesc, which: int) -> int:
+    n = ctypes.c_size_t()
+    _check(_lib.dl_conv_least_workspace_bytes(ctypes.byref(desc.c_struct()), which, ctypes.byref(n)),
+           "dl_conv_least_workspace_bytes")
+    return n.value
+
+
 def dl_conv_describe(desc: ConvDesc, which: int) -> str:
     """The kernels (with grids) that pass ``which`` of this convolution launches, in order."""
     buf = ctypes.create_string_buffer(2048)
@@ -183,9 +190,20 @@ def _workspace(nbytes: int, device, workspace: torch.Tensor | None):
     return workspace, workspace.numel() * workspace.element_size()
 
 
-def _conv_workspace(nbytes: int, device, workspace: torch.Tensor | None):
-    """As _workspace, for the calls that take none when they need none."""
-    return (None, 0) if workspace is None and nbytes == 0 else _workspace(nbytes, device, workspace)
+def _conv_workspace(desc: ConvDesc, which: int, nbytes: int, device, workspace: torch.Tensor | None):
+    """As _workspace for a convolution pass that prefers nbytes: none where it needs none, and the fewest bytes it runs with
+    where the device has no room for the preferred ones (channel-padded copies of large tensors, many slices)."""
+    if workspace is not None:
+        return _workspace(nbytes, device, workspace)
+    if nbytes == 0:
+        return None, 0
+    try:
+        return _workspace(nbytes, device, None)
+    except torch.cuda.OutOfMemoryError:
+        least = dl_conv_least_workspace_bytes(desc, which)
+        if least >= nbytes:
+            raise
+        return (None, 0) if least == 0 else _workspace(least, device, None)
 
 
 def _expect(t: torch.Tensor, shape, name: str):
@@ -203,7 +221,7 @@ def conv2d_fwd(desc: ConvDesc, x: torch.Tensor, w: torch.Tensor, y: torch.Tensor
     if y is None:
         y = torch.empty((desc.N, P, Q, desc.K), dtype=x.dtype, device=x.device)
     _expect(y, (desc.N, P, Q, desc.K), "y")
-    ws, nb = _conv_workspace(need[PASS_FWD], x.device, workspace)
+    ws, nb = _conv_workspace(desc, PASS_FWD, need[PASS_FWD], x.device, workspace)
     _check(_lib.conv2d_fwd(ref, _dev_ptr(x), _dev_ptr(w), _dev_ptr(y), _dev_ptr(ws), nb,
                            _stream()), "conv2d_fwd")
     return y
@@ -222,7 +240,7 @@ def conv2d_fwd_bias_relu(desc: ConvDesc, x: torch.Tensor, w: torch.Tensor, bias:
     if y is None:
         y = torch.empty((desc.N, P, Q, desc.K), dtype=x.dtype, device=x.device)
     _expect(y, (desc.N, P, Q, desc.K), "y")
-    ws, nb = _conv_workspace(need[PASS_FWD], x.device, workspace)
+    ws, nb = _conv_workspace(desc, PASS_FWD, need[PASS_FWD], x.device, workspace)
     _check(_lib.conv2d_fwd_bias_relu(ref, _dev_ptr(x), _dev_ptr(w), _dev_ptr(bias),
                                      1 if relu else 0, _dev_ptr(y), _dev_ptr(ws), nb, _stream()),
            "conv2d_fwd_bias_relu")
@@ -247,7 +265,7 @@ def conv2d_fwd_bias_add_relu(desc: ConvDesc, x: torch.Tensor, w: torch.Tensor, b
     if y is None:
         y = torch.empty((desc.N, P, Q, desc.K), dtype=x.dtype, device=x.device)
     _expect(y, (desc.N, P, Q, desc.K), "y")
-    ws, nb = _conv_workspace(need[PASS_FWD], x.device, workspace)
+    ws, nb = _conv_workspace(desc, PASS_FWD, need[PASS_FWD], x.device, workspace)
     _check(_lib.conv2d_fwd_bias_add_relu(ref, _dev_ptr(x), _dev_ptr(w), _dev_ptr(bias),
                                          _dev_ptr(residual), 1 if relu else 0, _dev_ptr(y), _dev_ptr(ws), nb, _stream()),
            "conv2d_fwd_bias_add_relu")
@@ -264,7 +282,7 @@ def conv2d_bwd_data(desc: ConvDesc, dy: torch.Tensor, w: torch.Tensor, dx: torch
     if dx is None:
         dx = torch.empty((desc.N, desc.H, desc.W, desc.C), dtype=dy.dtype, device=dy.device)
     _expect(dx, (desc.N, desc.H, desc.W, desc.C), "dx")
-    ws, nb = _conv_workspace(need[PASS_BWD_DATA], dy.device, workspace)
+    ws, nb = _conv_workspace(desc, PASS_BWD_DATA, need[PASS_BWD_DATA], dy.device, workspace)
     _check(_lib.conv2d_bwd_data(ref, _dev_ptr(dy), _dev_ptr(w), _dev_ptr(dx), _dev_ptr(ws),
                                 nb, _stream()), "conv2d_bwd_data")
     return dx
@@ -282,7 +300,7 @@ def conv2d_bwd_filter(desc: ConvDesc, x: torch.Tensor, dy: torch.Tensor, dw: tor
         dw = torch.empty((desc.K, desc.R, desc.S, desc.C), device=x.device,
                          dtype=torch.float32 if dwt == DL_F32 else x.dtype)
     _expect(dw, (desc.K, desc.R, desc.S, desc.C), "dw")
-    ws, nb = _workspace(need[PASS_BWD_FILTER], x.device, workspace)
+    ws, nb = _conv_workspace(desc, PASS_BWD_FILTER, need[PASS_BWD_FILTER], x.device, workspace)
     _check(_lib.conv2d_bwd_filter(ref, _dev_ptr(x), _dev_ptr(dy), _dev_ptr(dw),
                                   _dev_ptr(ws), nb, _stream()), "conv2d_bwd_filter")
     return dw
@@ -299,7 +317,7 @@ def conv2d_transpose_fwd(desc: ConvDesc, x: torch.Tensor, w: torch.Tensor, y: to
     if y is None:
         y = torch.empty((desc.N, desc.H, desc.W, desc.C), dtype=x.dtype, device=x.device)
     _expect(y, (desc.N, desc.H, desc.W, desc.C), "y")
-    ws, nb = _conv_workspace(need[PASS_BWD_DATA], x.device, workspace)
+    ws, nb = _conv_workspace(desc, PASS_BWD_DATA, need[PASS_BWD_DATA], x.device, workspace)
     _check(_lib.conv2d_transpose_fwd(ref, _dev_ptr(x), _dev_ptr(w), _dev_ptr(y),
                                      _dev_ptr(ws), nb, _stream()), "conv2d_transpose_fwd")
     return y
@@ -316,7 +334,7 @@ def conv2d_transpose_bwd_data(desc: ConvDesc, dy: torch.Tensor, w: torch.Tensor,
     if dx is None:
         dx = torch.empty((desc.N, P, Q, desc.K), dtype=dy.dtype, device=dy.device)
     _expect(dx, (desc.N, P, Q, desc.K), "dx")
-    ws, nb = _conv_workspace(need[PASS_FWD], dy.device, workspace)
+    ws, nb = _conv_workspace(desc, PASS_FWD, need[PASS_FWD], dy.device, workspace)
     _check(_lib.conv2d_transpose_bwd_data(ref, _dev_ptr(dy), _dev_ptr(w), _dev_ptr(dx),
                                           _dev_ptr(ws), nb, _stream()), "conv2d_transpose_bwd_data")
     return dx
@@ -335,7 +353,7 @@ def conv2d_transpose_bwd_filter(desc: ConvDesc, x: torch.Tensor, dy: torch.Tenso
         dw = torch.empty((desc.K, desc.R, desc.S, desc.C), device=x.device,
                          dtype=torch.float32 if dwt == DL_F32 else x.dtype)
     _expect(dw, (desc.K, desc.R, desc.S, desc.C), "dw")
-    ws, nb = _workspace(need[PASS_BWD_FILTER], x.device, workspace)
+    ws, nb = _conv_workspace(desc, PASS_BWD_FILTER, need[PASS_BWD_FILTER], x.device, workspace)
     _check(_lib.conv2d_transpose_bwd_filter(ref, _dev_ptr(x), _dev_ptr(dy), _dev_ptr(dw),
                                             _dev_ptr(ws), nb, _stream()), "conv2d_transpose_bwd_filter")
     return dw

@@ -411,6 +411,29 @@ dl_status dl_conv_workspace_bytes(const dl_conv_desc *desc, int pass, size_t *by
     return DL_ERR_UNSUPPORTED;
 }
 
+dl_status dl_conv_least_workspace_bytes(const dl_conv_desc *desc, int pass, size_t *bytes)
+{
+    if (!bytes) return DL_ERR_NULL;
+    Geometry g;
+    const dl_status st = check_desc(desc, &g);
+    if (st != DL_OK) return st;
+    switch (pass) {
+        case DL_PASS_FWD: {
+            dlk::IgemmArgs a = fwd_args(desc, g);
+            const size_t plain = igemm_scratch_bytes(a);
+            a.resid = reinterpret_cast<const uint16_t *>(uintptr_t(16));
+            *bytes = std::max(plain, igemm_scratch_bytes(a));
+            return DL_OK;
+        }
+        case DL_PASS_BWD_DATA:
+            *bytes = dgrad_workspace(desc, g, use_dgrad_stem(desc));
+            if (desc->C % 8 != 0) *bytes = std::min(*bytes, dgrad_workspace(desc, g, false));
+            return DL_OK;
+        case DL_PASS_BWD_FILTER: *bytes = std::min(wgrad_own_workspace(desc, g), wgrad_own_workspace(desc, g, 0)); return DL_OK;
+    }
+    return DL_ERR_UNSUPPORTED;
+}
+
 namespace {
 dl_status run_fwd(const dl_conv_desc *d, const void *x, const void *w, const float *bias, const void *residual, int relu,
                   void *y, void *workspace, size_t workspace_bytes, void *hip_stream)

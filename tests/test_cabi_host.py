@@ -49,6 +49,49 @@ def test_out_shape_and_workspace_queries(api):
     assert api.dl_ce_workspace_bytes(2 * 768 * 1152) >= 4
 
 
+def test_least_workspace(api):
+    """Never more than the preferred size, one byte less is refused, and what the padded copies and the stem kernel add for
+    channel counts that are not a multiple of 8 is not part of it."""
+    lib = api._lib
+    for C, K, R, st, H, W in ((300, 256, 3, 1, 768, 1152), (6, 64, 7, 2, 361, 577), (6, 40, 7, 2, 33, 45), (256, 256, 3, 2, 384, 576),
+                              (2048, 256, 3, 1, 48, 72), (100, 3, 1, 1, 90, 100), (16, 64, 7, 2, 768, 1152), (24, 24, 5, 1, 100, 100)):
+        d = api.ConvDesc(2, H, W, C, K, R, R, st, st, R // 2, R // 2, 1, 1, api.DL_F16)
+        for which, fn in ((api.PASS_FWD, lib.conv2d_fwd), (api.PASS_BWD_DATA, lib.conv2d_bwd_data), (api.PASS_BWD_FILTER, lib.conv2d_bwd_filter)):
+            least = api.dl_conv_least_workspace_bytes(d, which)
+            assert least <= api.dl_conv_workspace_bytes(d, which)
+            if least > 0:                                    # refused before anything is launched
+                assert fn(ctypes.byref(d.c_struct()), 4096, 4096, 4096, 4096, least - 1, None) == 5
+    big = api.ConvDesc(2, 768, 1152, 300, 256, 3, 3, 1, 1, 1, 1, 1, 1, api.DL_F16)
+    for which, bound in ((api.PASS_FWD, 0), (api.PASS_BWD_FILTER, 80e6)):
+        assert api.dl_conv_workspace_bytes(big, which) > 1e9 and api.dl_conv_least_workspace_bytes(big, which) <= bound
+    assert lib.dl_conv_least_workspace_bytes(ctypes.byref(big.c_struct()), 0, None) == 1
+    assert _code(api.dl_conv_least_workspace_bytes, big, 3) == 6
+    assert _code(api.dl_conv_least_workspace_bytes, api.ConvDesc(1, 8, 8, 8, 8, 3, 3, 0), 0) == 2
+
+
+def test_wrapper_takes_the_least_workspace_when_memory_is_short(api, monkeypatch):
+    torch = api.torch
+    big = api.ConvDesc(2, 768, 1152, 300, 256, 3, 3, 1, 1, 1, 1, 1, 1, api.DL_F16)
+    room = [0]
+    plain = torch.empty
+
+    def short(n, **kw):
+        if n > room[0]:
+            raise torch.cuda.OutOfMemoryError("no room")
+        return plain(n, **kw)
+    monkeypatch.setattr(torch, "empty", short)
+    ask = lambda which: api._conv_workspace(big, which, api.dl_conv_workspace_bytes(big, which), "meta", None)      # noqa: E731
+    assert ask(api.PASS_FWD) == (None, 0)
+    with pytest.raises(torch.cuda.OutOfMemoryError):
+        ask(api.PASS_BWD_FILTER)
+    room[0] = least = api.dl_conv_least_workspace_bytes(big, api.PASS_BWD_FILTER)
+    assert ask(api.PASS_BWD_FILTER)[1] == least
+    room[0] = 1 << 40
+    assert ask(api.PASS_BWD_FILTER)[1] == api.dl_conv_workspace_bytes(big, api.PASS_BWD_FILTER)
+    own = plain(64, dtype=torch.uint8)
+    assert api._conv_workspace(big, api.PASS_FWD, 1 << 30, "meta", own) == (own, 64)
+
+
 def _code(fn, *a):
     with pytest.raises(Exception) as e:
         fn(*a)

@@ -291,6 +291,30 @@ def test_forward_without_room_for_the_padded_copies(api):
         assert U.rel_err(U.to_host_f64(y), ref) <= U.TOL["f16"]
 
 
+@pytest.mark.parametrize("layer", [L("short.c20", 1, 60, 70, 20, 64, 3, 3, 1, 1, 1), L("short.stem.c6", 1, 61, 97, 6, 40, 7, 7, 2, 3, 1)],
+                         ids=lambda l: l.name)
+def test_passes_when_device_memory_is_short(api, layer, monkeypatch):
+    """The wrapper falls back to the fewest bytes a pass runs with."""
+    (x32, xb), (w32, wb), (dy32, dyb) = U.conv_inputs(layer, "f16", synth.seed_for(0, 697), "normal")
+    desc, s = api.desc_from_layer(layer, "f16"), U.shape_of(layer)
+    x, w, dy = (U.to_device(b, "f16") for b in (xb, wb, dyb))
+    plain, seen = torch.empty, []
+
+    def short(*a, **kw):
+        if kw.get("dtype") == torch.uint8:
+            which = seen[-1]
+            if a[0] > api.dl_conv_least_workspace_bytes(desc, which):
+                raise torch.cuda.OutOfMemoryError("no room")
+        return plain(*a, **kw)
+    monkeypatch.setattr(torch, "empty", short)
+    for which, call, ref in ((api.PASS_FWD, lambda: api.conv2d_fwd(desc, x, w), lambda: oracle.conv_fwd(s, x32, w32)),
+                             (api.PASS_BWD_DATA, lambda: api.conv2d_bwd_data(desc, dy, w), lambda: oracle.conv_bwd_data(s, dy32, w32)),
+                             (api.PASS_BWD_FILTER, lambda: api.conv2d_bwd_filter(desc, x, dy), lambda: oracle.conv_bwd_filter(s, x32, dy32))):
+        _say(f"[case] {layer.name} pass {which} preferred {api.dl_conv_workspace_bytes(desc, which)} least {api.dl_conv_least_workspace_bytes(desc, which)}")
+        seen.append(which)
+        assert U.rel_err(U.to_host_f64(call()), ref()) <= U.TOL["f16"]
+
+
 def test_gradients_in_a_smaller_workspace(api):
     """A filter gradient whose preferred plan takes many slices runs in the room of fewer, a stem's data gradient with an odd
     channel count in that of the general path; less than that is refused."""
