@@ -608,10 +608,9 @@ dl_status conv2d_bwd_data(const dl_conv_desc *d, const void *dy, const void *w, 
 
 namespace {
 // dw_c: channels of dw itself, smaller than d->C where d describes a channel-padded copy
-dl_status run_wgrad(const dl_conv_desc *d, const Geometry &g, const void *x, const void *dy, void *dw, int dw_c, void *workspace,
-                    size_t room, hipStream_t stream)
+dl_status run_wgrad(const dl_conv_desc *d, const Geometry &g, const dlk::WgradPlan &plan, const void *x, const void *dy, void *dw,
+                    int dw_c, void *workspace, hipStream_t stream)
 {
-    const dlk::WgradPlan plan = wgrad_plan(d, g, room);
     dlk::WgradArgs a{};
     a.x = static_cast<const uint16_t *>(x);
     a.dy = static_cast<const uint16_t *>(dy);
@@ -656,7 +655,8 @@ dl_status conv2d_bwd_filter(const dl_conv_desc *d, const void *x, const void *dy
     const dl_status st = check_desc(d, &g);
     if (st != DL_OK) return st;
     if (!aligned16(x) || !aligned16(dy) || !aligned16(dw)) return DL_ERR_ALIGN;
-    if (!workspace || workspace_bytes < wgrad_own_workspace(d, g, workspace_bytes)) return DL_ERR_WORKSPACE;
+    const dlk::WgradPlan plan = wgrad_plan(d, g, workspace_bytes);
+    if (!workspace || workspace_bytes < (size_t)plan.splits * (size_t)g.w_elems * sizeof(float)) return DL_ERR_WORKSPACE;
     if (!aligned16(workspace)) return DL_ERR_ALIGN;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     const size_t padded = wgrad_padded_workspace(d, g);
@@ -668,9 +668,9 @@ dl_status conv2d_bwd_filter(const dl_conv_desc *d, const void *x, const void *dy
         if (dlk::launch_pad_channels(static_cast<const uint16_t *>(x), reinterpret_cast<uint16_t *>(xp), (int64_t)d->N * d->H * d->W,
                                      nullptr, nullptr, 0, d->C, stream) != hipSuccess)
             return DL_ERR_LAUNCH;
-        return run_wgrad(&e, ge, xp, dy, dw, d->C, workspace, SIZE_MAX, stream);
+        return run_wgrad(&e, ge, wgrad_plan(&e, ge), xp, dy, dw, d->C, workspace, stream);
     }
-    return run_wgrad(d, g, x, dy, dw, d->C, workspace, workspace_bytes, stream);
+    return run_wgrad(d, g, plan, x, dy, dw, d->C, workspace, stream);
 }
 
 

@@ -272,12 +272,18 @@ WgradPlan wgrad_make_plan(int64_t npix, int64_t x_elems, int K, int C, int RSC, 
     static const Shape shapes[4] = {{256, 256, 1, 0.92}, {128, 128, 2, 0.55}, {64, 256, 2, 0.71}, {128, 256, 1, 0.88}};
     static const int forced_target = tuning_knob("DLCONV_WGRAD_TARGET", 0); // tuning override: workgroups wanted, unset in normal use
     const double outputs = (double)K * RSC;
-    double best = 1e300;
+    // Tiles of one slice that run on different XCDs share no L2.  With up to nine taps and operands beyond what the L2s hold
+    // (32 MB together) every operand tile of a dealt slice may come from the last-level cache or HBM, at about 9 TB/s
+    // (fetch_us below).  `pl` is the best plan without that term, `local` the best with it.
+    const bool large = fetch_term && RSC / C <= 9 && 2 * (x_elems + npix * K) >= 40000000;
+    double best = 1e300, best_local = 1e300, pl_steps = 0;
+    WgradPlan local = pl;
     for (int cfg = 0; cfg < 4; ++cfg) {
         if (forced >= 0 && cfg != forced) continue;
         const Shape &sh = shapes[cfg];
         const int64_t tiles = (int64_t)((K + sh.bm - 1) / sh.bm) * ((RSC + sh.bn - 1) / sh.bn);
         const int64_t cap = 32 * sh.per_cu;                  // workgroups one XCD holds at a time
+        const double fetch_us = 2.0 * tiles * (sh.bm + sh.bn) * (double)npix / 9e6;
         for (int cand = 0; cand < 64 + 15; ++cand) {
             // 8, 16, ... 512 slices, the same number on every XCD, each slice on one XCD; or
             // 1 .. 15 slices whose tiles are dealt over all XCDs
@@ -292,27 +298,37 @@ WgradPlan wgrad_make_plan(int64_t npix, int64_t x_elems, int K, int C, int RSC, 
             const int64_t per_xcd = (splits + 7) / 8;
             const int64_t rounds = spread ? (tiles * splits + 8 * cap - 1) / (8 * cap) : (tiles * per_xcd + cap - 1) / cap;
             const double reduce_us = (splits > 1 ? splits * outputs * 8.0 : outputs * 6.0) / 11.5e6;
-            // Tiles of one slice that run on different XCDs share no L2.  With up to nine taps and operands beyond
-            // what the L2s hold (32 MB together) every operand tile then comes from the last-level cache or HBM, at
-            // about 9 TB/s; where that takes longer than the steps, a slice belongs on one XCD (256 x 9 x 256 filter,
-            // stride 2, 110592 pixels: 14 dealt slices of 128 x 128 tiles, 2 GB, 240 us; 24 slices of 256 x 256 tiles
-            // on their XCDs 152 us; 1.2-1.9x on 21 of 24 such shapes, 0.95-0.97x on three).  Below that size, and with
-            // more taps, whose tiles meet in an XCD's L2, dealt slices were fetched at 10-16 TB/s and stayed ahead.
             const double steps_us = rounds * (chunk / 32 + 7) * sh.us_per_step;
-            const bool fetch_bound = fetch_term && spread && RSC / C <= 9 && 2 * (x_elems + npix * K) >= 40000000;
-            const double fetch_us = fetch_bound ? 2.0 * tiles * (sh.bm + sh.bn) * (double)npix / 9e6 : 0.0;
-            const double est = 9.0 + std::max(steps_us, fetch_us) + reduce_us;
+            const double est = 9.0 + steps_us + reduce_us;
             if (est < best) {
                 best = est;
-                pl.cfg = cfg;
-                pl.chunk = (int)chunk;
-                pl.splits = (int)splits;
-                pl.spread = spread ? 1 : 0;
+                pl = WgradPlan{cfg, (int)splits, (int)chunk, spread ? 1 : 0};
+                pl_steps = steps_us;
+            }
+            if (large) {
+                const double fetch_est = 9.0 + std::max(steps_us, spread ? fetch_us : 0.0) + reduce_us;
+                if (fetch_est < best_local) {
+                    best_local = fetch_est;
+                    local = WgradPlan{cfg, (int)splits, (int)chunk, spread ? 1 : 0};
+                }
             }
             if (forced_target > 0 && spread) break;
         }
     }
-    return pl;
+    if (!large || !pl.spread) return pl;
+    // What the XCDs together fetch of a dealt slice while its tiles keep in step: ids go to the XCDs in turn, column tiles
+    // fastest, so a column tile is on min(row tiles, 8 / gcd(column tiles, 8)) of them and a row tile on min(column tiles, 8).
+    // Where that, at 6 TB/s, takes longer than the steps does a slice belong on one XCD (not for one row tile of very many
+    // columns, whose x is fetched once per tap either way), and where a slice is so long that its tiles drift apart.
+    // 4600 random shapes, C and K up to 2048: 1.22x on average, 1.34x with C, K <= 512 (256 x 9 x 256 filter, stride 2,
+    // 110592 pixels: 14 dealt slices of 128 x 128 tiles 240 us, 24 slices of 256 x 256 tiles on their XCDs 152 us); 11 % of
+    // them are slower by more than 3 %, 3 % by more than a tenth, worst 0.76x (268 x 526 x 1600 -> 520, 2x2 stride 2), mostly
+    // with 1000 and more channels and few outputs.  With the fetch term for all of them these were 18 %, 6 % and 0.71x.
+    const Shape &sh = shapes[pl.cfg];
+    const int64_t rows = (K + sh.bm - 1) / sh.bm, cols = (RSC + sh.bn - 1) / sh.bn;
+    const int64_t spread8 = cols % 8 == 0 ? 1 : cols % 4 == 0 ? 2 : cols % 2 == 0 ? 4 : 8;
+    const double fetched = 2.0 * npix * (cols * std::min(rows, spread8) * sh.bn + rows * std::min<int64_t>(cols, 8) * sh.bm);
+    return (fetched / 6e6 > 1.05 * pl_steps && (rows > 1 || cols < 64)) || pl.chunk > 8000 ? local : pl;
 }
 
 template <class T>

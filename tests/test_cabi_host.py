@@ -275,6 +275,12 @@ def test_describe_names_the_kernels_of_the_decoder_layers(api):
     # filter gradient: large operands that every XCD would fetch for itself keep a slice on one XCD, small ones are dealt
     up = api.ConvDesc(2, 384, 576, 256, 256, 3, 3, 2, 2, 1, 1, 1, 1, api.DL_F16)
     assert api.dl_conv_describe(up, api.PASS_BWD_FILTER).startswith("wgrad_dma_kernel<256,256>[216]")
+    # ... and so do large ones of which the XCDs fetch little twice: one row tile (76 us dealt, 108 us with slices on one XCD),
+    # a number of column tiles that leaves every column on one XCD
+    for shape, dealt in (((4, 130, 189, 1008, 80, 3, 2), 7 * 71), ((2, 114, 117, 984, 112, 3, 1), 7 * 70)):
+        N, H, W, C, K, R, st = shape
+        text = api.dl_conv_describe(api.ConvDesc(N, H, W, C, K, R, R, st, st, 1, 1, 1, 1, api.DL_F16), api.PASS_BWD_FILTER)
+        assert text.startswith(f"wgrad_dma_kernel<128,128>[{dealt}]"), text
     # one-step reductions take their own kernel from 512 tiles of 128 x 128 on
     for H, name in ((256, "igemm_short_kernel["), (255, "igemm_dma_kernel")):
         assert api.dl_conv_describe(api.ConvDesc(1, H, 128, 64, 200, 1, 1), api.PASS_FWD).startswith(name)
