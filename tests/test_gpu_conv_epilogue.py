@@ -1,8 +1,9 @@
 """GPU parity of conv2d_fwd_bias_relu (bias and ReLU fused into the store of the
 forward convolution) against the fp64 oracle, on shapes that reach every
 forward kernel: the 3x3 halo-tile kernel with each column-tile width, the
-general halo-tile kernel, every tile of the plain engine, the split reduction,
-the element-wise kernel for odd channel counts, the 3-column logits layer."""
+general halo-tile kernel, every tile of the plain engine, the one-step kernel,
+the split reduction, the element-wise kernel and the channel-padded copies for
+odd channel counts, the 3-column logits layer."""
 import sys
 
 import numpy as np
@@ -61,19 +62,23 @@ CASES = [
     (L("e.halo3x3.k304", 1, 150, 260, 32, 304, 3, 3, 1, 1, 1), "bf16"),           # two 160-wide tiles, ragged
     (L("e.halo3x3.k192", 1, 210, 300, 24, 192, 3, 3, 1, 1, 1), "f16"),            # 128 + a 64-wide tile (bias offset)
     (L("e.halo.d2.k192", 1, 230, 250, 32, 192, 3, 3, 1, 2, 2), "bf16"),           # general halo kernel + remainder launch
-    (L("e.dma.256x256", 2, 192, 288, 16, 256, 3, 3, 1, 1, 1), "f16"),
-    (L("e.dma.k304.remainder", 2, 150, 200, 64, 304, 1, 1, 1, 0, 1), "f16"),      # 256 + 48 columns in two launches
+    (L("e.halo3x3.c16.k256", 2, 192, 288, 16, 256, 3, 3, 1, 1, 1), "f16"),
+    (L("e.short.k304", 2, 150, 200, 64, 304, 1, 1, 1, 0, 1), "f16"),              # the one-step kernel
     (L("e.dma.small", 2, 19, 23, 24, 40, 3, 3, 1, 1, 1), "bf16"),
     (L("e.dma.s2", 2, 21, 26, 32, 48, 3, 3, 2, 1, 1), "f16"),
     (L("e.dma.1x1.k136", 2, 17, 19, 72, 136, 1, 1, 1, 0, 1), "f16"),
     (L("e.ksplit.3x3.c1000", 1, 20, 24, 1000, 256, 3, 3, 1, 1, 1), "f16"),        # split reduction: tail in the reduce kernel
-    (L("e.scalar.odd-channels", 2, 9, 11, 3, 5, 3, 3, 1, 1, 1), "f16"),
+    (L("e.padded.odd-channels", 2, 9, 11, 3, 5, 3, 3, 1, 1, 1), "f16"),            # channel-padded copies: the plain engine
     (L("e.logits.k3", 1, 33, 47, 256, 3, 1, 1, 1, 0, 1), "bf16"),
     (L("e.thin.c4", 1, 40, 50, 4, 64, 1, 1, 1, 0, 1), "f16"),                     # 4 input channels: the streaming kernel
     (L("e.stem7x7", 2, 30, 44, 16, 64, 7, 7, 2, 3, 1), "bf16"),
     (L("e.narrow5x5.k32", 4, 75, 200, 16, 32, 5, 5, 1, 2, 1), "f16"),             # 5x5 kernel for <= 32 output channels
     (L("e.narrow5x5.k24", 3, 100, 230, 40, 24, 5, 5, 1, 2, 1), "bf16"),
     (L("e.narrow5x5.ksplit", 4, 50, 70, 96, 32, 5, 5, 1, 2, 1), "f16"),             # its split reduction: tail in the reduce kernel
+    (L("e.dma.k304.c96.remainder", 2, 150, 200, 96, 304, 1, 1, 1, 0, 1), "bf16"),  # 256 x 256 tiles + 48 columns: two launches
+    (L("e.scalar.c23.k32", 2, 19, 23, 23, 32, 1, 1, 1, 0, 1), "f16"),              # element-wise: at most 24 elements to add
+    (L("e.scalar.c2.k5", 2, 19, 23, 2, 5, 3, 3, 1, 1, 1), "bf16"),
+    (L("e.scalar.7x7.c1.k72", 1, 40, 31, 1, 72, 7, 7, 2, 3, 1), "f16"),            # element-wise: one channel
 ]
 
 
@@ -139,18 +144,19 @@ def check_residual(api, layer: ConvLayer, dtype: str, seed: int, bias=True, relu
 
 # every kernel a launch with a residual can take: the plain engine's staged store (several tile shapes, strided,
 # a remainder launch with offset pointers, output channels not a multiple of 4 or 8), its split reduction, the
-# general halo-tile kernel (+ remainder), the element-wise kernel, the streaming kernel for few input channels;
+# general halo-tile kernel (+ remainder), the element-wise kernel, channel-padded copies, the streaming kernel for few
+# input channels, the one-step kernel;
 # and the shapes that would take the 3x3 or 5x5 patch kernels without one
 RESIDUAL_CASES = [
     (L("r.res-block.1x1.64-256", 2, 40, 56, 64, 256, 1, 1, 1, 0, 1), "f16"),        # a ResNet block's last convolution
     (L("r.res-block.1x1.512-2048", 1, 20, 24, 512, 2048, 1, 1, 1, 0, 1), "bf16"),
-    (L("r.dma.k304.remainder", 2, 150, 200, 64, 304, 1, 1, 1, 0, 1), "f16"),
+    (L("r.short.k304", 2, 150, 200, 64, 304, 1, 1, 1, 0, 1), "f16"),
     (L("r.dma.s2.k48", 2, 21, 26, 32, 48, 3, 3, 2, 1, 1), "bf16"),
     (L("r.dma.k136", 2, 17, 19, 72, 136, 1, 1, 1, 0, 1), "f16"),
     (L("r.dma.k20", 1, 14, 15, 16, 20, 5, 5, 1, 2, 1), "f16"),                       # 8-byte alignment of rows varies
     (L("r.ksplit.3x3.c1000", 1, 20, 24, 1000, 256, 3, 3, 1, 1, 1), "f16"),
     (L("r.halo.d2.k192", 1, 230, 250, 32, 192, 3, 3, 1, 2, 2), "bf16"),
-    (L("r.scalar.odd-channels", 2, 9, 11, 3, 5, 3, 3, 1, 1, 1), "f16"),
+    (L("r.padded.odd-channels", 2, 9, 11, 3, 5, 3, 3, 1, 1, 1), "f16"),
     (L("r.thin.c4", 1, 40, 50, 4, 64, 1, 1, 1, 0, 1), "bf16"),
     (L("r.logits.k3", 1, 33, 47, 256, 3, 1, 1, 1, 0, 1), "f16"),                      # would take the streaming forward kernel
     (L("r.would-be-halo3x3.k256", 1, 200, 230, 40, 256, 3, 3, 1, 1, 1), "f16"),
@@ -163,12 +169,46 @@ RESIDUAL_CASES = [
     (L("r.64x64.ragged", 1, 23, 29, 256, 72, 1, 1, 1, 0, 1), "f16"),
     (L("r.short.ragged", 1, 181, 185, 64, 200, 1, 1, 1, 0, 1), "f16"),
     (L("r.short.32.s2", 1, 511, 514, 32, 72, 1, 1, 2, 0, 1), "bf16"),
+    (L("r.scalar.c23.k32", 2, 19, 23, 23, 32, 1, 1, 1, 0, 1), "bf16"),
+    (L("r.scalar.c2.k5", 2, 19, 23, 2, 5, 3, 3, 1, 1, 1), "f16"),
 ]
 
 
 @pytest.mark.parametrize("layer,dtype", RESIDUAL_CASES, ids=[l.name for l, _ in RESIDUAL_CASES])
 def test_bias_residual_relu(api, layer, dtype):
     check_residual(api, layer, dtype, synth.seed_for(0, 1500 + RESIDUAL_CASES.index((layer, dtype))))
+
+
+# the kernel that a case is named for is the one it reaches (dl_conv_describe plans a call without a residual)
+KERNELS = {"e.scalar": "igemm_scalar_kernel", "r.scalar": "igemm_scalar_kernel", "e.padded": "pad_channels_kernel",
+           "r.padded": "pad_channels_kernel", "e.short": "igemm_short_kernel", "r.short": "igemm_short_kernel",
+           "e.halo3x3": "igemm_halo3x3_kernel", "e.halo.": "igemm_halo_kernel", "e.dma": "igemm_dma_kernel",
+           "e.ksplit": "splitk_reduce", "e.narrow5x5": "igemm_narrow5x5_kernel", "e.thin": "thin_rows_kernel",
+           "e.logits": "thin_cols_kernel"}
+
+
+def test_cases_reach_the_kernels_they_are_named_for(api):
+    for layer, dtype in CASES + RESIDUAL_CASES:
+        for prefix, kernel in KERNELS.items():
+            if layer.name.startswith(prefix):
+                text = api.dl_conv_describe(api.desc_from_layer(layer, dtype), api.PASS_FWD)
+                assert kernel in text, f"{layer.name}: {text}"
+
+
+def test_element_wise_tail_without_room_for_the_copies(api):
+    """The same layer, bias, residual and ReLU on the copies and, in a workspace too small for them, element by element."""
+    layer = L("e.small-workspace", 2, 21, 25, 3, 40, 3, 3, 1, 1, 1)
+    (x32, xb), (w32, wb), _ = U.conv_inputs(layer, "f16", synth.seed_for(0, 1470), "normal")
+    r32, rb = synth.quantize(synth.normal(synth.seed_for(0, 1471), (layer.N, layer.P, layer.Q, layer.K)), "f16")
+    b = (synth.normal(synth.seed_for(0, 1472), (layer.K,)) * 0.7).astype(np.float32)
+    desc = api.desc_from_layer(layer, "f16")
+    assert "pad_channels_kernel" in api.dl_conv_describe(desc, api.PASS_FWD)
+    ref = E.conv_fwd_bias_add_relu(U.shape_of(layer), x32, w32, b, r32, True)
+    plain = E.conv_fwd_bias_relu(U.shape_of(layer), x32, w32, b, True)
+    x, w, r, bd = U.to_device(xb, "f16"), U.to_device(wb, "f16"), U.to_device(rb, "f16"), torch.from_numpy(b).cuda()
+    for ws in (None, torch.empty(16, dtype=torch.uint8, device="cuda")):
+        assert U.rel_err(U.to_host_f64(api.conv2d_fwd_bias_add_relu(desc, x, w, bd, r, True, workspace=ws)), ref) <= U.TOL["f16"]
+        assert U.rel_err(U.to_host_f64(api.conv2d_fwd_bias_relu(desc, x, w, bd, True, workspace=ws)), plain) <= U.TOL["f16"]
 
 
 def test_residual_only_and_null_residual(api):
