@@ -236,27 +236,62 @@ def test_reductions_of_one_step(api, layer, dtype, passes):
 
 
 # channel counts that are not a multiple of 8: channel-padded copies (forward, filter gradient), packed rows of the
-# stem's data gradient (odd and even counts, ragged patches), and the reductions on either side of the copies' limit
+# stem's data gradient (odd and even counts, ragged patches), and layers on either side of where the copies are made;
+# per pass (forward, data gradient, filter gradient) a kernel that it has to reach
+PAD, OWN, OWN_W, STEM = "pad_channels_kernel", "igemm_scalar_kernel", "wgrad_kernel<", "dgrad_stem_kernel"
 ODD = [
-    (L("odd.7x7s2.c3", 2, 33, 65, 3, 64, 7, 7, 2, 3, 1), "f16"),
-    (L("odd.7x7s2.c6", 1, 61, 97, 6, 48, 7, 7, 2, 3, 1), "bf16"),
-    (L("odd.7x7s2.c9", 1, 64, 35, 9, 32, 7, 7, 2, 3, 1), "f16"),
-    (L("odd.7x7s2.c14", 2, 17, 34, 14, 64, 7, 7, 2, 3, 1), "bf16"),
-    (L("odd.7x7s2.c1", 1, 40, 31, 1, 32, 7, 7, 2, 3, 1), "f16"),
-    (L("odd.3x3.c13", 2, 19, 23, 13, 64, 3, 3, 1, 1, 1), "f16"),
-    (L("odd.5x5s2.c7", 1, 30, 41, 7, 40, 5, 5, 2, 2, 1), "bf16"),
-    (L("odd.3x3d2.c20", 1, 26, 27, 20, 96, 3, 3, 1, 2, 2), "f16"),
-    (L("odd.1x1.c24", 1, 26, 27, 23, 32, 1, 1, 1, 0, 1), "f16"),
-    (L("odd.1x1.c25", 1, 26, 27, 25, 32, 1, 1, 1, 0, 1), "f16"),
-    (L("odd.1x1.c300", 1, 26, 27, 300, 72, 1, 1, 1, 0, 1), "bf16"),
-    (L("odd.3x3.k12", 1, 26, 27, 12, 12, 3, 3, 1, 1, 1), "f16"),
+    (L("odd.7x7s2.c3", 2, 33, 65, 3, 64, 7, 7, 2, 3, 1), "f16", (PAD, STEM, PAD)),
+    (L("odd.7x7s2.c6", 1, 61, 97, 6, 48, 7, 7, 2, 3, 1), "bf16", (PAD, STEM, PAD)),
+    (L("odd.7x7s2.c9", 1, 64, 35, 9, 32, 7, 7, 2, 3, 1), "f16", (PAD, STEM, PAD)),
+    (L("odd.7x7s2.c14", 2, 17, 34, 14, 64, 7, 7, 2, 3, 1), "bf16", (PAD, STEM, PAD)),
+    (L("odd.7x7s2.c1", 1, 40, 31, 1, 32, 7, 7, 2, 3, 1), "f16", (OWN, STEM, PAD)),
+    (L("odd.3x3.c13", 2, 19, 23, 13, 64, 3, 3, 1, 1, 1), "f16", (PAD, "igemm_dma_kernel", PAD)),
+    (L("odd.5x5s2.c7", 1, 30, 41, 7, 40, 5, 5, 2, 2, 1), "bf16", (PAD, "igemm_dma_kernel", PAD)),
+    (L("odd.3x3d2.c20", 1, 26, 27, 20, 96, 3, 3, 1, 2, 2), "f16", (PAD, "igemm_dma_kernel", PAD)),
+    (L("odd.1x1.c23", 1, 26, 27, 23, 32, 1, 1, 1, 0, 1), "f16", (OWN, "igemm_dma_kernel", OWN_W)),
+    (L("odd.1x1.c25", 1, 26, 27, 25, 32, 1, 1, 1, 0, 1), "f16", (PAD, "igemm_dma_kernel", OWN_W)),
+    (L("odd.1x1.c300", 1, 26, 27, 300, 72, 1, 1, 1, 0, 1), "bf16", (PAD, "igemm_dma_kernel", PAD)),
+    (L("odd.3x3.k12", 1, 26, 27, 12, 12, 3, 3, 1, 1, 1), "f16", (PAD, OWN, OWN_W)),
 ]
 
 
-@pytest.mark.parametrize("layer,dtype", ODD, ids=[l.name for l, _ in ODD])
-def test_channel_counts_without_16_byte_pieces(api, layer, dtype):
+def _reaches(api, layer, dtype, which, kernel):
+    text = api.dl_conv_describe(api.desc_from_layer(layer, dtype), which)
+    assert kernel in text, f"{layer.name} pass {which}: {text}"
+
+
+@pytest.mark.parametrize("layer,dtype,kernels", ODD, ids=[l.name for l, _, _ in ODD])
+def test_channel_counts_without_16_byte_pieces(api, layer, dtype, kernels):
+    for which, kernel in zip((api.PASS_FWD, api.PASS_BWD_DATA, api.PASS_BWD_FILTER), kernels):
+        _reaches(api, layer, dtype, which, kernel)
     check_layer(api, layer, dtype, synth.seed_for(0, 640 + layer.C), x_kind="normal")
     check_layer(api, layer, dtype, synth.seed_for(0, 660 + layer.C), x_kind="normal", dw_f32=True, passes=("wgrad",))
+
+
+# the same on maps large enough for the patch, strip, one-step, split-reduction and remainder kernels on the copies
+ODD_LARGE = [
+    (L("odd.halo3x3.c36", 1, 200, 230, 36, 256, 3, 3, 1, 1, 1), "f16", "fwd", "igemm_halo3x3_kernel"),
+    (L("odd.halo3x3.c13.k104", 1, 300, 330, 13, 104, 3, 3, 1, 1, 1), "bf16", "fwd", "igemm_halo3x3_kernel"),
+    (L("odd.narrow5x5.c20", 1, 300, 240, 20, 32, 5, 5, 1, 2, 1), "f16", "fwd", "igemm_narrow5x5_kernel"),
+    (L("odd.narrow5x5.c90.split", 4, 50, 70, 90, 32, 5, 5, 1, 2, 1), "bf16", "fwd", "igemm_narrow5x5_kernel"),
+    (L("odd.wide5x5.c12", 1, 150, 230, 12, 72, 5, 5, 1, 2, 1), "f16", "fwd", "igemm_wide5x5_kernel"),
+    (L("odd.halo.d2.c30", 1, 230, 250, 30, 192, 3, 3, 1, 2, 2), "bf16", "fwd", "igemm_halo_kernel"),
+    (L("odd.short.c60", 1, 270, 270, 60, 200, 1, 1, 1, 0, 1), "f16", "fwd", "igemm_short_kernel"),
+    (L("odd.split.c997", 1, 20, 24, 997, 256, 3, 3, 1, 1, 1), "f16", "fwd", "splitk_reduce"),
+    (L("odd.remainder.c70", 1, 250, 240, 70, 304, 1, 1, 1, 0, 1), "bf16", "fwd", "<128,64>"),
+    (L("odd.wgrad3x3.c37", 1, 330, 1000, 37, 72, 3, 3, 1, 1, 1), "f16", "wgrad", "wgrad3x3_kernel"),
+    (L("odd.wgrad5x5.c36", 2, 150, 240, 36, 32, 5, 5, 1, 2, 1), "bf16", "wgrad", "wgrad5x5_kernel"),
+    (L("odd.wgrad.c131", 1, 120, 140, 131, 264, 3, 3, 2, 1, 1), "f16", "wgrad", "wgrad_dma_kernel"),
+]
+
+
+@pytest.mark.parametrize("layer,dtype,which,kernel", ODD_LARGE, ids=[l.name for l, _, _, _ in ODD_LARGE])
+def test_patch_and_strip_kernels_on_padded_copies(api, layer, dtype, which, kernel):
+    for k in (PAD, kernel):
+        _reaches(api, layer, dtype, {"fwd": api.PASS_FWD, "wgrad": api.PASS_BWD_FILTER}[which], k)
+    check_layer(api, layer, dtype, synth.seed_for(0, 720 + layer.C), x_kind="normal", passes=(which,))
+    if which == "wgrad":
+        check_layer(api, layer, dtype, synth.seed_for(0, 740 + layer.C), x_kind="normal", dw_f32=True, passes=("wgrad",))
 
 
 # 1x1 layers with 1..4 output channels: the streaming filter gradient with few channel groups, i.e. many pixel lanes (16 parts
