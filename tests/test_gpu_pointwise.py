@@ -52,13 +52,24 @@ def test_mask_and_bias_gradient(api, n, K, dtype):
 
 
 # column blocks with a ragged last one (8-channel groups and odd counts), slabs that end inside the run of four pixels,
-# the change from four to eight pixels per thread and the limit of 1024 partial rows
+# and the limit of 1024 partial rows
 EDGES = [(7, 264), (31, 520), (4097, 1024), (131, 257), (65, 511), (262145, 8), (131073, 24), (32801, 256)]
 
 
 @pytest.mark.parametrize("n,K", EDGES, ids=[f"{n}x{K}" for n, K in EDGES])
 def test_column_blocks_and_slab_edges(api, n, K):
     _run(api, n, K, "f16", synth.seed_for(0, 1540 + (n + K) % 37))
+
+
+# either side of the change from four to eight pixels per thread (n * columns = 5 * 1024 * pixel lanes), where the number of
+# partial rows falls: 1024 to 640 with 256 channels, 320 to 160 with 1024
+SLABS = [(32737, 256), (40959, 256), (40960, 256), (10239, 1024), (10240, 1024)]
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("n,K", SLABS, ids=[f"{n}x{K}" for n, K in SLABS])
+def test_change_of_slab_length(api, n, K, dtype):
+    _run(api, n, K, dtype, synth.seed_for(0, 1550 + (n + K) % 13), relu=n % 2 == 1)
 
 
 # element-wise channel counts: workgroups of up to 256 channels below 4 M elements, interleaved columns of at most 64 from
