@@ -272,7 +272,7 @@ struct TailBwdArgs {
     float *partial, *dbias;
     int64_t npix, chunk;        // chunk: pixels per workgroup (set by the launcher)
     int32_t K, relu, rows;
-    int32_t groups, columns, gpb, lanes, interleave;        // how workgroups share a slab (set by the launcher)
+    int32_t groups, columns, gpb, lanes;                    // how workgroups share a slab (set by the launcher)
 };
 int tail_bwd_blocks(int64_t npix, int K);
 int tail_bwd_least_blocks(int64_t npix, int K);

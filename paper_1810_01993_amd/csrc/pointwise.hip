@@ -57,13 +57,15 @@ static TailBwdShape tail_bwd_shape(int64_t npix, int K)
     return npix * K < (1 << 22) ? tail_bwd_split(K, 1, TB_THREADS, false) : tail_bwd_split(K, 1, 64, true);
 }
 
-template <class T, int VEC, bool STREAM>
+// STREAM: dz is stored past the caches.  INTERLEAVE: see tail_bwd_shape (a template parameter: as an argument, its load is one
+// more round trip before a workgroup begins, 0.2 us of the 5-14 us launches).
+template <class T, int VEC, bool STREAM, bool INTERLEAVE>
 __global__ __launch_bounds__(TB_THREADS) void tail_bwd_kernel(const TailBwdArgs p)
 {
     __shared__ __align__(16) float red[TB_THREADS * VEC];
     __shared__ float part[TB_THREADS];
     int slab = blockIdx.x, column = blockIdx.y;
-    if (p.interleave) {                                             // one row of the grid: see tail_bwd_shape
+    if constexpr (INTERLEAVE) {                                     // the grid is one row of workgroups
         const int slot = blockIdx.x / 8;
         column = slot % p.columns;
         slab = slot / p.columns * 8 + blockIdx.x % 8;
@@ -200,21 +202,21 @@ hipError_t launch_tail_bwd(const TailBwdArgs &a0, bool is_bf16, hipStream_t stre
     a.columns = s.columns;
     a.gpb = s.gpb;
     a.lanes = s.lanes;
-    a.interleave = s.columns > 1 && a.K % 64 != 0 && a.npix * a.K >= (a.K % 8 == 0 ? 1 << 24 : 1 << 22);
-    const int64_t wgs = a.interleave ? (int64_t)(blocks + 7) / 8 * 8 * s.columns : blocks;
+    const bool interleave = s.columns > 1 && a.K % 64 != 0 && a.npix * a.K >= (a.K % 8 == 0 ? 1 << 24 : 1 << 22);
+    const int64_t wgs = interleave ? (int64_t)(blocks + 7) / 8 * 8 * s.columns : blocks;
     if (wgs > 0x7fffffff) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)wgs, a.interleave ? 1u : (unsigned)s.columns), block(TB_THREADS);
-    const bool stream_dz = a.npix * a.K * 2 > 300000000 && !a.interleave;     // (cut lines have to meet in the L2)
-    if (a.K % 8 == 0 && stream_dz) {
-        if (is_bf16) DLK_LAUNCH("tail_bwd_kernel", (tail_bwd_kernel<BF16, 8, true>), grid, block, 0, stream, a);
-        else DLK_LAUNCH("tail_bwd_kernel", (tail_bwd_kernel<F16, 8, true>), grid, block, 0, stream, a);
-    } else if (a.K % 8 == 0) {
-        if (is_bf16) DLK_LAUNCH("tail_bwd_kernel", (tail_bwd_kernel<BF16, 8, false>), grid, block, 0, stream, a);
-        else DLK_LAUNCH("tail_bwd_kernel", (tail_bwd_kernel<F16, 8, false>), grid, block, 0, stream, a);
-    } else {
-        if (is_bf16) DLK_LAUNCH("tail_bwd_kernel", (tail_bwd_kernel<BF16, 1, false>), grid, block, 0, stream, a);
-        else DLK_LAUNCH("tail_bwd_kernel", (tail_bwd_kernel<F16, 1, false>), grid, block, 0, stream, a);
-    }
+    const dim3 grid((unsigned)wgs, interleave ? 1u : (unsigned)s.columns), block(TB_THREADS);
+    const bool stream_dz = a.npix * a.K * 2 > 300000000 && !interleave;     // (cut lines have to meet in the L2)
+    const auto go = [&](auto type) {
+        using T = decltype(type);
+        if (a.K % 8 != 0 && interleave) DLK_LAUNCH("tail_bwd_kernel", (tail_bwd_kernel<T, 1, false, true>), grid, block, 0, stream, a);
+        else if (a.K % 8 != 0) DLK_LAUNCH("tail_bwd_kernel", (tail_bwd_kernel<T, 1, false, false>), grid, block, 0, stream, a);
+        else if (interleave) DLK_LAUNCH("tail_bwd_kernel", (tail_bwd_kernel<T, 8, false, true>), grid, block, 0, stream, a);
+        else if (stream_dz) DLK_LAUNCH("tail_bwd_kernel", (tail_bwd_kernel<T, 8, true, false>), grid, block, 0, stream, a);
+        else DLK_LAUNCH("tail_bwd_kernel", (tail_bwd_kernel<T, 8, false, false>), grid, block, 0, stream, a);
+    };
+    if (is_bf16) go(BF16{});
+    else go(F16{});
     hipError_t e = dlk::launch_status();
     if (e != hipSuccess) return e;
     return launch_splitk_reduce(a.partial, blocks, a.K, a.dbias, 2, stream);
