@@ -2,11 +2,11 @@
 // map, the data gradient of its contracting layer): the whole reduction is one 64-channel step of the direct-to-LDS
 // engine's tile code, fetched at once.
 //
-// Bound by memory: a 128 x 128 tile moves 32 KB in, 32 KB out (and 32 KB of residual) for 32 multiplies per wave.  What
+// Bound by memory: a 128 x 128 tile moves 32 KB in, 32 KB out (and 32 KB of residual) for 16 MFMAs (32x32x16) per wave.  What
 // counts is how many workgroups a CU holds at different stages of that: 32 KB of LDS and 122 registers leave room for
 // four, where the ring kernel's 256 x 256 tile (128 KB, and two of its four steps multiply zeros) leaves one.
 // Measured (fp16, plain / with bias, residual and ReLU, before -> after): 110592 pixels, 64 -> 256 23.3 -> 18.1 us /
-// 49.2 -> 32.7 us (4.5 TB/s), 64 -> 128 15.6 -> 11.3 / 27.0 -> 19.7 us; 442368 pixels, 32 -> 96 40.9 -> 27.7 /
+// 49.2 -> 32.7 us (3.9 TB/s), 64 -> 128 15.6 -> 11.3 / 27.0 -> 19.7 us; 442368 pixels, 32 -> 96 40.9 -> 27.7 /
 // 70.9 -> 52.5 us, 64 -> 304 105 -> 90 / 282 -> 162 us; data gradient with 64 output channels 23.2 -> 17.9 us.
 #include "igemm_dma_tile.h"
 

@@ -48,7 +48,7 @@ static TailBwdShape tail_bwd_split(int K, int vec, int cap, bool even)
 // With 16-byte pieces a column is 256 channels wide where they are whole 128-byte lines (K % 64 == 0), and on tensors of
 // less than 16 M elements.  Other rows share lines with their neighbours wherever they are cut: up to 512 channels they
 // are not cut, wider ones into columns of at most 512 channels, interleaved as above.  Measured (fp16, ReLU; columns of
-// 256 channels -> now): 884736 x 304 481 -> 330 us (4.9 TB/s), 442368 x 520 430 -> 345 us, 110592 x 520 89 -> 74 us,
+// 256 channels -> now): 884736 x 304 481 -> 311 us (5.2 TB/s), 442368 x 520 430 -> 345 us, 110592 x 520 89 -> 74 us,
 // 442368 x 1160 936 -> 789 us; below the line 3015 x 304 8.7 us, 9.3 with one column.
 static TailBwdShape tail_bwd_shape(int64_t npix, int K)
 {
