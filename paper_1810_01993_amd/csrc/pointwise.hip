@@ -40,21 +40,25 @@ static TailBwdShape tail_bwd_split(int K, int vec, int cap, bool even)
     return s;
 }
 
-// Without 16-byte pieces a workgroup of 256 channels has one pixel lane: from 4 M elements on it covers at most 64
-// (four and more lanes), and consecutive workgroups of an XCD take the columns of one slab side by side, so that the
-// pieces of a 128-byte line that two of them write meet in its L2.  Measured (ReLU, against 256 channels):
-// 442368 x 257 559 -> 330 us, 1000000 x 100 357 -> 199 us; below the line 3015 x 257 8.8 us, 9.4 with 64.
+// Without 16-byte pieces a workgroup of 256 channels has one pixel lane: from 4 M elements on (8 M without ReLU, where
+// nothing is stored) it covers at most 64 (four and more lanes), and consecutive workgroups of an XCD take the columns of
+// one slab side by side, so that the pieces of a 128-byte line that two of them write meet in its L2.  Measured (ReLU,
+// against 256 channels): 442368 x 257 559 -> 330 us, 1000000 x 100 357 -> 199 us; below the line 3015 x 257 8.8 us, 9.4
+// with 64.
 //
 // With 16-byte pieces a column is 256 channels wide where they are whole 128-byte lines (K % 64 == 0), and on tensors of
 // less than 16 M elements.  Other rows share lines with their neighbours wherever they are cut: up to 512 channels they
 // are not cut, wider ones into columns of at most 512 channels, interleaved as above.  Measured (fp16, ReLU; columns of
 // 256 channels -> now): 884736 x 304 481 -> 311 us (5.2 TB/s), 442368 x 520 430 -> 345 us, 110592 x 520 89 -> 74 us,
 // 442368 x 1160 936 -> 789 us; below the line 3015 x 304 8.7 us, 9.3 with one column.
-static TailBwdShape tail_bwd_shape(int64_t npix, int K)
+static bool tail_bwd_large(const TailBwdArgs &a)
 {
-    if (K % 64 == 0 || (K % 8 == 0 && npix * K < (1 << 24))) return tail_bwd_split(K, 8, TB_THREADS / 8, false);
-    if (K % 8 == 0) return tail_bwd_split(K, 8, 64, true);
-    return npix * K < (1 << 22) ? tail_bwd_split(K, 1, TB_THREADS, false) : tail_bwd_split(K, 1, 64, true);
+    return a.K % 64 != 0 && a.npix * a.K >= (a.K % 8 == 0 ? 1 << 24 : a.relu ? 1 << 22 : 1 << 23);
+}
+static TailBwdShape tail_bwd_shape(const TailBwdArgs &a)
+{
+    const int vec = a.K % 8 == 0 ? 8 : 1;
+    return tail_bwd_large(a) ? tail_bwd_split(a.K, vec, 64, true) : tail_bwd_split(a.K, vec, TB_THREADS / vec, false);
 }
 
 // STREAM: dz is stored past the caches.  INTERLEAVE: see tail_bwd_shape (a template parameter: as an argument, its load is one
@@ -197,12 +201,12 @@ hipError_t launch_tail_bwd(const TailBwdArgs &a0, bool is_bf16, hipStream_t stre
     if (blocks < 1) return hipErrorInvalidValue;
     a.chunk = (a.npix + blocks - 1) / blocks;
     if (a.chunk < 1) a.chunk = 1;
-    const TailBwdShape s = tail_bwd_shape(a.npix, a.K);
+    const TailBwdShape s = tail_bwd_shape(a);
     a.groups = s.groups;
     a.columns = s.columns;
     a.gpb = s.gpb;
     a.lanes = s.lanes;
-    const bool interleave = s.columns > 1 && a.K % 64 != 0 && a.npix * a.K >= (a.K % 8 == 0 ? 1 << 24 : 1 << 22);
+    const bool interleave = s.columns > 1 && tail_bwd_large(a);
     const int64_t wgs = interleave ? (int64_t)(blocks + 7) / 8 * 8 * s.columns : blocks;
     if (wgs > 0x7fffffff) return hipErrorInvalidValue;
     const dim3 grid((unsigned)wgs, interleave ? 1u : (unsigned)s.columns), block(TB_THREADS);

@@ -82,6 +82,11 @@ def test_element_wise_columns(api, n, K):
     _run(api, n, K, "f16" if n % 2 else "bf16", synth.seed_for(0, 1560 + (n + K) % 17))
 
 
+@pytest.mark.parametrize("n", [32767, 32769])
+def test_element_wise_columns_without_relu(api, n):
+    _run(api, n, 257, "f16", synth.seed_for(0, 1585), relu=False)       # the line lies at 8 M elements here
+
+
 # rows that are not whole 128-byte lines, from 16 M elements on: up to 512 channels in one column, wider ones interleaved
 # (last slab group short of eight, last column short); below that and with whole lines columns of 256 channels
 PIECES = [(33289, 504), (55190, 304), (32300, 520), (14503, 1160), (16289, 1032), (4100, 4104), (77, 328), (1000, 576)]
