@@ -82,11 +82,14 @@ struct FilterSrc { const uint16_t *src; int64_t base, sj, sr, ss, sc; };
 int halo_columns(const dlk::IgemmArgs &a) { return dlk::igemm_halo_columns(a); }
 
 // Scratch one implicit GEMM needs: the blocked filter copy of a halo kernel, or the fp32 partial
-// sums of a split reduction of the plain engine (never both).
-size_t igemm_scratch_bytes(const dlk::IgemmArgs &a)
+// sums of a split reduction of the plain engine (never both).  least: the fewest bytes it runs with.
+size_t igemm_scratch_bytes(const dlk::IgemmArgs &a, bool least = false)
 {
     const int cols = halo_columns(a);
-    if (!cols) return align_up(dlk::igemm_split_bytes(a), 256);
+    if (!cols) {
+        const size_t fewest = dlk::igemm_split_least_bytes(a);
+        return align_up(least ? fewest : std::max(fewest, dlk::igemm_split_bytes(a)), 256);
+    }
     dlk::IgemmArgs h = a;
     h.Nout = cols;
     // (the 5x5 kernel for at most 32 output channels may split its reduction on small maps: partial sums behind the copy)
@@ -95,12 +98,14 @@ size_t igemm_scratch_bytes(const dlk::IgemmArgs &a)
 }
 
 // a.B: plain [Nout][taps*Cin] filter (may be null if the halo kernel takes every column).
-hipError_t run_igemm(const dlk::IgemmArgs &a, bool bf16, const FilterSrc &fs, uint16_t *scratch, hipStream_t stream)
+// room: bytes at scratch.
+hipError_t run_igemm(const dlk::IgemmArgs &a, bool bf16, const FilterSrc &fs, uint16_t *scratch, size_t room, hipStream_t stream)
 {
     const int cols = halo_columns(a);
     if (!cols) {
         dlk::IgemmArgs g = a;
-        g.part = dlk::igemm_split_bytes(a) ? reinterpret_cast<float *>(scratch) : nullptr;
+        g.part = room > 0 ? reinterpret_cast<float *>(scratch) : nullptr;
+        g.part_bytes = room;
         return dlk::launch_igemm(g, bf16, stream);
     }
     dlk::FilterBlockArgs f{};
@@ -211,7 +216,7 @@ struct DgradClass {
     size_t wt_bytes, blk_bytes;
 };
 
-DgradClass dgrad_class(const dl_conv_desc *d, const Geometry &g, int ca, int cb)
+DgradClass dgrad_class(const dl_conv_desc *d, const Geometry &g, int ca, int cb, bool least = false)
 {
     DgradClass c{};
     const int OH = ca < d->H ? (d->H - ca + d->stride_h - 1) / d->stride_h : 0;
@@ -229,7 +234,7 @@ DgradClass dgrad_class(const dl_conv_desc *d, const Geometry &g, int ca, int cb)
     a.th0 = c.th.t0; a.dth = c.th.dt; a.tw0 = c.tw.t0; a.dtw = c.tw.dt;
     a.FH = d->H; a.FW = d->W; a.osh = d->stride_h; a.osw = d->stride_w; a.ooh = ca; a.oow = cb;
     a.ldd = d->C;
-    c.blk_bytes = (c.empty || !c.has_taps) ? 0 : igemm_scratch_bytes(a);
+    c.blk_bytes = (c.empty || !c.has_taps) ? 0 : igemm_scratch_bytes(a, least);
     return c;
 }
 
@@ -241,13 +246,14 @@ bool use_dgrad_stem(const dl_conv_desc *d)
 
 size_t dgrad_stem_workspace(const dl_conv_desc *d) { return align_up(dlk::dgrad_stem_filter_bytes(d->C, d->K), 256); }
 
-size_t dgrad_workspace(const dl_conv_desc *d, const Geometry &g, bool stem)
+// least: the fewest bytes it runs with
+size_t dgrad_workspace(const dl_conv_desc *d, const Geometry &g, bool stem, bool least = false)
 {
     if (stem) return dgrad_stem_workspace(d);
     size_t total = 0;
     for (int ca = 0; ca < d->stride_h; ++ca)
         for (int cb = 0; cb < d->stride_w; ++cb) {
-            const DgradClass c = dgrad_class(d, g, ca, cb);
+            const DgradClass c = dgrad_class(d, g, ca, cb, least);
             total += c.wt_bytes + c.blk_bytes;
         }
     return total;
@@ -420,14 +426,14 @@ dl_status dl_conv_least_workspace_bytes(const dl_conv_desc *desc, int pass, size
     switch (pass) {
         case DL_PASS_FWD: {
             dlk::IgemmArgs a = fwd_args(desc, g);
-            const size_t plain = igemm_scratch_bytes(a);
+            const size_t plain = igemm_scratch_bytes(a, true);
             a.resid = reinterpret_cast<const uint16_t *>(uintptr_t(16));
-            *bytes = std::max(plain, igemm_scratch_bytes(a));
+            *bytes = std::max(plain, igemm_scratch_bytes(a, true));
             return DL_OK;
         }
         case DL_PASS_BWD_DATA:
-            *bytes = dgrad_workspace(desc, g, use_dgrad_stem(desc));
-            if (desc->C % 8 != 0) *bytes = std::min(*bytes, dgrad_workspace(desc, g, false));
+            *bytes = dgrad_workspace(desc, g, use_dgrad_stem(desc), true);
+            if (desc->C % 8 != 0) *bytes = std::min(*bytes, dgrad_workspace(desc, g, false, true));
             return DL_OK;
         case DL_PASS_BWD_FILTER: *bytes = std::min(wgrad_own_workspace(desc, g), wgrad_own_workspace(desc, g, 0)); return DL_OK;
     }
@@ -447,7 +453,7 @@ dl_status run_fwd(const dl_conv_desc *d, const void *x, const void *w, const flo
     if (bias && (reinterpret_cast<uintptr_t>(bias) & 3u)) return DL_ERR_ALIGN;
     dlk::IgemmArgs a = fwd_args(d, g);
     a.resid = static_cast<const uint16_t *>(residual);    // decides which kernels may take the launch
-    const size_t need = igemm_scratch_bytes(a);
+    const size_t need = igemm_scratch_bytes(a, true);
     if (need > 0 && (!workspace || workspace_bytes < need)) return DL_ERR_WORKSPACE;
     if (need > 0 && !aligned16(workspace)) return DL_ERR_ALIGN;
     // (a workspace too small for the copies, or none, still runs the layer on its own tensors)
@@ -469,7 +475,8 @@ dl_status run_fwd(const dl_conv_desc *d, const void *x, const void *w, const flo
     a.bias = bias;
     a.relu = relu ? 1 : 0;
     const FilterSrc fs{a.B, 0, (int64_t)d->R * d->S * d->C, (int64_t)d->S * d->C, d->C, 1};
-    return hip_status(run_igemm(a, d->dtype == DL_BF16, fs, static_cast<uint16_t *>(workspace),
+    const size_t room = workspace && aligned16(workspace) ? workspace_bytes : 0;
+    return hip_status(run_igemm(a, d->dtype == DL_BF16, fs, static_cast<uint16_t *>(workspace), room,
                                 static_cast<hipStream_t>(hip_stream)));
 }
 }  // namespace
@@ -504,9 +511,10 @@ dl_status conv2d_bwd_data(const dl_conv_desc *d, const void *dy, const void *w, 
     // the stem kernel's filter copy is rounded up to 32 output channels: for channel counts that the general path served
     // from fewer bytes, those bytes are still enough
     const bool stem = use_dgrad_stem(d) && (d->C % 8 == 0 || (workspace && workspace_bytes >= dgrad_stem_workspace(d)));
-    const size_t need = dgrad_workspace(d, g, stem);
+    const size_t need = dgrad_workspace(d, g, stem, true);
     if (need > 0 && (!workspace || workspace_bytes < need)) return DL_ERR_WORKSPACE;
     if (need > 0 && !aligned16(workspace)) return DL_ERR_ALIGN;
+    const bool least = !workspace || !aligned16(workspace) || workspace_bytes < dgrad_workspace(d, g, stem);
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     const bool bf16 = d->dtype == DL_BF16;
 
@@ -532,7 +540,7 @@ dl_status conv2d_bwd_data(const dl_conv_desc *d, const void *dy, const void *w, 
     // filter re-laid-out as [c][tap][k].  Classes that take the plain engine with
     // one tile shape share a launch (their tiles of one image region then run
     // side by side); the others are launched one by one.
-    struct Pending { dlk::IgemmArgs a; FilterSrc fs; uint16_t *blk; };
+    struct Pending { dlk::IgemmArgs a; FilterSrc fs; uint16_t *blk; size_t room; };
     Pending pending[dlk::IgemmBatch::MAX];
     int n_pending = 0;
     bool overflow = false;
@@ -551,7 +559,7 @@ dl_status conv2d_bwd_data(const dl_conv_desc *d, const void *dy, const void *w, 
     }
     for (int ca = 0; ca < d->stride_h; ++ca)
         for (int cb = 0; cb < d->stride_w; ++cb) {
-            DgradClass c = dgrad_class(d, g, ca, cb);
+            DgradClass c = dgrad_class(d, g, ca, cb, least);
             uint16_t *wt = reinterpret_cast<uint16_t *>(static_cast<char *>(workspace) + ws_off);
             uint16_t *blk = reinterpret_cast<uint16_t *>(static_cast<char *>(workspace) + ws_off + c.wt_bytes);
             ws_off += c.wt_bytes + c.blk_bytes;
@@ -585,12 +593,12 @@ dl_status conv2d_bwd_data(const dl_conv_desc *d, const void *dy, const void *w, 
                                c.th.rstep * SC, (int64_t)c.tw.rstep * d->C, (int64_t)d->R * SC};
             if (c.has_taps && halo_columns(a) == 0 && !overflow) {
                 if (n_pending < dlk::IgemmBatch::MAX) {
-                    pending[n_pending++] = Pending{a, fs, blk};
+                    pending[n_pending++] = Pending{a, fs, blk, c.blk_bytes};
                     continue;
                 }
                 overflow = true;                        // more classes than one launch holds: one by one after all
             }
-            if (run_igemm(a, bf16, fs, blk, stream) != hipSuccess) return DL_ERR_LAUNCH;
+            if (run_igemm(a, bf16, fs, blk, c.blk_bytes, stream) != hipSuccess) return DL_ERR_LAUNCH;
         }
     if (n_pending > 0) {
         dlk::IgemmBatch b{};
@@ -600,7 +608,7 @@ dl_status conv2d_bwd_data(const dl_conv_desc *d, const void *dy, const void *w, 
             if (dlk::launch_igemm_batch(b, bf16, stream) != hipSuccess) return DL_ERR_LAUNCH;
         } else {
             for (int i = 0; i < n_pending; ++i)
-                if (run_igemm(pending[i].a, bf16, pending[i].fs, pending[i].blk, stream) != hipSuccess) return DL_ERR_LAUNCH;
+                if (run_igemm(pending[i].a, bf16, pending[i].fs, pending[i].blk, pending[i].room, stream) != hipSuccess) return DL_ERR_LAUNCH;
         }
     }
     return DL_OK;

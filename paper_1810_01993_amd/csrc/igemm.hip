@@ -8,8 +8,8 @@
 // kernel and tile for one implicit GEMM, the element-wise kernel for channel
 // counts that are not a multiple of 8, and the filter re-layout for data
 // gradients that cannot read the filter in place.
-#include <cstdlib>
-#include <cstring>
+#include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 #include "device_common.h"
@@ -121,80 +121,145 @@ __global__ __launch_bounds__(256) void igemm_scalar_kernel(const IgemmArgs p)
 // ===========================================================================
 // Host side: tile selection and launch
 // ===========================================================================
-// Tuning override: DLCONV_IGEMM_CFG=<n> forces tile configuration n for every
-// vector-path launch (used by the tile sweeps; unset in normal use).
-static int forced_cfg()
-{
-    static const int v = tuning_knob("DLCONV_IGEMM_CFG", -1);
-    return v;
-}
+// Tuning override: DLCONV_IGEMM_CFG=<n> forces tile n for every vector-path launch (used by the tile sweeps; unset in
+// normal use).
+static int forced_cfg() { return tuning_knob("DLCONV_IGEMM_CFG", -1); }
 
 static bool choose_c_outer(const IgemmArgs &a)
 {
-    static const int force_order = tuning_knob("DLCONV_C_OUTER", -1);
     // channel-major order needs the tap mask to fit 64 bits and no chunk that is mostly padding
-    const bool cm_ok = a.TR * a.TS <= 64;
-    return cm_ok && (force_order >= 0 ? force_order != 0 : (a.Cin % 32 == 0 || a.Cin >= 128));
+    return a.TR * a.TS <= 64 && (a.Cin % 32 == 0 || a.Cin >= 128);
 }
 
-// Split of the reduction for GEMMs with few output pixels and a very long reduction (the
-// ASPP 3x3 layers' forward pass: 6912 x 256 outputs, reduction 18432).  With tiles small enough
-// to give every CU one, such a GEMM is bound by the L2 -> LDS traffic of its operand tiles
-// (12 KB per 0.5 MFLOP step of a 128 x 64 tile: 1.5 GB, 12 TB/s).  Instead the 256 x 256 tile
-// (a third of the traffic per FLOP) is used and ranges of channel chunks run side by side;
-// an ordered reduce adds their fp32 partial sums.  Returns the number of ranges (1: no split)
-// and the chunks per range.
-static int choose_ksplits(const IgemmArgs &a, int *chunks_per_split)
+// ---- tile and split of the reduction ---------------------------------------------
+// Estimated time of a GEMM in us: t0 + (steps * step + fix) * (tiles a compute unit works through).  The last factor is
+// the number of rounds where a compute unit holds one tile, and the tiles themselves, rounded up while they are few, where it
+// holds several.  t0, step and fix per tile, for 1x1 filters and for more taps, are fitted to 465 random GEMMs (forward and
+// data gradient, 400..260000 pixels, 32..2048 x 40..2048 channels, 1x1 to 5x5; fp16) timed with every tile: the choice is
+// 3 % slower than the best tile of each on average, 26 % at worst.
+struct TileCost { double t0, step, fix; };
+struct TileInfo {
+    int bm, bn, kb, per_cu;
+    TileCost cost[2];           // 1x1, more taps
+};
+static const TileInfo TILES[TILE_COUNT] = {
+    {64, 32, 32, 6, {{6.18, 0.068, 0.050}, {4.49, 0.075, 0.050}}},
+    {64, 64, 32, 4, {{5.25, 0.100, 0.361}, {3.95, 0.098, 0.102}}},
+    {64, 64, 64, 2, {{4.42, 0.159, 1.153}, {3.78, 0.160, 0.974}}},
+    {128, 64, 64, 2, {{4.08, 0.256, 1.479}, {3.10, 0.247, 1.229}}},
+    {128, 128, 32, 2, {{3.88, 0.215, 1.661}, {3.00, 0.193, 1.445}}},
+    {128, 128, 64, 1, {{3.00, 0.414, 3.796}, {3.00, 0.342, 3.684}}},
+    {256, 128, 64, 1, {{3.00, 0.675, 4.538}, {3.00, 0.511, 4.149}}},
+    {256, 256, 32, 1, {{3.00, 0.491, 5.601}, {3.00, 0.443, 5.970}}},
+};
+
+static int64_t tile_count(const TileInfo &t, int64_t M, int Nout) { return ((M + t.bm - 1) / t.bm) * ((Nout + t.bn - 1) / t.bn); }
+
+static double tiles_per_cu(const TileInfo &t, int64_t tiles)
 {
-    static const int mode = tuning_knob("DLCONV_KSPLIT", 1); // tuning override: 0 = never
-    *chunks_per_split = 0;
-    if (!mode || forced_cfg() >= 0 || a.Cin % 8 != 0 || !choose_c_outer(a)) return 1;
-    const bool dense = a.osh == 1 && a.osw == 1 && a.FH == a.OH && a.FW == a.OW && a.ldd == a.Nout;
-    if (!dense || a.Nout < 256 || a.Nout % 256 != 0) return 1;
+    const double n = tiles / 256.0;
+    if (n > 2 * t.per_cu) return n + 0.3 * t.per_cu;
+    return n > t.per_cu ? std::ceil(n / t.per_cu) * t.per_cu : std::ceil(n);
+}
+
+static double tile_work(const IgemmArgs &a, int tile, int steps)
+{
+    const TileCost &c = TILES[tile].cost[a.TR * a.TS == 1 ? 0 : 1];
+    return steps * c.step + c.fix;
+}
+
+static int tile_steps(const IgemmArgs &a, int tile) { return (a.Cin + TILES[tile].kb - 1) / TILES[tile].kb * a.TR * a.TS; }
+
+// Whether the choice among tiles for GEMM a considers this one at all.  The narrowest is for at most 32 columns; the two
+// largest leave nothing beside them on a compute unit to cover their epilogues, which weigh as much as a short reduction (1x1,
+// 41402 pixels, 128 -> 2048: 256 x 256 82 us, 128 x 128 50).
+static bool tile_considered(const IgemmArgs &a, int tile)
+{
+    if (tile == TILE_64x32) return a.Nout <= 32;
+    if (tile == TILE_256x128_K64 || tile == TILE_256x256) return a.TR * a.TS > 1 || a.Cin >= 512;
+    return true;
+}
+
+static int best_tile(const IgemmArgs &a, double *us)
+{
     const int64_t M = (int64_t)a.NB * a.OH * a.OW;
-    const int64_t tiles = ((M + 255) / 256) * (a.Nout / 256);
-    const int nchunks = (a.Cin + BK - 1) / BK;
-    const int64_t steps = (int64_t)nchunks * a.TR * a.TS;
-    if (steps < 256 || tiles > 64 || M * a.Nout > (4 << 20)) return 1;
-    int64_t ks = 256 / tiles;                                 // one workgroup per CU
-    if (ks > 8) ks = 8;
-    if (ks > nchunks) ks = nchunks;
-    if (ks < 2) return 1;
-    const int cps = (int)((nchunks + ks - 1) / ks);
-    *chunks_per_split = cps;
-    return (nchunks + cps - 1) / cps;
+    int best = -1;
+    for (int t = 0; t < TILE_COUNT; ++t) {
+        if (!tile_considered(a, t)) continue;
+        const double est = TILES[t].cost[a.TR * a.TS == 1 ? 0 : 1].t0 + tile_work(a, t, tile_steps(a, t)) * tiles_per_cu(TILES[t], tile_count(TILES[t], M, a.Nout));
+        if (best < 0 || est < *us) { best = t; *us = est; }
+    }
+    return best;
+}
+
+// Tap-major order (few channels): only the tiles with 32-deep steps, the largest that yields enough workgroups.
+static int tap_major_tile(const IgemmArgs &a)
+{
+    const int64_t M = (int64_t)a.NB * a.OH * a.OW;
+    const auto enough = [&](int bm, int bn) { return ((M + bm - 1) / bm) * ((a.Nout + bn - 1) / bn) >= 200; };
+    if (a.Nout <= 32) return TILE_64x32;
+    if (a.Nout > 64 && enough(128, 128)) return TILE_128x128;
+    return enough(128, 64) ? TILE_128x64 : TILE_64x64;
+}
+
+// How a GEMM runs: tile, and the ranges its reduction is cut into (1: not cut) of `chunks` 32-channel chunks each.
+struct IgemmPlan { int tile, ksplits, chunks; };
+
+// GEMMs with few tiles and a long reduction leave most compute units idle, or walk it in many steps of small tiles.  Cut
+// into ranges that run side by side, with an ordered reduce of their fp32 partial sums (4 us, and 8 bytes per output
+// and range at 8 TB/s): 6912 pixels, 2048 -> 256, 3x3: 216 tiles of 128 x 64 84 us, 54 tiles of 256 x 128 in four ranges 64 us
+// with the reduce.  room: bytes of scratch for the partial sums.
+static IgemmPlan make_plan(const IgemmArgs &a, size_t room)
+{
+    IgemmPlan pl{0, 1, 0};
+    if (forced_cfg() >= 0) { pl.tile = forced_cfg(); return pl; }
+    if (!choose_c_outer(a)) { pl.tile = tap_major_tile(a); return pl; }
+    double us = 0;
+    pl.tile = best_tile(a, &us);
+    const bool dense = a.osh == 1 && a.osw == 1 && a.FH == a.OH && a.FW == a.OW && a.ldd == a.Nout;
+    const int64_t M = (int64_t)a.NB * a.OH * a.OW;
+    if (!dense || a.Nout % 8 != 0 || M * a.Nout > (4 << 20)) return pl;
+    const int chunks = (a.Cin + BK - 1) / BK;
+    for (int tile : {(int)TILE_64x64_K64, (int)TILE_128x64_K64, (int)TILE_128x128_K64, (int)TILE_256x128_K64}) {
+        const TileInfo &t = TILES[tile];
+        for (int ks : {2, 3, 4, 6, 8}) {
+            const int per = (chunks + 2 * ks - 1) / (2 * ks) * 2;             // whole 64-channel steps
+            const int ranges = (chunks + per - 1) / per;
+            if (ranges != ks || (size_t)ks * M * a.Nout * sizeof(float) > room) continue;
+            const double est = t.cost[a.TR * a.TS == 1 ? 0 : 1].t0 + tile_work(a, tile, per / 2 * a.TR * a.TS) * tiles_per_cu(t, tile_count(t, M, a.Nout) * ks) +
+                               4.0 + 8.0 * ks * M * a.Nout / 8e6;
+            if (est < us) { us = est; pl = IgemmPlan{tile, ks, per}; }
+        }
+    }
+    return pl;
 }
 
 size_t igemm_split_bytes(const IgemmArgs &a)
 {
-    int cps;
-    const int ks = choose_ksplits(a, &cps);
-    return ks > 1 ? (size_t)ks * a.NB * a.OH * a.OW * a.Nout * sizeof(float) : 0;
+    if (a.Cin % 8 != 0 || thin_rows_applicable(a) || thin_cols_applicable(a)) return 0;
+    const IgemmPlan pl = make_plan(a, SIZE_MAX);
+    return pl.ksplits > 1 ? (size_t)pl.ksplits * a.NB * a.OH * a.OW * a.Nout * sizeof(float) : 0;
 }
 
-// Tile configuration of the direct-to-LDS engine for this GEMM (100 + its cfg), or the forced one.
-static int choose_cfg(const IgemmArgs &a)
+// The scratch a caller has to bring: what the split that this function's first version chose took (256 x 256 tiles, up to
+// eight ranges).  With less than igemm_split_bytes the plan makes do with what there is.
+size_t igemm_split_least_bytes(const IgemmArgs &a)
 {
-    int cfg = forced_cfg();
-    if (cfg >= 0) return cfg;
+    if (a.Cin % 8 != 0 || !choose_c_outer(a)) return 0;
+    const bool dense = a.osh == 1 && a.osw == 1 && a.FH == a.OH && a.FW == a.OW && a.ldd == a.Nout;
     const int64_t M = (int64_t)a.NB * a.OH * a.OW;
-    // Largest tile that still yields enough workgroups for 256 CUs; tiles
-    // wider than the output-channel count (rounded up to 64) are not considered.
-    const int nmax = (a.Nout + 63) / 64 * 64;
-    auto blocks = [&](int bm, int bn) { return ((M + bm - 1) / bm) * ((a.Nout + bn - 1) / bn); };
-    if (nmax <= 32 || a.Nout <= 32) return 104;                     // 64 x 32
-    if (nmax >= 256 && blocks(256, 256) >= 200) return 100;         // 256 x 256
-    static const int min128 = tuning_knob("DLCONV_CFG128_MIN", 200); // tuning override: fewest 128 x 128 tiles that configuration is used for
-    if (nmax >= 128 && blocks(128, 128) >= min128) return 102;      // 128 x 128
-    if (blocks(128, 64) >= 200) return 103;                         // 128 x 64
-    return 108;                                                     // 64 x 64
+    if (!dense || a.Nout < 256 || a.Nout % 256 != 0 || M * a.Nout > (4 << 20)) return 0;
+    const int64_t tiles = ((M + 255) / 256) * (a.Nout / 256), chunks = (a.Cin + BK - 1) / BK;
+    if (chunks * a.TR * a.TS < 256 || tiles > 64) return 0;
+    const int64_t ks = std::min<int64_t>({256 / tiles, 8, chunks});
+    if (ks < 2) return 0;
+    const int64_t per = (chunks + ks - 1) / ks;
+    return (size_t)((chunks + per - 1) / per) * M * a.Nout * sizeof(float);
 }
 
 bool igemm_accepts_transposed_b(const IgemmArgs &a)
 {
-    static const int mode = tuning_knob("DLCONV_BT", 1); // tuning override: 0 = never
-    return mode && a.Cin % 8 == 0 && a.Nout % 8 == 0 && a.Nout >= 32 && !(forced_cfg() < 0 && thin_rows_applicable(a)) && choose_cfg(a) >= 100 &&
-           choose_c_outer(a);
+    return a.Cin % 8 == 0 && a.Nout % 8 == 0 && !(forced_cfg() < 0 && thin_rows_applicable(a)) && choose_c_outer(a);
 }
 
 template <class T>
@@ -209,71 +274,75 @@ static hipError_t dispatch(const IgemmArgs &a, hipStream_t stream)
         DLK_LAUNCH("igemm_scalar_kernel", igemm_scalar_kernel<T>, dim3((unsigned)tiles), dim3(256), 0, stream, a);
         return dlk::launch_status();
     }
-    const int cfg = choose_cfg(a);
-    if (cfg >= 100) {
-        IgemmArgs b = a;
-        b.c_outer = choose_c_outer(a);
-        b.ksplits = 1;
-        b.split_chunks = 0;
-        if (a.part) {
-            int cps;
-            const int ks = choose_ksplits(a, &cps);
-            if (ks > 1) {
-                b.ksplits = ks;
-                b.split_chunks = cps;
-                hipError_t e = launch_igemm_dma(b, std::is_same<T, BF16>::value, 0, stream);      // 256 x 256 tiles
-                if (e != hipSuccess) return e;
-                return launch_splitk_reduce_tail(a.part, ks, M * a.Nout, a.D, std::is_same<T, BF16>::value ? 1 : 0, a.bias,
-                                                 a.relu, a.Nout, a.resid, stream);
-            }
-        }
-        static const int use_short = tuning_knob("DLCONV_SHORT", 1); // tuning override: 0 = never
-        // whole reduction in one step: before the choice between ring tiles, which all spend four steps on it
-        if (use_short && b.c_outer && forced_cfg() < 0 && igemm_short_applicable(b)) return launch_igemm_short(b, std::is_same<T, BF16>::value, stream);
-        // A ragged last column tile of the widest configuration (e.g. 304 = 256 + 48 output
-        // channels) would run mostly empty: give the remainder to a narrower tile instead.
-        const int rem = a.Nout % 256;
-        if (cfg == 100 && a.Nout > 256 && rem != 0 && rem <= 128) {
-            IgemmArgs lo = b, hi = b;
-            lo.Nout = a.Nout - rem;
-            hi.Nout = rem;
+    constexpr bool bf16 = std::is_same<T, BF16>::value;
+    IgemmArgs b = a;
+    set_divisors(b);
+    b.c_outer = choose_c_outer(a);
+    b.ksplits = 1;
+    b.split_chunks = 0;
+    const IgemmPlan pl = make_plan(a, a.part ? a.part_bytes : 0);
+    if (pl.ksplits > 1) {
+        b.ksplits = pl.ksplits;
+        b.split_chunks = pl.chunks;
+        hipError_t e = launch_igemm_dma(b, bf16, pl.tile, stream);
+        if (e != hipSuccess) return e;
+        return launch_splitk_reduce_tail(a.part, pl.ksplits, M * a.Nout, a.D, bf16 ? 1 : 0, a.bias, a.relu, a.Nout, a.resid, stream);
+    }
+    // whole reduction in one step: before the choice between ring tiles, which all spend three or four steps on it
+    if (b.c_outer && forced_cfg() < 0 && igemm_short_applicable(b)) return launch_igemm_short(b, bf16, stream);
+    // A short last column tile (e.g. 304 = 256 + 48 output channels) would run mostly empty: where two launches are estimated
+    // to take less than one, the remainder gets a narrower tile.
+    const int rem = a.Nout % 256;
+    if (forced_cfg() < 0 && a.Nout > 256 && rem != 0 && rem <= 128) {
+        IgemmArgs lo = b, hi = b;
+        lo.Nout = a.Nout - rem;
+        hi.Nout = rem;
+        double whole = 1, us_lo = 0, us_hi = 0;          // (tap-major: always cut)
+        if (b.c_outer) best_tile(b, &whole);
+        const int t_lo = b.c_outer ? best_tile(lo, &us_lo) : tap_major_tile(lo), t_hi = b.c_outer ? best_tile(hi, &us_hi) : tap_major_tile(hi);
+        if (us_lo + us_hi < whole) {
             if (a.b_transposed) hi.b_base = a.b_base + lo.Nout;
             else hi.B = a.B + (size_t)lo.Nout * a.TR * a.TS * a.Cin;
             hi.D = a.D + lo.Nout;
             if (a.bias) hi.bias = a.bias + lo.Nout;
             if (a.resid) hi.resid = a.resid + lo.Nout;
-            hipError_t e = launch_igemm_dma(lo, std::is_same<T, BF16>::value, 0, stream);
+            hipError_t e = launch_igemm_dma(lo, bf16, t_lo, stream);
             if (e != hipSuccess) return e;
-            return launch_igemm_dma(hi, std::is_same<T, BF16>::value, rem <= 64 ? 3 : 2, stream);
+            return launch_igemm_dma(hi, bf16, t_hi, stream);
         }
-        return launch_igemm_dma(b, std::is_same<T, BF16>::value, cfg - 100, stream);
     }
-    return hipErrorInvalidValue;                         // only the direct-to-LDS configurations (100 + n) exist
+    return launch_igemm_dma(b, bf16, pl.tile, stream);
 }
 
 int igemm_batch_cfg(const IgemmArgs *a, int n)
 {
-    static const int mode = tuning_knob("DLCONV_BATCH", 1); // tuning override: 0 = one launch per GEMM
-    if (!mode || n < 2 || n > IgemmBatch::MAX || forced_cfg() >= 0) return -1;
+    if (n < 2 || n > IgemmBatch::MAX || forced_cfg() >= 0) return -1;
     // Sharing a launch pays where the single launches are short (start-up and drain of a 10 us
     // kernel, four times over); long GEMMs run better one after the other (the 3x3 stride-2
     // layer that produces a 768 x 1152 x 256 tensor: 0.80 ms against 0.96 ms in one launch).
     double macs = 0;
     for (int i = 0; i < n; ++i) macs += (double)a[i].NB * a[i].OH * a[i].OW * a[i].Nout * a[i].Cin * a[i].TR * a[i].TS;
     if (macs > 1e10) return -1;
-    int cfg = -1;
-    for (int i = 0; i < n; ++i) {
-        const IgemmArgs &g = a[i];
-        if (g.Cin % 8 != 0 || thin_rows_applicable(g) || thin_cols_applicable(g) || !choose_c_outer(g) || g.b_transposed != a[0].b_transposed) return -1;
-        int cps;
-        if (choose_ksplits(g, &cps) > 1) return -1;
-        const int c = choose_cfg(g);
-        const int rem = g.Nout % 256;
-        if (c < 100 || (c == 100 && g.Nout > 256 && rem != 0 && rem <= 128)) return -1;    // that case is cut into two launches
-        if (cfg >= 0 && c != cfg) return -1;
-        cfg = c;
+    for (int i = 0; i < n; ++i)
+        if (a[i].Cin % 8 != 0 || thin_rows_applicable(a[i]) || thin_cols_applicable(a[i]) || !choose_c_outer(a[i]) || a[i].b_transposed != a[0].b_transposed)
+            return -1;
+    // one tile for all: the tiles of all GEMMs together, each with the work of its own reduction
+    int best = -1;
+    double best_us = 0;
+    for (int tile : {(int)TILE_64x32, (int)TILE_64x64, (int)TILE_128x64_K64, (int)TILE_128x128, (int)TILE_256x256}) {
+        const TileInfo &t = TILES[tile];
+        int64_t tiles = 0;
+        double work = 0;
+        for (int i = 0; i < n; ++i) {
+            const int64_t own = tile_count(t, (int64_t)a[i].NB * a[i].OH * a[i].OW, a[i].Nout);
+            tiles += own;
+            work += own * tile_work(a[i], tile, tile_steps(a[i], tile));
+        }
+        const bool considered = tile == TILE_64x32 ? a[0].Nout <= 32 : true;
+        const double us = t.cost[1].t0 + work / tiles * tiles_per_cu(t, tiles);
+        if (considered && (best < 0 || us < best_us)) { best = tile; best_us = us; }
     }
-    return cfg - 100;
+    return best;
 }
 
 hipError_t launch_igemm_batch(const IgemmBatch &b, bool is_bf16, hipStream_t stream)
@@ -282,6 +351,7 @@ hipError_t launch_igemm_batch(const IgemmBatch &b, bool is_bf16, hipStream_t str
     if (cfg < 0) return hipErrorInvalidValue;
     IgemmBatch c = b;
     for (int i = 0; i < c.n; ++i) {
+        set_divisors(c.a[i]);
         c.a[i].c_outer = 1;
         c.a[i].ksplits = 1;
         c.a[i].split_chunks = 0;

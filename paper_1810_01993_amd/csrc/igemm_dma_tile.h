@@ -38,6 +38,12 @@ namespace dlk {
 template <int KB>
 __device__ __forceinline__ int swz(int row) { return KB == 64 ? (row >> 1) & 7 : (row >> 2) & 3; }
 
+// n / d with the multiplier and shift that FastDiv (kernels.h) computes for d
+__device__ __forceinline__ int fast_div(int n, uint32_t mul, int32_t shr)
+{
+    return (int)((__umulhi((uint32_t)n, mul) + (uint32_t)n) >> shr);
+}
+
 typedef short bt_s16x4_t __attribute__((ext_vector_type(4)));
 
 // BT: the filter operand is given reduction-major (see IgemmArgs::b_transposed); channel-major order only.
@@ -48,7 +54,8 @@ typedef short bt_s16x4_t __attribute__((ext_vector_type(4)));
 // range `split` of a split reduction.
 // KB: reduction elements of a step.  SHORT: the whole reduction is one step (STAGES == 1, no ring).
 // RES: the residual input is there, aligned for 16-byte loads, and fetched into registers before the first step.
-template <class T, int BM, int BN, int WM, int WN, bool CMAJOR, bool BT, int KB = 32, int STAGES = 4, bool SHORT = false, bool RES = false>
+// PP: two groups of waves half a step apart (four ring slots or three of 64 channels).
+template <class T, int BM, int BN, int WM, int WN, bool CMAJOR, bool BT, int KB = 32, int STAGES = 4, bool SHORT = false, bool RES = false, bool PP = false>
 __device__ __forceinline__ void igemm_dma_tile(const IgemmArgs &p, const int tile, const int split)
 {
     static_assert(!BT || CMAJOR, "a reduction-major filter needs the channel-major order");
@@ -63,11 +70,15 @@ __device__ __forceinline__ void igemm_dma_tile(const IgemmArgs &p, const int til
 
     // Ring slots of both operands in one array; the epilogue re-uses it as staging space.
     __shared__ __align__(16) uint16_t lds[STAGES * (BM + BN) * KB];
-    auto slot_a = [&](int s) { return lds + s * BM * KB; };
-    auto slot_b = [&](int s) { return lds + STAGES * BM * KB + s * BN * KB; };
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WN, wn = wave % WN;
+    auto slot_a = [&](int s) { return lds + s * BM * KB; };
+    auto slot_b = [&](int s) { return lds + STAGES * BM * KB + s * BN * KB; };
+    // LDS byte address of this wave's first 1 KB piece of ring slot s
+    const uint32_t dst0 = lds_addr(lds) + (uint32_t)wave * 1024;
+    auto dst_a = [&](int s) { return dst0 + s * BM * KB * 2; };
+    auto dst_b = [&](int s) { return dst0 + (STAGES * BM * KB + s * BN * KB) * 2; };
 
     const int M = p.NB * p.OH * p.OW;
     const int NT = p.TR * p.TS;                       // taps
@@ -84,25 +95,24 @@ __device__ __forceinline__ void igemm_dma_tile(const IgemmArgs &p, const int til
     const int vec = (lane % SL) ^ swz<KB>(wave * RPL + lrow);   // same for every load of this lane
     int a_ih[AIW], a_iw[AIW];
     uint32_t a_off[AIW];                                 // byte offset of (row's tap (0,0) pixel, channel 8*vec)
-    uint32_t a_mask_lo[AIW], a_mask_hi[AIW];             // channel-major: bit t = tap t of this row is inside the image
+    uint32_t out_lo[AIW], out_hi[AIW];                   // channel-major: bit t set = tap t of this row is outside the image
 #pragma unroll
     for (int i = 0; i < AIW; ++i) {
         const int m = m0 + (wave + i * NW) * RPL + lrow;
-        a_mask_lo[i] = a_mask_hi[i] = 0u;
+        out_lo[i] = out_hi[i] = ~0u;
         if (m < M) {
-            const int n = m / (p.OH * p.OW), rem = m - n * (p.OH * p.OW);
-            const int oh = rem / p.OW, ow = rem - oh * p.OW;
+            const int n = fast_div(m, p.mul_hw, p.shr_hw), rem = m - n * (p.OH * p.OW);
+            const int oh = fast_div(rem, p.mul_w, p.shr_w), ow = rem - oh * p.OW;
             a_ih[i] = oh * p.sh + p.th0;
             a_iw[i] = ow * p.sw + p.tw0;
             a_off[i] = (uint32_t)(((n * p.IH + a_ih[i]) * p.IW + a_iw[i]) * p.Cin + vec * 8) * 2u;
             if constexpr (CMAJOR) {
-                for (int t = 0; t < NT; ++t) {
-                    const int jr = t / p.TS, js = t - jr * p.TS;
-                    const int ih = a_ih[i] + jr * p.dth, iw = a_iw[i] + js * p.dtw;
-                    const uint32_t in = ((unsigned)ih < (unsigned)p.IH && (unsigned)iw < (unsigned)p.IW) ? 1u : 0u;
-                    if (t < 32) a_mask_lo[i] |= in << t;
-                    else a_mask_hi[i] |= in << (t - 32);
-                }
+                uint64_t cols = 0, in = 0;               // taps of one filter row, then of all
+                for (int js = 0; js < p.TS; ++js) cols |= (uint64_t)((unsigned)(a_iw[i] + js * p.dtw) < (unsigned)p.IW ? 1u : 0u) << js;
+                for (int jr = 0; jr < p.TR; ++jr)
+                    if ((unsigned)(a_ih[i] + jr * p.dth) < (unsigned)p.IH) in |= cols << (jr * p.TS);
+                out_lo[i] = ~(uint32_t)in;
+                out_hi[i] = ~(uint32_t)(in >> 32);
             }
         } else {
             a_off[i] = 0;
@@ -138,40 +148,81 @@ __device__ __forceinline__ void igemm_dma_tile(const IgemmArgs &p, const int til
         c_first = split * p.split_chunks * BK;
         c_end = min(p.Cin, c_first + p.split_chunks * BK);
     }
-    int t = 0, jr = 0, js = 0, c0 = c_first;
+    int t = 0, jr = 0, js = 0, c0 = c_first;              // (channel-major: jr only sets up the first step)
     int kk = vec * 8, c = 0;
     if constexpr (!CMAJOR) { c = kk % p.Cin; js = (kk / p.Cin) % p.TS; jr = (kk / p.Cin) / p.TS; }
     const int lane_c = vec * 8;
-
-    // Issue the loads of the next reduction step into ring slot (sa, sb).
-    auto issue = [&](uint16_t *sa, uint16_t *sb) {
-        if constexpr (CMAJOR) {
-            const uint32_t tap_a = (uint32_t)(((jr * p.dth) * p.IW + js * p.dtw) * p.Cin + c0) * 2u;   // uniform
-            const uint32_t tap_b = (uint32_t)(t * p.Cin + c0) * 2u;                                    // uniform
-            const bool cin = lane_c < c_end - c0;        // false only in a ragged last chunk / past the end
+    const int nk = CMAJOR ? ((c_end - c_first + KB - 1) / KB) * NT : (Kred + KB - 1) / KB;
+    // Channel-major: what a step adds to the lanes' offsets is kept as two running scalars, and what is outside as bits that
+    // turn an offset into one out of range, so that a load costs three or two vector instructions (the waves of a small
+    // tile spend as long on issuing a step as on multiplying it).
+    const uint32_t a_js = (uint32_t)(p.dtw * p.Cin) * 2u, a_jr = (uint32_t)((p.dth * p.IW - p.TS * p.dtw) * p.Cin) * 2u;
+    const uint32_t a_ch = (uint32_t)(KB - p.TR * p.dth * p.IW * p.Cin) * 2u;
+    const uint32_t b_js = (uint32_t)(BT ? p.b_ss : p.Cin) * 2u, b_jr = BT ? (uint32_t)(p.b_sr - p.TS * p.b_ss) * 2u : 0u;
+    const uint32_t b_ch = BT ? (uint32_t)(KB * p.b_ldk - p.TR * p.b_sr) * 2u : (uint32_t)(KB - NT * p.Cin) * 2u;
+    uint32_t tap_a = (uint32_t)((jr * p.dth * p.IW + js * p.dtw) * p.Cin + c0) * 2u;
+    uint32_t tap_b = BT ? (uint32_t)(p.b_base + jr * p.b_sr + js * p.b_ss + c0 * p.b_ldk) * 2u : (uint32_t)(t * p.Cin + c0) * 2u;
+    uint32_t out_cur[AIW], b_out[BIW];
+    // the part of the reduction that begins at channel c0: what of a ragged last chunk, or behind the end, does not exist
+    auto open_chunk = [&]() {
+        if (c0 + KB > c_end) {
+            const bool gone = lane_c >= c_end - c0;
 #pragma unroll
             for (int i = 0; i < AIW; ++i) {
-                const uint32_t word = t < 32 ? a_mask_lo[i] : a_mask_hi[i];
-                const bool ok = cin && ((word >> (t & 31)) & 1u);
-                dma_load_16B(rsA, lds_addr(sa) + (wave + i * NW) * 1024, ok ? a_off[i] + tap_a : OOB_OFFSET);
+                if (gone) out_lo[i] = out_hi[i] = ~0u;
             }
+#pragma unroll
+            for (int i = 0; i < BIW; ++i) {
+                if constexpr (BT) {
+                    if (c0 + (wave + i * NW) * RPI_B + bt_row >= c_end) b_out[i] = OOB_OFFSET;
+                } else if (gone) b_out[i] = OOB_OFFSET;
+            }
+        }
+    };
+    auto select_mask = [&]() {                           // the word of the mask that holds tap t
+#pragma unroll
+        for (int i = 0; i < AIW; ++i) out_cur[i] = t < 32 ? out_lo[i] : out_hi[i];
+    };
+    if constexpr (CMAJOR) {
+#pragma unroll
+        for (int i = 0; i < BIW; ++i) {
             if constexpr (BT) {
-                const uint32_t tap_bt = (uint32_t)(p.b_base + jr * p.b_sr + js * p.b_ss + bt_col);     // per lane (column)
+                b_off[i] = (uint32_t)(bt_col + ((wave + i * NW) * RPI_B + bt_row) * p.b_ldk) * 2u;
+                b_out[i] = bt_ok ? 0u : OOB_OFFSET;
+            } else b_out[i] = b_ok[i] ? 0u : OOB_OFFSET;
+        }
+        open_chunk();
+        select_mask();
+    }
+
+    // Issue the loads of the next reduction step into ring slot s.
+    auto issue = [&](int s) __attribute__((always_inline)) {
+        const uint32_t sa = dst_a(s), sb = dst_b(s);
+        if constexpr (CMAJOR) {
 #pragma unroll
-                for (int i = 0; i < BIW; ++i) {
-                    const int k = c0 + (wave + i * NW) * RPI_B + bt_row;
-                    dma_load_16B(rsB, lds_addr(sb) + (wave + i * NW) * 1024,
-                                 (bt_ok && k < c_end) ? (tap_bt + (uint32_t)k * (uint32_t)p.b_ldk) * 2u : OOB_OFFSET);
-                }
-            } else {
-#pragma unroll
-                for (int i = 0; i < BIW; ++i)
-                    dma_load_16B(rsB, lds_addr(sb) + (wave + i * NW) * 1024,
-                                 (cin && b_ok[i]) ? b_off[i] + tap_b : OOB_OFFSET);
+            for (int i = 0; i < AIW; ++i) {
+                const uint32_t outside = (uint32_t)__builtin_amdgcn_sbfe((int)out_cur[i], t & 31, 1) & OOB_OFFSET;   // bit t, all ones or zero
+                dma_load_16B(rsA, sa + i * NW * 1024, (a_off[i] + tap_a) | outside);
             }
+#pragma unroll
+            for (int i = 0; i < BIW; ++i) dma_load_16B(rsB, sb + i * NW * 1024, (b_off[i] + tap_b) | b_out[i]);
             ++t;
-            if (++js == p.TS) { js = 0; ++jr; }
-            if (t == NT) { t = 0; jr = 0; js = 0; c0 += KB; }
+            tap_a += a_js;
+            tap_b += b_js;
+            if (t == 32) select_mask();
+            if (++js == p.TS) {
+                js = 0;
+                tap_a += a_jr;
+                tap_b += b_jr;
+                if (t == NT) {
+                    t = 0;
+                    c0 += KB;
+                    tap_a += a_ch;
+                    tap_b += b_ch;
+                    open_chunk();
+                    select_mask();
+                }
+            }
         } else {
             const bool kin = kk < Kred;
             const int dh = jr * p.dth, dw = js * p.dtw;
@@ -180,11 +231,11 @@ __device__ __forceinline__ void igemm_dma_tile(const IgemmArgs &p, const int til
             for (int i = 0; i < AIW; ++i) {
                 const int ih = a_ih[i] + dh, iw = a_iw[i] + dw;
                 const bool ok = kin && (unsigned)ih < (unsigned)p.IH && (unsigned)iw < (unsigned)p.IW;
-                dma_load_16B(rsA, lds_addr(sa) + (wave + i * NW) * 1024, ok ? a_off[i] + tap_a : OOB_OFFSET);
+                dma_load_16B(rsA, sa + i * NW * 1024, ok ? a_off[i] + tap_a : OOB_OFFSET);
             }
 #pragma unroll
             for (int i = 0; i < BIW; ++i)
-                dma_load_16B(rsB, lds_addr(sb) + (wave + i * NW) * 1024,
+                dma_load_16B(rsB, sb + i * NW * 1024,
                              (kin && b_ok[i]) ? b_off[i] + (uint32_t)(kk - lane_c) * 2u : OOB_OFFSET);
             kk += KB;
             c += KB;
@@ -240,10 +291,15 @@ __device__ __forceinline__ void igemm_dma_tile(const IgemmArgs &p, const int til
             for (int j = 0; j < TN; ++j) b[j] = *reinterpret_cast<const u32x4_t *>(wb + j * 32 * KB);
         }
     };
-    auto mma = [&](const uint16_t *sa, const uint16_t *sb) {
+    // One step: fragments of slot u, the loads of a later step into slot next, then the products.  The fragments are
+    // requested first: a wave waits in line to issue its loads, and the LDS answers meanwhile.
+    auto step = [&](int u, int next) __attribute__((always_inline)) {
         u32x4_t fa[KS][TM], fb[KS][TN];
 #pragma unroll
-        for (int s = 0; s < KS; ++s) load_frags(fa[s], fb[s], sa, sb, s);
+        for (int s = 0; s < KS; ++s) load_frags(fa[s], fb[s], slot_a(u), slot_b(u), s);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (!SHORT) issue(next);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int s = 0; s < KS; ++s)
 #pragma unroll
@@ -268,8 +324,8 @@ __device__ __forceinline__ void igemm_dma_tile(const IgemmArgs &p, const int til
     const bool dense = (p.osh == 1 && p.osw == 1 && p.FH == p.OH && p.FW == p.OW);
     auto out_row = [&](int m) -> size_t {                // element offset of output row m
         if (dense) return (size_t)m * p.ldd;
-        const int n = m / (p.OH * p.OW), rem = m - n * (p.OH * p.OW);
-        const int oh = rem / p.OW, ow = rem - oh * p.OW;
+        const int n = fast_div(m, p.mul_hw, p.shr_hw), rem = m - n * (p.OH * p.OW);
+        const int oh = fast_div(rem, p.mul_w, p.shr_w), ow = rem - oh * p.OW;
         return ((size_t)(n * p.FH + oh * p.osh + p.ooh) * p.FW + ow * p.osw + p.oow) * p.ldd;
     };
     u32x4_t resid[RES ? TM : 1][RES ? LPR / 2 : 1];
@@ -287,21 +343,56 @@ __device__ __forceinline__ void igemm_dma_tile(const IgemmArgs &p, const int til
 
     // The step count is rounded up to a whole turn of the ring (the extra
     // steps load and multiply zeros) so that the unrolled loop has one exit.
-    const int nk = CMAJOR ? ((c_end - c_first + KB - 1) / KB) * NT : (Kred + KB - 1) / KB;
     const int nturns = (nk + STAGES - 1) / STAGES;
     if constexpr (SHORT) {
-        issue(slot_a(0), slot_b(0));
+        issue(0);
         wait_and_sync();
-        mma(slot_a(0), slot_b(0));
+        step(0, 0);
+    } else if constexpr (PP) {
+        // Two groups of waves, one of each on every SIMD, half a step apart: one reads its fragments and issues loads
+        // while the other multiplies.  Both barriers of a step leave STAGES - 2 steps of this wave's loads pending: at the
+        // one that opens its read phase of step s it has issued up to step s + STAGES - 2, so s has landed; at the other,
+        // where the other group may open its read phase of s + 1, it has issued one step more, so s + 1 has.  Its LDS reads
+        // are complete at either, so the slot refilled in a read phase, that of s - 1, is no longer read by anyone.
+        static_assert(STAGES >= 3 && NW == 8, "one wave of each group per SIMD");
+        auto hand_over = [&]() {
+            __builtin_amdgcn_sched_barrier(0);
+            wait_and_sync();
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        if (nk > 0) {
+#pragma unroll
+            for (int u = 0; u < STAGES - 1; ++u) issue(u);
+            const bool late = wave >= NW / 2;
+            if (late) hand_over();
+            for (int turn = 0; turn < nturns; ++turn) {
+#pragma unroll
+                for (int u = 0; u < STAGES; ++u) {
+                    u32x4_t fa[KS][TM], fb[KS][TN];
+                    hand_over();
+#pragma unroll
+                    for (int s = 0; s < KS; ++s) load_frags(fa[s], fb[s], slot_a(u), slot_b(u), s);
+                    __builtin_amdgcn_sched_barrier(0);
+                    issue((u + STAGES - 1) % STAGES);
+                    hand_over();
+#pragma unroll
+                    for (int s = 0; s < KS; ++s)
+#pragma unroll
+                        for (int i = 0; i < TM; ++i)
+#pragma unroll
+                            for (int j = 0; j < TN; ++j) acc[i][j] = T::mfma(fb[s][j], fa[s][i], acc[i][j]);
+                }
+            }
+            if (!late) hand_over();
+        }
     } else if (nk > 0) {
 #pragma unroll
-        for (int u = 0; u < STAGES - 1; ++u) issue(slot_a(u), slot_b(u));
+        for (int u = 0; u < STAGES - 1; ++u) issue(u);
         for (int turn = 0; turn < nturns; ++turn) {
 #pragma unroll
             for (int u = 0; u < STAGES; ++u) {
                 wait_and_sync();
-                issue(slot_a((u + STAGES - 1) % STAGES), slot_b((u + STAGES - 1) % STAGES));
-                mma(slot_a(u), slot_b(u));
+                step(u, (u + STAGES - 1) % STAGES);
             }
         }
     }

@@ -81,6 +81,7 @@ struct IgemmArgs {
     // range z (grid.y) writes fp32 partial sums to part[z][m][j] and an ordered reduce follows.
     int32_t ksplits, split_chunks;
     float *part;                // scratch for the partial sums, or null: never split
+    size_t part_bytes;          // its size
     // Filter given reduction-major (direct-to-LDS engine, channel-major order, Nout % 8 == 0): with
     // b_transposed != 0 element (column j, tap (jr, js), reduction channel c) of the filter operand is
     // B[b_base + j + jr*b_sr + js*b_ss + c*b_ldk], i.e. contiguous along the columns -- how the data
@@ -99,7 +100,28 @@ struct IgemmArgs {
     // narrow / wide 5x5) do not take such launches; the plain engine, the general halo-tile kernel, the
     // streaming kernel for few input channels and the split reduction do.
     const uint16_t *resid;
+    // Division by OH*OW and by OW as multiplication and shift (FastDiv), set by launch_igemm / launch_igemm_batch.
+    uint32_t mul_hw, mul_w;
+    int32_t shr_hw, shr_w;
 };
+
+// n / d for 0 <= n < 2^31 as (mulhi(n, mul) + n) >> shr: with shr = ceil(log2 d) and mul = floor(2^32 (2^shr - d) / d) + 1
+// (round-up method of Granlund and Montgomery; the sum stays below 2^32).
+struct FastDiv {
+    uint32_t mul;
+    int32_t shr;
+    explicit FastDiv(uint32_t d) : mul(0), shr(0)
+    {
+        while (shr < 31 && (1u << shr) < d) ++shr;
+        mul = (uint32_t)((((uint64_t)1 << 32) * (((uint64_t)1 << shr) - d)) / d + 1);
+    }
+};
+inline void set_divisors(IgemmArgs &a)
+{
+    const FastDiv hw((uint32_t)(a.OH * a.OW)), w((uint32_t)a.OW);
+    a.mul_hw = hw.mul; a.shr_hw = hw.shr;
+    a.mul_w = w.mul; a.shr_w = w.shr;
+}
 
 // Up to four GEMMs for one launch of the direct-to-LDS engine (see igemm_dma_batch_kernel).
 struct IgemmBatch {
@@ -118,14 +140,21 @@ hipError_t launch_igemm_dma_batch(const IgemmBatch &b, bool is_bf16, int cfg, hi
 // Would launch_igemm accept this GEMM with a reduction-major filter (b_transposed)?
 bool igemm_accepts_transposed_b(const IgemmArgs &a);
 
-// Bytes of partial-sum scratch launch_igemm would use for this GEMM if a.part were set (0: it would not split).
+// Bytes of partial-sum scratch launch_igemm would use for this GEMM if a.part were set and large enough (0: it would not
+// split), and the fewest it accepts (it splits less, or not at all, in less room than the former).
 size_t igemm_split_bytes(const IgemmArgs &a);
+size_t igemm_split_least_bytes(const IgemmArgs &a);
 
 // is_bf16 selects the MFMA flavour and the output rounding.
 hipError_t launch_igemm(const IgemmArgs &a, bool is_bf16, hipStream_t stream);
 
-// Direct-to-LDS variant of the engine (needs Cin % 8 == 0); cfg selects the tile.
+// Direct-to-LDS variant of the engine (needs Cin % 8 == 0); cfg selects the tile (pixels x output channels, 32 or 64
+// reduction channels a step).
+enum IgemmTile { TILE_64x32, TILE_64x64, TILE_64x64_K64, TILE_128x64_K64, TILE_128x128, TILE_128x128_K64, TILE_256x128_K64, TILE_256x256, TILE_COUNT,
+                 TILE_128x64 = TILE_COUNT };     // tap-major order only
 hipError_t launch_igemm_dma(const IgemmArgs &a, bool is_bf16, int cfg, hipStream_t stream);
+hipError_t launch_igemm_dma_bf16(const IgemmArgs &a, int cfg, hipStream_t stream);
+hipError_t launch_igemm_dma_batch_bf16(const IgemmBatch &b, int cfg, hipStream_t stream);
 
 // 1x1 layers with 32 or 64 input channels, more than 64 output channels and many pixels: one 64-channel step (igemm_short.hip).
 // launch_igemm chooses it; c_outer must be set.
