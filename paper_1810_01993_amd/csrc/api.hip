@@ -272,7 +272,7 @@ bool use_wgrad5x5(const dl_conv_desc *d)
 }
 
 // room: bytes of workspace the plan may use.  A caller that brings fewer bytes than the preferred plan takes (say, the size
-// that an earlier version of the library asked for) gets the plan without the fetch term, whose slices were as few.
+// that an earlier version of the library asked for) gets as many slices as they hold, down to wgrad_least_slices.
 dlk::WgradPlan wgrad_plan(const dl_conv_desc *d, const Geometry &g, size_t room = SIZE_MAX)
 {
     if (use_wgrad5x5(d)) {
@@ -284,16 +284,28 @@ dlk::WgradPlan wgrad_plan(const dl_conv_desc *d, const Geometry &g, size_t room 
         return dlk::WgradPlan{-3, p3.slices, 0};
     }
     const bool thin = dlk::thin_wgrad_applicable(d->K, d->C, d->R, d->S, d->stride_h, d->stride_w, d->pad_h, d->pad_w);
-    const auto plan = [&](bool fetch_term) {
-        return dlk::wgrad_make_plan((int64_t)d->N * g.P * g.Q, g.x_elems, d->K, d->C, d->R * d->S * d->C, thin, fetch_term);
+    const auto plan = [&](bool fetch_term, int64_t max_splits) {
+        return dlk::wgrad_make_plan((int64_t)d->N * g.P * g.Q, g.x_elems, d->K, d->C, d->R * d->S * d->C, thin, fetch_term, max_splits);
     };
-    const dlk::WgradPlan best = plan(true);
-    return (size_t)best.splits * (size_t)g.w_elems * sizeof(float) <= room ? best : plan(false);
+    const size_t slice = (size_t)g.w_elems * sizeof(float);
+    const dlk::WgradPlan best = plan(true, INT64_MAX);
+    if (best.cfg < 0 || best.splits * slice <= room) return best;
+    const int64_t least = std::min(best.splits, dlk::wgrad_least_slices((int64_t)d->N * g.P * g.Q, g.x_elems, d->K, d->C, d->R * d->S * d->C));
+    const int64_t fit = (int64_t)(room / slice);
+    return fit < least ? best : plan(false, fit);                  // (too little: the caller refuses)
 }
 
 size_t wgrad_own_workspace(const dl_conv_desc *d, const Geometry &g, size_t room = SIZE_MAX)
 {
     return (size_t)wgrad_plan(d, g, room).splits * (size_t)g.w_elems * sizeof(float);
+}
+
+// The fewest bytes a filter gradient runs with.
+size_t wgrad_least_workspace(const dl_conv_desc *d, const Geometry &g)
+{
+    const dlk::WgradPlan best = wgrad_plan(d, g);
+    const int least = best.cfg < 0 ? best.splits : std::min(best.splits, dlk::wgrad_least_slices((int64_t)d->N * g.P * g.Q, g.x_elems, d->K, d->C, d->R * d->S * d->C));
+    return (size_t)least * (size_t)g.w_elems * sizeof(float);
 }
 
 // As fwd_padded_workspace, for the filter gradient: partial sums of the padded filter, then the copy of x.
@@ -435,7 +447,7 @@ dl_status dl_conv_least_workspace_bytes(const dl_conv_desc *desc, int pass, size
             *bytes = dgrad_workspace(desc, g, use_dgrad_stem(desc), true);
             if (desc->C % 8 != 0) *bytes = std::min(*bytes, dgrad_workspace(desc, g, false, true));
             return DL_OK;
-        case DL_PASS_BWD_FILTER: *bytes = std::min(wgrad_own_workspace(desc, g), wgrad_own_workspace(desc, g, 0)); return DL_OK;
+        case DL_PASS_BWD_FILTER: *bytes = wgrad_least_workspace(desc, g); return DL_OK;
     }
     return DL_ERR_UNSUPPORTED;
 }

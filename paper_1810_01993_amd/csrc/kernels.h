@@ -252,7 +252,9 @@ struct WgradPlan {
     int chunk;                  // pixels per slice, multiple of 32
     int spread;                 // see WgradArgs
 };
-WgradPlan wgrad_make_plan(int64_t npix, int64_t x_elems, int K, int C, int RSC, bool thin_ok, bool fetch_term);
+// max_splits: the most slices there is room for (one is always planned for)
+WgradPlan wgrad_make_plan(int64_t npix, int64_t x_elems, int K, int C, int RSC, bool thin_ok, bool fetch_term, int64_t max_splits);
+int wgrad_least_slices(int64_t npix, int64_t x_elems, int K, int C, int RSC);
 
 // Filter gradient of dense RxR (3x3 or 5x5), stride 1, dilation 1, "same"-padded layers on large images by
 // the strip-walk kernels (cfg -3 / -4 of the plan): all taps per workgroup, partial[slice][K][R*R][C].

@@ -15,7 +15,7 @@
 // The pixel range is cut into `splits` slices; every slice writes an fp32
 // partial tile and a second kernel adds the slices in a fixed order.
 #include <algorithm>
-#include <cstdlib>
+#include <cmath>
 
 #include "device_common.h"
 #include "kernels.h"
@@ -24,23 +24,6 @@ namespace dlk {
 
 typedef short s16x4_t __attribute__((ext_vector_type(4)));
 
-struct PixCursor {            // (n, p, q) of one output pixel, advanced without division
-    int n, p, q;
-    __device__ __forceinline__ void init(int pix, int P, int Q) {
-        n = pix / (P * Q);
-        const int rem = pix - n * (P * Q);
-        p = rem / Q;
-        q = rem - p * Q;
-    }
-    __device__ __forceinline__ void advance(int by, int P, int Q) {
-        q += by;
-        while (q >= Q) {
-            q -= Q;
-            if (++p == P) { p = 0; ++n; }
-        }
-    }
-};
-
 // LDS image of a tile: row = pixel (BX channels = 2*BX bytes), and within a
 // row the 32-byte block b (16 channels) sits at block b ^ (2 * (pixel & 3))
 // (b ^ (pixel & 3) for rows of only four blocks).  Half a wave (the unit a
@@ -48,22 +31,25 @@ struct PixCursor {            // (n, p, q) of one output pixel, advanced without
 // blocks; rows are a multiple of the 256-byte bank width apart, and the rule
 // puts those eight 32-byte pieces on eight different bank ranges.
 __device__ __host__ constexpr int swz_shift(int BX) { return BX >= 128 ? 1 : 0; }
-template <class T, int BM, int BN, int WM, int WN, int STAGES>
+// KB: pixels of a step.  LINEAR: 1x1, unit stride, no padding, so x is read like dy.  PP: two groups of waves half a step apart.
+template <class T, int BM, int BN, int WM, int WN, int KB, int STAGES, bool PP, bool LINEAR>
 __global__ __launch_bounds__(WM *WN * 64) void wgrad_dma_kernel(const WgradArgs p)
 {
     constexpr int NW = WM * WN;
     constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
     constexpr int LPR_A = BM / 8, LPR_B = BN / 8;          // lanes (16-byte chunks) per pixel row
     constexpr int PPI_A = 64 / LPR_A, PPI_B = 64 / LPR_B;  // pixel rows per load instruction
-    constexpr int AIW = BK / PPI_A / NW, BIW = BK / PPI_B / NW;   // load instructions per wave per step
+    constexpr int AIW = KB / PPI_A / NW, BIW = KB / PPI_B / NW;   // load instructions per wave per step
     static_assert(BM >= 64 && BN >= 64 && BM <= 512 && BN <= 512, "a row must be 4..32 chunks of 32 bytes");
-    static_assert((BK / PPI_A) % NW == 0 && (BK / PPI_B) % NW == 0, "every wave must issue the same number of loads");
+    static_assert((KB / PPI_A) % NW == 0 && (KB / PPI_B) % NW == 0, "every wave must issue the same number of loads");
     static_assert(AIW >= 1 && BIW >= 1 && TM >= 1 && TN >= 1, "tile too small for this many waves");
     static_assert(STAGES == 3 || STAGES == 4, "ring of 3 or 4 LDS buffers");
+    static_assert(!PP || NW == 8, "one wave of each group per SIMD");
     constexpr int IN_FLIGHT = (STAGES - 2) * (AIW + BIW);
 
-    __shared__ __align__(16) uint16_t sA0[BK * BM], sA1[BK * BM], sA2[BK * BM], sA3[STAGES == 4 ? BK * BM : 8];
-    __shared__ __align__(16) uint16_t sB0[BK * BN], sB1[BK * BN], sB2[BK * BN], sB3[STAGES == 4 ? BK * BN : 8];
+    __shared__ __align__(16) uint16_t lds[STAGES * KB * (BM + BN)];
+    auto slot_a = [&](int s) { return lds + s * KB * BM; };
+    auto slot_b = [&](int s) { return lds + STAGES * KB * BM + s * KB * BN; };
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WN, wn = wave % WN;
@@ -95,41 +81,91 @@ __global__ __launch_bounds__(WM *WN * 64) void wgrad_dma_kernel(const WgradArgs 
     // pixel & 3 is the same for all of this lane's instructions (see static_asserts on NW / PPI)
     const int a_pix3 = ((wave * PPI_A) + a_prow) & 3;
     const int a_ch = k0 + ((((a_pchunk >> 1) ^ (a_pix3 << swz_shift(BM))) << 1) | (a_pchunk & 1)) * 8;
-    const bool a_ok = a_ch < p.K;
 
     const int b_prow = lane / LPR_B, b_pchunk = lane % LPR_B;
     const int b_pix3 = ((wave * PPI_B) + b_prow) & 3;
     const int b_col = j0 + ((((b_pchunk >> 1) ^ (b_pix3 << swz_shift(BN))) << 1) | (b_pchunk & 1)) * 8;
-    const bool b_ok = b_col < RSC;
-    const int b_tap = b_col / p.C, b_c = b_col - b_tap * p.C;
+    const int b_tap = LINEAR ? 0 : b_col / p.C, b_c = b_col - b_tap * p.C;
     const int b_r = b_tap / p.S, b_s = b_tap - b_r * p.S;
     const int b_dh = b_r * p.dh - p.ph, b_dw = b_s * p.dw - p.pw;
     static_assert((NW * PPI_A) % 4 == 0 && (NW * PPI_B) % 4 == 0, "swizzle must not depend on the instruction index");
 
-    PixCursor cur[BIW];
+    // Byte offsets and the pixels they stand for run along with the steps: what lies outside is or-ed with OOB_OFFSET, the
+    // pixel's place in x moves by additions and selects (a decoded pixel costs six multiplications a load, which a wave
+    // issues in the time of three MFMAs).
+    const uint32_t a_bad = a_ch < p.K ? 0u : OOB_OFFSET, b_bad = b_col < RSC ? 0u : OOB_OFFSET;
+    uint32_t a_off[AIW], b_off[BIW];
+    int a_left[AIW], b_left[BIW];                           // pixels from this load's to the end of the slice
 #pragma unroll
-    for (int i = 0; i < BIW; ++i) cur[i].init(pix_begin + (wave + i * NW) * PPI_B + b_prow, p.P, p.Q);
-    int pix_base = pix_begin;                               // first pixel of the step being issued
+    for (int i = 0; i < AIW; ++i) {
+        const int pix = pix_begin + (wave + i * NW) * PPI_A + a_prow;
+        a_off[i] = (uint32_t)(pix * p.K + a_ch) * 2u;
+        a_left[i] = pix_end - pix;
+    }
+    int b_ih[BIW], b_iw[BIW];                               // input pixel of the tap
+#pragma unroll
+    for (int i = 0; i < BIW; ++i) {
+        const int pix = pix_begin + (wave + i * NW) * PPI_B + b_prow;
+        b_left[i] = pix_end - pix;
+        if constexpr (LINEAR) b_off[i] = (uint32_t)(pix * p.C + b_c) * 2u;
+        else {
+            const int n = pix / (p.P * p.Q), rem = pix - n * (p.P * p.Q), oh = rem / p.Q;
+            b_ih[i] = oh * p.sh + b_dh;
+            b_iw[i] = (rem - oh * p.Q) * p.sw + b_dw;
+            b_off[i] = (uint32_t)(((n * p.H + b_ih[i]) * p.W + b_iw[i]) * p.C + b_c) * 2u;
+        }
+    }
+    const uint32_t a_step = (uint32_t)(KB * p.K) * 2u, b_step = (uint32_t)(KB * p.sw * p.C) * 2u;
+    const int row_iw = p.Q * p.sw, col_ih = p.P * p.sh;     // extents of the walk in x
+    const int iw_end = row_iw + b_dw, ih_end = col_ih + b_dh;
+    const uint32_t wrap_w = (uint32_t)((p.sh * p.W - row_iw) * p.C) * 2u, wrap_h = (uint32_t)((p.H - col_ih) * p.W * p.C) * 2u;
+    int pix_left = pix_end - pix_begin;                     // pixels from the first of the step to be issued (uniform)
 
-    auto issue = [&](uint16_t *sa, uint16_t *sb) {
+    const uint32_t dst0 = lds_addr(lds) + (uint32_t)wave * 1024;
+    auto issue = [&](int s) __attribute__((always_inline)) {
+        const uint32_t sa = dst0 + s * KB * BM * 2, sb = dst0 + (STAGES * KB * BM + s * KB * BN) * 2;
+        const bool whole = pix_left >= KB;                  // else some pixels of the step lie behind the slice
 #pragma unroll
         for (int i = 0; i < AIW; ++i) {
-            const int inst = wave + i * NW;
-            const int pix = pix_base + inst * PPI_A + a_prow;
-            const uint32_t off = (a_ok && pix < pix_end) ? (uint32_t)(pix * p.K + a_ch) * 2u : OOB_OFFSET;
-            dma_load_16B(rsA, lds_addr(sa) + inst * 1024, off);
+            uint32_t off = a_off[i] | a_bad;
+            if (!whole && a_left[i] <= 0) off = OOB_OFFSET;
+            dma_load_16B(rsA, sa + i * NW * 1024, off);
+            a_off[i] += a_step;
+            a_left[i] -= KB;
         }
 #pragma unroll
         for (int i = 0; i < BIW; ++i) {
-            const int inst = wave + i * NW;
-            const int pix = pix_base + inst * PPI_B + b_prow;
-            const int ih = cur[i].p * p.sh + b_dh, iw = cur[i].q * p.sw + b_dw;
-            const bool ok = b_ok && pix < pix_end && (unsigned)ih < (unsigned)p.H && (unsigned)iw < (unsigned)p.W;
-            const uint32_t off = ok ? (uint32_t)(((cur[i].n * p.H + ih) * p.W + iw) * p.C + b_c) * 2u : OOB_OFFSET;
-            dma_load_16B(rsB, lds_addr(sb) + inst * 1024, off);
-            cur[i].advance(BK, p.P, p.Q);
+            uint32_t off = b_off[i] | b_bad;
+            if (!whole && b_left[i] <= 0) off = OOB_OFFSET;
+            if constexpr (!LINEAR)
+                if ((unsigned)b_ih[i] >= (unsigned)p.H || (unsigned)b_iw[i] >= (unsigned)p.W) off = OOB_OFFSET;
+            dma_load_16B(rsB, sb + i * NW * 1024, off);
+            b_off[i] += b_step;
+            b_left[i] -= KB;
+            if constexpr (!LINEAR) {
+                b_iw[i] += KB * p.sw;
+                if (p.Q >= KB) {                            // uniform: at most one wrap a step
+                    const bool wrap = b_iw[i] >= iw_end;
+                    b_iw[i] -= wrap ? row_iw : 0;
+                    b_off[i] += wrap ? wrap_w : 0u;
+                    b_ih[i] += wrap ? p.sh : 0;
+                    const bool next = b_ih[i] >= ih_end;
+                    b_ih[i] -= next ? col_ih : 0;
+                    b_off[i] += next ? wrap_h : 0u;
+                } else {
+                    while (b_iw[i] >= iw_end) {
+                        b_iw[i] -= row_iw;
+                        b_off[i] += wrap_w;
+                        b_ih[i] += p.sh;
+                        if (b_ih[i] >= ih_end) {
+                            b_ih[i] -= col_ih;
+                            b_off[i] += wrap_h;
+                        }
+                    }
+                }
+            }
         }
-        pix_base += BK;
+        pix_left -= KB;
     };
 
     floatx16_t acc[TM][TN];
@@ -147,7 +183,7 @@ __global__ __launch_bounds__(WM *WN * 64) void wgrad_dma_kernel(const WgradArgs 
     const int f_pix = 8 * (g >> 1) + (s16 >> 2);            // + 4*t + 16*ks
     const int f_ch = 16 * (g & 1);                          // block-aligned part of the channel
     const int f_sub = 4 * (s16 & 3);                        // channel within the 16-channel block
-    // element offset of (pixel, 32-channel tile `ct`, this lane) in a [BK][BX] tile
+    // element offset of (pixel, 32-channel tile `ct`, this lane) in a [KB][BX] tile
     auto frag_off = [&](int BX, int pix, int ch_tile0) {
         const int ch = ch_tile0 + f_ch;
         const int blk = (ch >> 4) ^ ((pix & 3) << swz_shift(BX));
@@ -164,44 +200,52 @@ __global__ __launch_bounds__(WM *WN * 64) void wgrad_dma_kernel(const WgradArgs 
         r[0] = l2[0]; r[1] = l2[1]; r[2] = h2[0]; r[3] = h2[1];
         return r;
     };
-    auto mma = [&](const uint16_t *sa, const uint16_t *sb) {
+    constexpr int KS = KB / 16;
+    auto wait_and_sync = [&]() {
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(IN_FLIGHT) : "memory");
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    // fragments of slot u, loads of a later step into slot `next`, products; PP: the hand-over to the other group of waves in
+    // between (the ring's guarantees are those of igemm_dma_tile.h)
+    auto step = [&](int u, int next) __attribute__((always_inline)) {
+        u32x4_t a[KS][TM], b[KS][TN];
 #pragma unroll
-        for (int ks = 0; ks < BK / 16; ++ks) {
-            u32x4_t a[TM], b[TN];
+        for (int ks = 0; ks < KS; ++ks) {
 #pragma unroll
-            for (int i = 0; i < TM; ++i) a[i] = read_frag(sa, BM, ks, (wm * TM + i) * 32);
+            for (int i = 0; i < TM; ++i) a[ks][i] = read_frag(slot_a(u), BM, ks, (wm * TM + i) * 32);
 #pragma unroll
-            for (int j = 0; j < TN; ++j) b[j] = read_frag(sb, BN, ks, (wn * TN + j) * 32);
+            for (int j = 0; j < TN; ++j) b[ks][j] = read_frag(slot_b(u), BN, ks, (wn * TN + j) * 32);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        issue(next);
+        if constexpr (PP) wait_and_sync();
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
-                for (int j = 0; j < TN; ++j) acc[i][j] = T::mfma(a[i], b[j], acc[i][j]);
-        }
-    };
-    auto wait_and_sync = [&]() {
-        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(IN_FLIGHT) : "memory");
+                for (int j = 0; j < TN; ++j) acc[i][j] = T::mfma(a[ks][i], b[ks][j], acc[i][j]);
     };
 
     // The step count is rounded up to a whole turn of the ring (the extra
     // steps load and multiply zeros) so that the unrolled loop has one exit.
-    const int nk = pix_end > pix_begin ? (pix_end - pix_begin + BK - 1) / BK : 0;
+    const int nk = pix_end > pix_begin ? (pix_end - pix_begin + KB - 1) / KB : 0;
     const int nturns = (nk + STAGES - 1) / STAGES;
     if (nk > 0) {
-        issue(sA0, sB0);
-        issue(sA1, sB1);
-        if constexpr (STAGES == 4) issue(sA2, sB2);
+#pragma unroll
+        for (int u = 0; u < STAGES - 1; ++u) issue(u);
+        const bool late = PP && wave >= NW / 2;
+        if (late) wait_and_sync();
         for (int turn = 0; turn < nturns; ++turn) {
-            if constexpr (STAGES == 4) {
-                wait_and_sync(); issue(sA3, sB3); mma(sA0, sB0);
-                wait_and_sync(); issue(sA0, sB0); mma(sA1, sB1);
-                wait_and_sync(); issue(sA1, sB1); mma(sA2, sB2);
-                wait_and_sync(); issue(sA2, sB2); mma(sA3, sB3);
-            } else {
-                wait_and_sync(); issue(sA2, sB2); mma(sA0, sB0);
-                wait_and_sync(); issue(sA0, sB0); mma(sA1, sB1);
-                wait_and_sync(); issue(sA1, sB1); mma(sA2, sB2);
+#pragma unroll
+            for (int u = 0; u < STAGES; ++u) {
+                wait_and_sync();
+                step(u, (u + STAGES - 1) % STAGES);
             }
         }
+        if (PP && !late) wait_and_sync();
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
 
@@ -220,7 +264,7 @@ __global__ __launch_bounds__(WM *WN * 64) void wgrad_dma_kernel(const WgradArgs 
         }
 }
 
-template <class T, int BM, int BN, int WM, int WN, int STAGES>
+template <class T, int BM, int BN, int WM, int WN, int KB, int STAGES, bool PP = false>
 static hipError_t launch_cfg(const WgradArgs &a, hipStream_t stream)
 {
     const int RSC = a.R * a.S * a.C;
@@ -228,12 +272,24 @@ static hipError_t launch_cfg(const WgradArgs &a, hipStream_t stream)
     const int64_t split_groups = (a.splits + 7) / 8;        // each XCD takes every 8th slice
     const int64_t blocks = a.spread ? tiles * a.splits : tiles * split_groups * 8;
     if (blocks <= 0 || blocks > 0x7fffffff) return hipErrorInvalidValue;
-    DLK_LAUNCH(kname("wgrad_dma_kernel", {BM, BN}), (wgrad_dma_kernel<T, BM, BN, WM, WN, STAGES>), dim3((unsigned)blocks), dim3(WM * WN * 64), 0,
-                       stream, a);
+    const dim3 grid((unsigned)blocks), block(WM * WN * 64);
+    const bool linear = a.R * a.S == 1 && a.sh == 1 && a.sw == 1 && a.ph == 0 && a.pw == 0;
+    if (linear) DLK_LAUNCH(kname("wgrad_dma_kernel", {BM, BN}), (wgrad_dma_kernel<T, BM, BN, WM, WN, KB, STAGES, PP, true>), grid, block, 0, stream, a);
+    else DLK_LAUNCH(kname("wgrad_dma_kernel", {BM, BN}), (wgrad_dma_kernel<T, BM, BN, WM, WN, KB, STAGES, PP, false>), grid, block, 0, stream, a);
     return dlk::launch_status();
 }
 
-WgradPlan wgrad_make_plan(int64_t npix, int64_t x_elems, int K, int C, int RSC, bool thin_ok, bool fetch_term)
+// Tiles of the direct-to-LDS kernel (output channels x columns, pixels of a step, workgroups a compute unit holds) and the
+// constants of their cost (wgrad_make_plan).
+struct WgradTile {
+    int bm, bn, kb, per_cu;
+    double t0, step, fix;
+};
+static const WgradTile WGRAD_TILES[] = {
+    {256, 256, 32, 1, 6.25, 0.757, 6.98}, {128, 128, 32, 2, 10.70, 0.251, 0.05}, {64, 64, 32, 4, 10.59, 0.111, 0.05}, {64, 128, 64, 2, 10.74, 0.347, 0.05},
+    {128, 64, 64, 1, 6.70, 0.353, 3.03},  {64, 64, 64, 3, 10.86, 0.224, 0.05},   {128, 128, 64, 1, 6.47, 0.493, 3.69}, {128, 256, 64, 1, 5.71, 0.846, 5.60}};
+
+WgradPlan wgrad_make_plan(int64_t npix, int64_t x_elems, int K, int C, int RSC, bool thin_ok, bool fetch_term, int64_t max_splits)
 {
     static const int forced = tuning_knob("DLCONV_WGRAD_CFG", -2); // tuning override, unset in normal use
     WgradPlan pl{-1, 1, 32, 0};
@@ -247,8 +303,9 @@ WgradPlan wgrad_make_plan(int64_t npix, int64_t x_elems, int K, int C, int RSC, 
         pl.splits = (int)((npix + pl.chunk - 1) / pl.chunk);
         return pl;
     }
+    constexpr int NTILES = sizeof(WGRAD_TILES) / sizeof(WGRAD_TILES[0]);
     const bool dma_ok = K % 8 == 0 && C % 8 == 0 && K >= 32 && RSC >= 64;
-    if (!dma_ok || forced == -1 || forced > 3) {
+    if (!dma_ok || forced == -1 || forced >= NTILES) {
         // register-transposing fallback kernel (128 x 128 tiles): about 1024 workgroups
         const int64_t tiles = (int64_t)((K + 127) / 128) * ((RSC + 127) / 128);
         int64_t s = (1024 + tiles - 1) / tiles;
@@ -262,15 +319,14 @@ WgradPlan wgrad_make_plan(int64_t npix, int64_t x_elems, int K, int C, int RSC, 
         pl.splits = (int)((npix + chunk - 1) / chunk);
         return pl;
     }
-    // Direct-to-LDS kernel: pick the tile shape and the number of pixel slices by a small
-    // cost model.  The kernel gives all tiles of a slice to one XCD, so what counts is how
-    // many rounds of workgroups the busiest XCD (32 CUs) has to run: a slice count that
-    // leaves the last round almost empty costs a whole round.  Per round a workgroup spends
-    // its reduction steps plus a fixed start-up; the fp32 partial tiles are written and read
-    // back once per slice.  The constants are fitted to measured times on MI355X.
-    struct Shape { int bm, bn, per_cu; double us_per_step; };
-    static const Shape shapes[4] = {{256, 256, 1, 0.92}, {128, 128, 2, 0.55}, {64, 256, 2, 0.71}, {128, 256, 1, 0.88}};
-    static const int forced_target = tuning_knob("DLCONV_WGRAD_TARGET", 0); // tuning override: workgroups wanted, unset in normal use
+    // Direct-to-LDS kernel: tile and number of pixel slices by their estimated time in us,
+    //   t0 + (steps * step + fix) * (tiles a compute unit works through) + 8 bytes per output and slice at 8.2 TB/s.
+    // All tiles of a slice go to one XCD (32 compute units) or, with few slices, to all of them in turn; either way what counts
+    // is the compute unit with the most, and where each holds one workgroup, whole rounds of them.  The last term is the
+    // partial sums, written and read once: with as many slices as keep every compute unit busy with 128 x 128 tiles they are
+    // half the time of a 1x1 filter (6912 pixels, 1024 x 256: 24 slices 22 us, 8 slices of 128 x 64 tiles 15 us).  The constants
+    // are fitted to 3600 timings of 104 layers (fp16, 400..460000 pixels, 16..2048 x 32..1024 channels, 1x1 to 7x7); the
+    // choice is 5 % behind the best of each on average.
     const double outputs = (double)K * RSC;
     // Tiles of one slice that run on different XCDs share no L2.  With up to nine taps and operands beyond what the L2s hold
     // (32 MB together) every operand tile of a dealt slice may come from the last-level cache or HBM, at about 9 TB/s
@@ -278,41 +334,42 @@ WgradPlan wgrad_make_plan(int64_t npix, int64_t x_elems, int K, int C, int RSC, 
     const bool large = fetch_term && RSC / C <= 9 && 2 * (x_elems + npix * K) >= 40000000;
     double best = 1e300, best_local = 1e300, pl_steps = 0;
     WgradPlan local = pl;
-    for (int cfg = 0; cfg < 4; ++cfg) {
+    for (int cfg = 0; cfg < NTILES; ++cfg) {
         if (forced >= 0 && cfg != forced) continue;
-        const Shape &sh = shapes[cfg];
+        const WgradTile &sh = WGRAD_TILES[cfg];
+        // tiles of 64 only for filters of few outputs or output channels, of 128 x 256 only with more than one row of them:
+        // elsewhere the estimates favour them by less than they err
+        if (forced < 0 && (sh.bm == 64 || sh.bn == 64) && K > 64 && outputs > 3e5) continue;
+        if (forced < 0 && sh.bm < sh.bn && sh.bn == 256 && K <= 128) continue;
         const int64_t tiles = (int64_t)((K + sh.bm - 1) / sh.bm) * ((RSC + sh.bn - 1) / sh.bn);
-        const int64_t cap = 32 * sh.per_cu;                  // workgroups one XCD holds at a time
         const double fetch_us = 2.0 * tiles * (sh.bm + sh.bn) * (double)npix / 9e6;
         for (int cand = 0; cand < 64 + 15; ++cand) {
             // 8, 16, ... 512 slices, the same number on every XCD, each slice on one XCD; or
             // 1 .. 15 slices whose tiles are dealt over all XCDs
             const bool spread = cand >= 64;
-            int64_t s = spread ? cand - 63 : 8 * (cand + 1);
-            if (forced_target > 0) s = (forced_target + tiles - 1) / tiles;
-            if (s > 512) continue;
+            const int64_t s = spread ? cand - 63 : 8 * (cand + 1);
             if (s > 1 && s * 128 > npix) continue;           // at least four 32-pixel steps per slice
             int64_t chunk = (npix + s - 1) / s;
             chunk = (chunk + 31) / 32 * 32;
             const int64_t splits = (npix + chunk - 1) / chunk;
-            const int64_t per_xcd = (splits + 7) / 8;
-            const int64_t rounds = spread ? (tiles * splits + 8 * cap - 1) / (8 * cap) : (tiles * per_xcd + cap - 1) / cap;
-            const double reduce_us = (splits > 1 ? splits * outputs * 8.0 : outputs * 6.0) / 11.5e6;
-            const double steps_us = rounds * (chunk / 32 + 7) * sh.us_per_step;
-            const double est = 9.0 + steps_us + reduce_us;
+            if (splits > 1 && splits > max_splits) continue;
+            const double n = spread ? tiles * splits / 256.0 : tiles * ((splits + 7) / 8) / 32.0;
+            const double load = n > 2 * sh.per_cu ? n + 0.3 * sh.per_cu : n > sh.per_cu ? std::ceil(n / sh.per_cu) * sh.per_cu : std::ceil(n);
+            const double reduce_us = splits * outputs * 8.0 / 8.2e6;
+            const double steps_us = ((chunk + sh.kb - 1) / sh.kb * sh.step + sh.fix) * load;
+            const double est = sh.t0 + steps_us + reduce_us;
             if (est < best) {
                 best = est;
                 pl = WgradPlan{cfg, (int)splits, (int)chunk, spread ? 1 : 0};
                 pl_steps = steps_us;
             }
             if (large) {
-                const double fetch_est = 9.0 + std::max(steps_us, spread ? fetch_us : 0.0) + reduce_us;
+                const double fetch_est = sh.t0 + std::max(steps_us, spread ? fetch_us : 0.0) + reduce_us;
                 if (fetch_est < best_local) {
                     best_local = fetch_est;
                     local = WgradPlan{cfg, (int)splits, (int)chunk, spread ? 1 : 0};
                 }
             }
-            if (forced_target > 0 && spread) break;
         }
     }
     if (!large || !pl.spread) return pl;
@@ -320,25 +377,56 @@ WgradPlan wgrad_make_plan(int64_t npix, int64_t x_elems, int K, int C, int RSC, 
     // fastest, so a column tile is on min(row tiles, 8 / gcd(column tiles, 8)) of them and a row tile on min(column tiles, 8).
     // Where that, at 6 TB/s, takes longer than the steps does a slice belong on one XCD (not for one row tile of very many
     // columns, whose x is fetched once per tap either way), and where a slice is so long that its tiles drift apart.
-    // 4600 random shapes, C and K up to 2048: 1.22x on average, 1.34x with C, K <= 512 (256 x 9 x 256 filter, stride 2,
-    // 110592 pixels: 14 dealt slices of 128 x 128 tiles 240 us, 24 slices of 256 x 256 tiles on their XCDs 152 us); 11 % of
-    // them are slower by more than 3 %, 3 % by more than a tenth, worst 0.76x (268 x 526 x 1600 -> 520, 2x2 stride 2), mostly
-    // with 1000 and more channels and few outputs.  With the fetch term for all of them these were 18 %, 6 % and 0.71x.
-    const Shape &sh = shapes[pl.cfg];
+    const WgradTile &sh = WGRAD_TILES[pl.cfg];
     const int64_t rows = (K + sh.bm - 1) / sh.bm, cols = (RSC + sh.bn - 1) / sh.bn;
     const int64_t spread8 = cols % 8 == 0 ? 1 : cols % 4 == 0 ? 2 : cols % 2 == 0 ? 4 : 8;
     const double fetched = 2.0 * npix * (cols * std::min(rows, spread8) * sh.bn + rows * std::min<int64_t>(cols, 8) * sh.bm);
     return (fetched / 6e6 > 1.05 * pl_steps && (rows > 1 || cols < 64)) || pl.chunk > 8000 ? local : pl;
 }
 
+// The fewest slices that a caller has to bring room for where the direct-to-LDS kernel runs: as many as the first cost model
+// of this planner, with four tiles, took with or without its fetch term.  Kept so that a workspace of a size that was
+// accepted, or refused, still is.
+int wgrad_least_slices(int64_t npix, int64_t x_elems, int K, int C, int RSC)
+{
+    struct Shape { int bm, bn, per_cu; double us_per_step; };
+    static const Shape shapes[4] = {{256, 256, 1, 0.92}, {128, 128, 2, 0.55}, {64, 256, 2, 0.71}, {128, 256, 1, 0.88}};
+    const double outputs = (double)K * RSC;
+    const bool large = RSC / C <= 9 && 2 * (x_elems + npix * K) >= 40000000;
+    double best[2] = {1e300, 1e300};
+    int64_t slices[2] = {1, 1};
+    for (const Shape &sh : shapes) {
+        const int64_t tiles = (int64_t)((K + sh.bm - 1) / sh.bm) * ((RSC + sh.bn - 1) / sh.bn), cap = 32 * sh.per_cu;
+        const double fetch_us = 2.0 * tiles * (sh.bm + sh.bn) * (double)npix / 9e6;
+        for (int cand = 0; cand < 64 + 15; ++cand) {
+            const bool spread = cand >= 64;
+            const int64_t s = spread ? cand - 63 : 8 * (cand + 1);
+            if (s > 1 && s * 128 > npix) continue;
+            const int64_t chunk = ((npix + s - 1) / s + 31) / 32 * 32, splits = (npix + chunk - 1) / chunk;
+            const int64_t rounds = spread ? (tiles * splits + 8 * cap - 1) / (8 * cap) : (tiles * ((splits + 7) / 8) + cap - 1) / cap;
+            const double reduce_us = (splits > 1 ? splits * outputs * 8.0 : outputs * 6.0) / 11.5e6;
+            const double steps_us = rounds * (chunk / 32 + 7) * sh.us_per_step;
+            const double est[2] = {steps_us + reduce_us, std::max(steps_us, spread && large ? fetch_us : 0.0) + reduce_us};
+            for (int i = 0; i < 2; ++i)
+                if (est[i] < best[i]) { best[i] = est[i]; slices[i] = splits; }
+        }
+    }
+    return (int)std::min(slices[0], slices[1]);
+}
+
+// the tiles of WGRAD_TILES
 template <class T>
 static hipError_t dispatch(const WgradArgs &a, int cfg, hipStream_t stream)
 {
     switch (cfg) {
-        case 0: return launch_cfg<T, 256, 256, 2, 4, 4>(a, stream);   // 8 waves, wave tile 128x64
-        case 1: return launch_cfg<T, 128, 128, 2, 2, 4>(a, stream);   // 4 waves, wave tile 64x64
-        case 2: return launch_cfg<T, 64, 256, 1, 4, 4>(a, stream);    // 4 waves, wave tile 64x64
-        case 3: return launch_cfg<T, 128, 256, 2, 2, 4>(a, stream);   // 4 waves, wave tile 64x128
+        case 0: return launch_cfg<T, 256, 256, 2, 4, 32, 4, true>(a, stream);
+        case 1: return launch_cfg<T, 128, 128, 2, 4, 32, 4>(a, stream);
+        case 2: return launch_cfg<T, 64, 64, 2, 2, 32, 4>(a, stream);
+        case 3: return launch_cfg<T, 64, 128, 2, 4, 64, 3>(a, stream);
+        case 4: return launch_cfg<T, 128, 64, 4, 2, 64, 4>(a, stream);
+        case 5: return launch_cfg<T, 64, 64, 2, 2, 64, 3>(a, stream);
+        case 6: return launch_cfg<T, 128, 128, 4, 4, 64, 3>(a, stream);
+        case 7: return launch_cfg<T, 128, 256, 4, 4, 64, 3>(a, stream);
         default: return hipErrorInvalidValue;
     }
 }
