@@ -159,7 +159,7 @@ static double tiles_per_cu(const TileInfo &t, int64_t tiles)
 {
     const double n = tiles / 256.0;
     if (n > 2 * t.per_cu) return n + 0.3 * t.per_cu;
-    return n > t.per_cu ? std::ceil(n / t.per_cu) * t.per_cu : std::ceil(n);
+    return n > t.per_cu ? 2 * t.per_cu : std::ceil(n);
 }
 
 static double tile_work(const IgemmArgs &a, int tile, int steps)

@@ -332,6 +332,19 @@ WgradPlan wgrad_make_plan(int64_t npix, int64_t x_elems, int K, int C, int RSC, 
     // (32 MB together) every operand tile of a dealt slice may come from the last-level cache or HBM, at about 9 TB/s
     // (fetch_us below).  `pl` is the best plan without that term, `local` the best with it.
     const bool large = fetch_term && RSC / C <= 9 && 2 * (x_elems + npix * K) >= 40000000;
+    // Numbers of slices looked at, with the pixels of each: 8, 16, ... 512, the same number on every XCD, each slice on one XCD,
+    // or 1 .. 15 whose tiles are dealt over all XCDs.  (Worked out once for all tiles: this runs on every call.)
+    struct Slices { int splits, chunk; bool spread; };
+    Slices cands[20 + 15];
+    int n_cands = 0;
+    for (int i = 0; i < 20 + 15; ++i) {
+        const bool spread = i >= 20;
+        const int s = spread ? i - 19 : i < 8 ? 8 * (i + 1) : i < 12 ? 64 + 16 * (i - 7) : i < 16 ? 128 + 32 * (i - 11) : 256 + 64 * (i - 15);
+        if (s > 1 && (int64_t)s * 128 > npix) continue;      // at least four 32-pixel steps per slice
+        const uint32_t chunk = (((uint32_t)npix + s - 1) / s + 31) / 32 * 32;
+        const int splits = (int)(((uint32_t)npix + chunk - 1) / chunk);
+        if (splits == 1 || splits <= max_splits) cands[n_cands++] = Slices{splits, (int)chunk, spread};
+    }
     double best = 1e300, best_local = 1e300, pl_steps = 0;
     WgradPlan local = pl;
     for (int cfg = 0; cfg < NTILES; ++cfg) {
@@ -343,31 +356,23 @@ WgradPlan wgrad_make_plan(int64_t npix, int64_t x_elems, int K, int C, int RSC, 
         if (forced < 0 && sh.bm < sh.bn && sh.bn == 256 && K <= 128) continue;
         const int64_t tiles = (int64_t)((K + sh.bm - 1) / sh.bm) * ((RSC + sh.bn - 1) / sh.bn);
         const double fetch_us = 2.0 * tiles * (sh.bm + sh.bn) * (double)npix / 9e6;
-        for (int cand = 0; cand < 64 + 15; ++cand) {
-            // 8, 16, ... 512 slices, the same number on every XCD, each slice on one XCD; or
-            // 1 .. 15 slices whose tiles are dealt over all XCDs
-            const bool spread = cand >= 64;
-            const int64_t s = spread ? cand - 63 : 8 * (cand + 1);
-            if (s > 1 && s * 128 > npix) continue;           // at least four 32-pixel steps per slice
-            int64_t chunk = (npix + s - 1) / s;
-            chunk = (chunk + 31) / 32 * 32;
-            const int64_t splits = (npix + chunk - 1) / chunk;
-            if (splits > 1 && splits > max_splits) continue;
-            const double n = spread ? tiles * splits / 256.0 : tiles * ((splits + 7) / 8) / 32.0;
-            const double load = n > 2 * sh.per_cu ? n + 0.3 * sh.per_cu : n > sh.per_cu ? std::ceil(n / sh.per_cu) * sh.per_cu : std::ceil(n);
-            const double reduce_us = splits * outputs * 8.0 / 8.2e6;
-            const double steps_us = ((chunk + sh.kb - 1) / sh.kb * sh.step + sh.fix) * load;
+        for (int i = 0; i < n_cands; ++i) {
+            const Slices &c = cands[i];
+            const double n = c.spread ? tiles * c.splits / 256.0 : tiles * ((c.splits + 7) / 8) / 32.0;
+            const double load = n > 2 * sh.per_cu ? n + 0.3 * sh.per_cu : n > sh.per_cu ? 2 * sh.per_cu : std::ceil(n);
+            const double reduce_us = c.splits * outputs * (8.0 / 8.2e6);
+            const double steps_us = (((unsigned)(c.chunk + sh.kb - 1) >> (sh.kb == 64 ? 6 : 5)) * sh.step + sh.fix) * load;
             const double est = sh.t0 + steps_us + reduce_us;
             if (est < best) {
                 best = est;
-                pl = WgradPlan{cfg, (int)splits, (int)chunk, spread ? 1 : 0};
+                pl = WgradPlan{cfg, c.splits, c.chunk, c.spread ? 1 : 0};
                 pl_steps = steps_us;
             }
             if (large) {
-                const double fetch_est = sh.t0 + std::max(steps_us, spread ? fetch_us : 0.0) + reduce_us;
+                const double fetch_est = sh.t0 + std::max(steps_us, c.spread ? fetch_us : 0.0) + reduce_us;
                 if (fetch_est < best_local) {
                     best_local = fetch_est;
-                    local = WgradPlan{cfg, (int)splits, (int)chunk, spread ? 1 : 0};
+                    local = WgradPlan{cfg, c.splits, c.chunk, c.spread ? 1 : 0};
                 }
             }
         }
