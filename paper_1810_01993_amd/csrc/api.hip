@@ -155,11 +155,19 @@ dlk::IgemmArgs fwd_args(const dl_conv_desc *d, const Geometry &g)
     return a;
 }
 
+// The stem's forward kernel (no residual input there).
+bool use_stem_fwd(const dl_conv_desc *d)
+{
+    return dlk::stem_fwd_applicable(d->C, d->K, d->R, d->S, d->stride_h, d->stride_w, d->pad_h, d->pad_w, d->dil_h, d->dil_w);
+}
+
 // Whether the forward pass of d gains from the channel-padded copies, on which it is the GEMM a of the layer e.  The lines
 // come from 9000 random layers timed both ways (fp16, C 1..400, 1..256 outputs, maps of 8 x 8 to 768 x 1500).
 bool fwd_copies_pay(const dl_conv_desc *d, const dl_conv_desc *e, const dlk::IgemmArgs &a)
 {
     const int64_t taps = (int64_t)d->R * d->S, red = taps * d->C;
+    // the stem's kernel: 361 x 577 x 6 -> 64, batch 2: 56 us without the copies, 17 with them; one channel left as it was
+    if (use_stem_fwd(e) && !a.resid) return d->C > 1;
     if (red <= 24) return false;                         // 60 x 90 x 17 -> 64, 1x1: 9.1 us, 9.9 through the copy
     const int64_t steps = (red + 31) / 32;               // of the element-wise kernel
     const int64_t strides = (int64_t)d->stride_h * d->stride_w;
@@ -271,8 +279,28 @@ bool use_wgrad5x5(const dl_conv_desc *d)
                                     d->dil_h, d->dil_w);
 }
 
-// room: bytes of workspace the plan may use.  A caller that brings fewer bytes than the preferred plan takes (say, the size
-// that an earlier version of the library asked for) gets as many slices as they hold, down to wgrad_least_slices.
+bool use_wgrad_stem(const dl_conv_desc *d)
+{
+    return dlk::wgrad_stem_applicable(d->C, d->K, d->R, d->S, d->stride_h, d->stride_w, d->pad_h, d->pad_w, d->dil_h, d->dil_w);
+}
+
+// Plan of the kernels that serve any layer, for a workspace of `room` bytes.  A caller that brings fewer bytes than the
+// preferred plan takes (say, the size that an earlier version of the library asked for) gets as many slices as they hold, down
+// to *least.
+dlk::WgradPlan wgrad_general_plan(const dl_conv_desc *d, const Geometry &g, size_t room, int *least)
+{
+    const int64_t npix = (int64_t)d->N * g.P * g.Q;
+    const int RSC = d->R * d->S * d->C;
+    const bool thin = dlk::thin_wgrad_applicable(d->K, d->C, d->R, d->S, d->stride_h, d->stride_w, d->pad_h, d->pad_w);
+    const dlk::WgradPlan best = dlk::wgrad_make_plan(npix, g.x_elems, d->K, d->C, RSC, thin, true, INT64_MAX);
+    const size_t slice = (size_t)g.w_elems * sizeof(float);
+    *least = best.splits;
+    if (best.cfg < 0 || (room != 0 && best.splits * slice <= room)) return best;
+    *least = std::min(best.splits, dlk::wgrad_least_slices(npix, g.x_elems, d->K, d->C, RSC));
+    const int64_t fit = (int64_t)(room / slice);
+    return fit < *least ? best : dlk::wgrad_make_plan(npix, g.x_elems, d->K, d->C, RSC, thin, false, fit);  // (too little: the caller refuses)
+}
+
 dlk::WgradPlan wgrad_plan(const dl_conv_desc *d, const Geometry &g, size_t room = SIZE_MAX)
 {
     if (use_wgrad5x5(d)) {
@@ -283,16 +311,12 @@ dlk::WgradPlan wgrad_plan(const dl_conv_desc *d, const Geometry &g, size_t room 
         const dlk::WgradStripPlan p3 = dlk::wgrad3x3_make_plan(d->N, d->H, d->W, d->C, d->K);
         return dlk::WgradPlan{-3, p3.slices, 0};
     }
-    const bool thin = dlk::thin_wgrad_applicable(d->K, d->C, d->R, d->S, d->stride_h, d->stride_w, d->pad_h, d->pad_w);
-    const auto plan = [&](bool fetch_term, int64_t max_splits) {
-        return dlk::wgrad_make_plan((int64_t)d->N * g.P * g.Q, g.x_elems, d->K, d->C, d->R * d->S * d->C, thin, fetch_term, max_splits);
-    };
-    const size_t slice = (size_t)g.w_elems * sizeof(float);
-    const dlk::WgradPlan best = plan(true, INT64_MAX);
-    if (best.cfg < 0 || best.splits * slice <= room) return best;
-    const int64_t least = std::min(best.splits, dlk::wgrad_least_slices((int64_t)d->N * g.P * g.Q, g.x_elems, d->K, d->C, d->R * d->S * d->C));
-    const int64_t fit = (int64_t)(room / slice);
-    return fit < least ? best : plan(false, fit);                  // (too little: the caller refuses)
+    if (use_wgrad_stem(d)) {
+        const int splits = dlk::wgrad_stem_splits(d->N, d->K, g.P, g.Q);
+        if (splits * (size_t)g.w_elems * sizeof(float) <= room) return dlk::WgradPlan{-5, splits, 0, 0};
+    }
+    int least;
+    return wgrad_general_plan(d, g, room, &least);
 }
 
 size_t wgrad_own_workspace(const dl_conv_desc *d, const Geometry &g, size_t room = SIZE_MAX)
@@ -304,7 +328,11 @@ size_t wgrad_own_workspace(const dl_conv_desc *d, const Geometry &g, size_t room
 size_t wgrad_least_workspace(const dl_conv_desc *d, const Geometry &g)
 {
     const dlk::WgradPlan best = wgrad_plan(d, g);
-    const int least = best.cfg < 0 ? best.splits : std::min(best.splits, dlk::wgrad_least_slices((int64_t)d->N * g.P * g.Q, g.x_elems, d->K, d->C, d->R * d->S * d->C));
+    int least = best.splits;
+    if (best.cfg >= 0 || best.cfg == -5) {
+        wgrad_general_plan(d, g, 0, &least);
+        least = std::min(least, best.splits);
+    }
     return (size_t)least * (size_t)g.w_elems * sizeof(float);
 }
 
@@ -468,6 +496,16 @@ dl_status run_fwd(const dl_conv_desc *d, const void *x, const void *w, const flo
     const size_t need = igemm_scratch_bytes(a, true);
     if (need > 0 && (!workspace || workspace_bytes < need)) return DL_ERR_WORKSPACE;
     if (need > 0 && !aligned16(workspace)) return DL_ERR_ALIGN;
+    if (!residual && use_stem_fwd(d)) {
+        dlk::StemFwdArgs f{};
+        f.x = static_cast<const uint16_t *>(x);
+        f.w = static_cast<const uint16_t *>(w);
+        f.y = static_cast<uint16_t *>(y);
+        f.N = d->N; f.H = d->H; f.W = d->W; f.C = d->C; f.K = d->K; f.P = g.P; f.Q = g.Q;
+        f.bias = bias;
+        f.relu = relu ? 1 : 0;
+        return hip_status(dlk::launch_stem_fwd(f, d->dtype == DL_BF16, static_cast<hipStream_t>(hip_stream)));
+    }
     // (a workspace too small for the copies, or none, still runs the layer on its own tensors)
     const size_t padded = fwd_padded_workspace(d, g, residual != nullptr);
     if (padded > 0 && workspace && workspace_bytes >= padded && aligned16(workspace)) {
@@ -655,6 +693,12 @@ dl_status run_wgrad(const dl_conv_desc *d, const Geometry &g, const dlk::WgradPl
         w.N = d->N; w.H = d->H; w.W = d->W; w.C = d->C; w.K = d->K;
         w.slices = p5.slices; w.rs = p5.rs; w.xs = p5.xs;
         e = dlk::launch_wgrad5x5(w, d->dtype == DL_BF16, stream);
+    } else if (plan.cfg == -5) {
+        dlk::WgradStemArgs w{};
+        w.x = a.x; w.dy = a.dy; w.partial = a.partial;
+        w.N = d->N; w.H = d->H; w.W = d->W; w.C = d->C; w.K = d->K; w.P = g.P; w.Q = g.Q;
+        w.splits = plan.splits;
+        e = dlk::launch_wgrad_stem(w, d->dtype == DL_BF16, stream);
     } else
     e = plan.cfg >= 0    ? dlk::launch_wgrad_dma(a, d->dtype == DL_BF16, plan.cfg, stream)
                    : plan.cfg == -2 ? dlk::launch_thin_wgrad(a, d->dtype == DL_BF16, stream)

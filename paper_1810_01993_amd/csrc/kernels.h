@@ -209,6 +209,19 @@ bool dgrad_stem_applicable(int N, int H, int W, int C, int K, int R, int S, int 
 size_t dgrad_stem_filter_bytes(int C, int K);
 hipError_t launch_dgrad_stem(const DgradStemArgs &a, bool is_bf16, hipStream_t stream);
 
+// Forward pass of the same layers with 8 or 16 input channels and at most 64 output channels, a multiple of 8: reads x and w as
+// they lie, no scratch.
+struct StemFwdArgs {
+    const uint16_t *x;          // [N][H][W][C]
+    const uint16_t *w;          // [K][7][7][C]
+    uint16_t *y;                // [N][P][Q][K]
+    int32_t N, H, W, C, K, P, Q;
+    const float *bias;          // point-wise tail as in IgemmArgs
+    int32_t relu;
+};
+bool stem_fwd_applicable(int C, int K, int R, int S, int sh, int sw, int ph, int pw, int dh, int dw);
+hipError_t launch_stem_fwd(const StemFwdArgs &a, bool is_bf16, hipStream_t stream);
+
 // Filter re-layout for the data gradient: for one stride-parity class,
 //   wt[c][jr][js][k] = w[k][r0 + jr*rstep][s0 + js*sstep][c]
 struct FilterRelayoutArgs {
@@ -275,6 +288,19 @@ hipError_t launch_wgrad3x3(const WgradStripArgs &a, bool is_bf16, hipStream_t st
 bool wgrad5x5_applicable(int N, int H, int W, int C, int K, int R, int S, int sh, int sw, int ph, int pw, int dh, int dw);
 WgradStripPlan wgrad5x5_make_plan(int N, int H, int W, int C, int K);
 hipError_t launch_wgrad5x5(const WgradStripArgs &a, bool is_bf16, hipStream_t stream);
+
+// Filter gradient of the stem (7x7, stride 2, padding 3, 8 or 16 input and at most 64 output channels; cfg -5 of the plan):
+// partial[slice][K][7][7][C].
+struct WgradStemArgs {
+    const uint16_t *x;          // [N][H][W][C]
+    const uint16_t *dy;         // [N][P][Q][K]
+    float *partial;
+    int32_t N, H, W, C, K, P, Q;
+    int32_t splits;             // runs of patches
+};
+bool wgrad_stem_applicable(int C, int K, int R, int S, int sh, int sw, int ph, int pw, int dh, int dw);
+int wgrad_stem_splits(int N, int K, int P, int Q);
+hipError_t launch_wgrad_stem(const WgradStemArgs &a, bool is_bf16, hipStream_t stream);
 
 // Streaming kernels for 1x1 layers with <= 4 channels on one side (cfg -2 of the plan).
 bool thin_rows_applicable(const IgemmArgs &a);
