@@ -264,6 +264,10 @@ static bool use_wide(const IgemmArgs &a) { return halo_mode() == 1 && igemm_wide
 static bool halo_takes(const IgemmArgs &a)
 {
     if (!halo_mode() || a.Nout <= 0) return false;
+    // 3x3 with 48..64 columns and a short reduction of whole chunks, or of half a chunk: one column tile, mostly set-up (and the
+    // filter copy ahead of it), where the ring kernels take 0.6-0.98x the time (110592 pixels, 64 -> 64: 21.6 -> 15.3 us;
+    // 162936, 16 -> 64: 23.8 -> 14.7).  With 48 input channels either is faster, from 96 on this one.
+    if (use_3x3(a) && a.Nout >= 48 && a.Nout <= 64 && (a.Cin <= 16 || a.Cin == 32 || a.Cin == 64)) return false;
     if (use_3x3(a)) return igemm_halo3x3_tiles(a) >= 200;
     const int NT = a.TR * a.TS;
     const bool dense = a.sh == 1 && a.sw == 1 && a.osh == 1 && a.osw == 1 && a.FH == a.OH && a.FW == a.OW;
@@ -271,7 +275,10 @@ static bool halo_takes(const IgemmArgs &a)
     if (!dense || a.Cin % 8 != 0 || aw == 0 || aw > NT - 2) return false;
     const int64_t tiles = (int64_t)a.NB * ((a.OH + HALO_TH - 1) / HALO_TH) * ((a.OW + HALO_TW - 1) / HALO_TW) *
                           ((a.Nout + HALO_BN - 1) / HALO_BN);
-    return tiles >= 200;
+    // One round of workgroups at most.  From there on the ring kernels, whose waves hand over in the same way but start
+    // without a filter copy and reach further tiles sooner, are 1.1-2.5x as fast on every one of 55 layers (16..512 -> 160..512
+    // channels, dilations 2 and 6, 5x5; 128736 pixels, 128 -> 256, dilation 2: 144 -> 77 us).
+    return tiles >= 200 && tiles <= 256;
 }
 
 // Leading output columns a halo-tile kernel takes (0 = none).  The 3x3 kernel takes any
