@@ -66,6 +66,10 @@ class ConvDesc:
         return _Desc(self.N, self.H, self.W, self.C, self.K, self.R, self.S, self.stride_h, self.stride_w,
                      self.pad_h, self.pad_w, self.dil_h, self.dil_w, self.dtype, dwt)
 
+    def __getstate__(self):
+        """The fields alone: what _call_plan keeps beside them holds C pointers."""
+        return {k: v for k, v in self.__dict__.items() if k != "_kept"}
+
 
 def _load() -> ctypes.CDLL:
     if not os.path.exists(LIB_PATH):
@@ -178,6 +182,18 @@ def _plan(desc: ConvDesc):
     return (ref, *p)
 
 
+def _call_plan(desc: ConvDesc):
+    """(reference to the C descriptor, workspace bytes per pass, shapes of x, w and y): _plan once per descriptor, whose fields
+    cannot change and which therefore keeps it (building the C structure anew takes 2 of the 10 us that a call spends in
+    Python)."""
+    kept = desc.__dict__.get("_kept")
+    if kept is None:
+        ref, P, Q, need = _plan(desc)
+        kept = (ref, need, (desc.N, desc.H, desc.W, desc.C), (desc.K, desc.R, desc.S, desc.C), (desc.N, P, Q, desc.K))
+        object.__setattr__(desc, "_kept", kept)
+    return kept
+
+
 def dl_ce_workspace_bytes(n_pixels: int) -> int:
     n = ctypes.c_size_t()
     _check(_lib.dl_ce_workspace_bytes(n_pixels, ctypes.byref(n)), "dl_ce_workspace_bytes")
@@ -207,20 +223,20 @@ def _conv_workspace(desc: ConvDesc, which: int, nbytes: int, device, workspace: 
 
 
 def _expect(t: torch.Tensor, shape, name: str):
-    if tuple(t.shape) != tuple(shape):
+    if t.shape != shape:
         raise ValueError(f"{name}: expected shape {tuple(shape)}, got {tuple(t.shape)}")
 
 
 def conv2d_fwd(desc: ConvDesc, x: torch.Tensor, w: torch.Tensor, y: torch.Tensor | None = None,
                workspace: torch.Tensor | None = None) -> torch.Tensor:
-    ref, P, Q, need = _plan(desc)
-    _expect(x, (desc.N, desc.H, desc.W, desc.C), "x")
-    _expect(w, (desc.K, desc.R, desc.S, desc.C), "w")
+    ref, need, x_shape, w_shape, y_shape = _call_plan(desc)
+    _expect(x, x_shape, "x")
+    _expect(w, w_shape, "w")
     if _dtype_code(x) != desc.dtype or w.dtype != x.dtype:
         raise TypeError("tensor dtype does not match the descriptor")
     if y is None:
-        y = torch.empty((desc.N, P, Q, desc.K), dtype=x.dtype, device=x.device)
-    _expect(y, (desc.N, P, Q, desc.K), "y")
+        y = torch.empty(y_shape, dtype=x.dtype, device=x.device)
+    _expect(y, y_shape, "y")
     ws, nb = _conv_workspace(desc, PASS_FWD, need[PASS_FWD], x.device, workspace)
     _check(_lib.conv2d_fwd(ref, _dev_ptr(x), _dev_ptr(w), _dev_ptr(y), _dev_ptr(ws), nb,
                            _stream()), "conv2d_fwd")
@@ -230,16 +246,16 @@ def conv2d_fwd(desc: ConvDesc, x: torch.Tensor, w: torch.Tensor, y: torch.Tensor
 def conv2d_fwd_bias_relu(desc: ConvDesc, x: torch.Tensor, w: torch.Tensor, bias: torch.Tensor | None, relu: bool,
                          y: torch.Tensor | None = None, workspace: torch.Tensor | None = None) -> torch.Tensor:
     """y = act(conv(x, w) + bias): bias float32[K] on the device or None; relu cuts negative results."""
-    ref, P, Q, need = _plan(desc)
-    _expect(x, (desc.N, desc.H, desc.W, desc.C), "x")
-    _expect(w, (desc.K, desc.R, desc.S, desc.C), "w")
+    ref, need, x_shape, w_shape, y_shape = _call_plan(desc)
+    _expect(x, x_shape, "x")
+    _expect(w, w_shape, "w")
     if _dtype_code(x) != desc.dtype or w.dtype != x.dtype:
         raise TypeError("tensor dtype does not match the descriptor")
     if bias is not None and (bias.dtype != torch.float32 or tuple(bias.shape) != (desc.K,)):
         raise ValueError("bias must be float32[K]")
     if y is None:
-        y = torch.empty((desc.N, P, Q, desc.K), dtype=x.dtype, device=x.device)
-    _expect(y, (desc.N, P, Q, desc.K), "y")
+        y = torch.empty(y_shape, dtype=x.dtype, device=x.device)
+    _expect(y, y_shape, "y")
     ws, nb = _conv_workspace(desc, PASS_FWD, need[PASS_FWD], x.device, workspace)
     _check(_lib.conv2d_fwd_bias_relu(ref, _dev_ptr(x), _dev_ptr(w), _dev_ptr(bias),
                                      1 if relu else 0, _dev_ptr(y), _dev_ptr(ws), nb, _stream()),
@@ -251,20 +267,20 @@ def conv2d_fwd_bias_add_relu(desc: ConvDesc, x: torch.Tensor, w: torch.Tensor, b
                              residual: torch.Tensor | None, relu: bool, y: torch.Tensor | None = None,
                              workspace: torch.Tensor | None = None) -> torch.Tensor:
     """y = act(conv(x, w) + bias + residual): residual [N,P,Q,K] of x's dtype or None (a ResNet block's tail)."""
-    ref, P, Q, need = _plan(desc)
-    _expect(x, (desc.N, desc.H, desc.W, desc.C), "x")
-    _expect(w, (desc.K, desc.R, desc.S, desc.C), "w")
+    ref, need, x_shape, w_shape, y_shape = _call_plan(desc)
+    _expect(x, x_shape, "x")
+    _expect(w, w_shape, "w")
     if _dtype_code(x) != desc.dtype or w.dtype != x.dtype:
         raise TypeError("tensor dtype does not match the descriptor")
     if bias is not None and (bias.dtype != torch.float32 or tuple(bias.shape) != (desc.K,)):
         raise ValueError("bias must be float32[K]")
     if residual is not None:
-        _expect(residual, (desc.N, P, Q, desc.K), "residual")
+        _expect(residual, y_shape, "residual")
         if residual.dtype != x.dtype:
             raise TypeError("the residual must have x's dtype")
     if y is None:
-        y = torch.empty((desc.N, P, Q, desc.K), dtype=x.dtype, device=x.device)
-    _expect(y, (desc.N, P, Q, desc.K), "y")
+        y = torch.empty(y_shape, dtype=x.dtype, device=x.device)
+    _expect(y, y_shape, "y")
     ws, nb = _conv_workspace(desc, PASS_FWD, need[PASS_FWD], x.device, workspace)
     _check(_lib.conv2d_fwd_bias_add_relu(ref, _dev_ptr(x), _dev_ptr(w), _dev_ptr(bias),
                                          _dev_ptr(residual), 1 if relu else 0, _dev_ptr(y), _dev_ptr(ws), nb, _stream()),
@@ -274,14 +290,14 @@ def conv2d_fwd_bias_add_relu(desc: ConvDesc, x: torch.Tensor, w: torch.Tensor, b
 
 def conv2d_bwd_data(desc: ConvDesc, dy: torch.Tensor, w: torch.Tensor, dx: torch.Tensor | None = None,
                     workspace: torch.Tensor | None = None) -> torch.Tensor:
-    ref, P, Q, need = _plan(desc)
-    _expect(dy, (desc.N, P, Q, desc.K), "dy")
-    _expect(w, (desc.K, desc.R, desc.S, desc.C), "w")
+    ref, need, x_shape, w_shape, y_shape = _call_plan(desc)
+    _expect(dy, y_shape, "dy")
+    _expect(w, w_shape, "w")
     if _dtype_code(dy) != desc.dtype or w.dtype != dy.dtype:
         raise TypeError("tensor dtype does not match the descriptor")
     if dx is None:
-        dx = torch.empty((desc.N, desc.H, desc.W, desc.C), dtype=dy.dtype, device=dy.device)
-    _expect(dx, (desc.N, desc.H, desc.W, desc.C), "dx")
+        dx = torch.empty(x_shape, dtype=dy.dtype, device=dy.device)
+    _expect(dx, x_shape, "dx")
     ws, nb = _conv_workspace(desc, PASS_BWD_DATA, need[PASS_BWD_DATA], dy.device, workspace)
     _check(_lib.conv2d_bwd_data(ref, _dev_ptr(dy), _dev_ptr(w), _dev_ptr(dx), _dev_ptr(ws),
                                 nb, _stream()), "conv2d_bwd_data")
@@ -290,16 +306,16 @@ def conv2d_bwd_data(desc: ConvDesc, dy: torch.Tensor, w: torch.Tensor, dx: torch
 
 def conv2d_bwd_filter(desc: ConvDesc, x: torch.Tensor, dy: torch.Tensor, dw: torch.Tensor | None = None,
                       workspace: torch.Tensor | None = None) -> torch.Tensor:
-    ref, P, Q, need = _plan(desc)
-    _expect(x, (desc.N, desc.H, desc.W, desc.C), "x")
-    _expect(dy, (desc.N, P, Q, desc.K), "dy")
+    ref, need, x_shape, w_shape, y_shape = _call_plan(desc)
+    _expect(x, x_shape, "x")
+    _expect(dy, y_shape, "dy")
     if _dtype_code(x) != desc.dtype or dy.dtype != x.dtype:
         raise TypeError("tensor dtype does not match the descriptor")
     dwt = desc.dtype if desc.dw_dtype is None else desc.dw_dtype
     if dw is None:
-        dw = torch.empty((desc.K, desc.R, desc.S, desc.C), device=x.device,
+        dw = torch.empty(w_shape, device=x.device,
                          dtype=torch.float32 if dwt == DL_F32 else x.dtype)
-    _expect(dw, (desc.K, desc.R, desc.S, desc.C), "dw")
+    _expect(dw, w_shape, "dw")
     ws, nb = _conv_workspace(desc, PASS_BWD_FILTER, need[PASS_BWD_FILTER], x.device, workspace)
     _check(_lib.conv2d_bwd_filter(ref, _dev_ptr(x), _dev_ptr(dy), _dev_ptr(dw),
                                   _dev_ptr(ws), nb, _stream()), "conv2d_bwd_filter")
@@ -309,14 +325,14 @@ def conv2d_bwd_filter(desc: ConvDesc, x: torch.Tensor, dy: torch.Tensor, dw: tor
 def conv2d_transpose_fwd(desc: ConvDesc, x: torch.Tensor, w: torch.Tensor, y: torch.Tensor | None = None,
                          workspace: torch.Tensor | None = None) -> torch.Tensor:
     """x: [N,P,Q,K] -> y: [N,H,W,C]; ``desc`` names the underlying convolution (see the header)."""
-    ref, P, Q, need = _plan(desc)
-    _expect(x, (desc.N, P, Q, desc.K), "x")
-    _expect(w, (desc.K, desc.R, desc.S, desc.C), "w")
+    ref, need, x_shape, w_shape, y_shape = _call_plan(desc)
+    _expect(x, y_shape, "x")
+    _expect(w, w_shape, "w")
     if _dtype_code(x) != desc.dtype or w.dtype != x.dtype:
         raise TypeError("tensor dtype does not match the descriptor")
     if y is None:
-        y = torch.empty((desc.N, desc.H, desc.W, desc.C), dtype=x.dtype, device=x.device)
-    _expect(y, (desc.N, desc.H, desc.W, desc.C), "y")
+        y = torch.empty(x_shape, dtype=x.dtype, device=x.device)
+    _expect(y, x_shape, "y")
     ws, nb = _conv_workspace(desc, PASS_BWD_DATA, need[PASS_BWD_DATA], x.device, workspace)
     _check(_lib.conv2d_transpose_fwd(ref, _dev_ptr(x), _dev_ptr(w), _dev_ptr(y),
                                      _dev_ptr(ws), nb, _stream()), "conv2d_transpose_fwd")
@@ -326,14 +342,14 @@ def conv2d_transpose_fwd(desc: ConvDesc, x: torch.Tensor, w: torch.Tensor, y: to
 def conv2d_transpose_bwd_data(desc: ConvDesc, dy: torch.Tensor, w: torch.Tensor, dx: torch.Tensor | None = None,
                               workspace: torch.Tensor | None = None) -> torch.Tensor:
     """dy: [N,H,W,C] -> dx: [N,P,Q,K]."""
-    ref, P, Q, need = _plan(desc)
-    _expect(dy, (desc.N, desc.H, desc.W, desc.C), "dy")
-    _expect(w, (desc.K, desc.R, desc.S, desc.C), "w")
+    ref, need, x_shape, w_shape, y_shape = _call_plan(desc)
+    _expect(dy, x_shape, "dy")
+    _expect(w, w_shape, "w")
     if _dtype_code(dy) != desc.dtype or w.dtype != dy.dtype:
         raise TypeError("tensor dtype does not match the descriptor")
     if dx is None:
-        dx = torch.empty((desc.N, P, Q, desc.K), dtype=dy.dtype, device=dy.device)
-    _expect(dx, (desc.N, P, Q, desc.K), "dx")
+        dx = torch.empty(y_shape, dtype=dy.dtype, device=dy.device)
+    _expect(dx, y_shape, "dx")
     ws, nb = _conv_workspace(desc, PASS_FWD, need[PASS_FWD], dy.device, workspace)
     _check(_lib.conv2d_transpose_bwd_data(ref, _dev_ptr(dy), _dev_ptr(w), _dev_ptr(dx),
                                           _dev_ptr(ws), nb, _stream()), "conv2d_transpose_bwd_data")
@@ -343,16 +359,16 @@ def conv2d_transpose_bwd_data(desc: ConvDesc, dy: torch.Tensor, w: torch.Tensor,
 def conv2d_transpose_bwd_filter(desc: ConvDesc, x: torch.Tensor, dy: torch.Tensor, dw: torch.Tensor | None = None,
                                 workspace: torch.Tensor | None = None) -> torch.Tensor:
     """x: [N,P,Q,K], dy: [N,H,W,C] -> dw: [K,R,S,C]."""
-    ref, P, Q, need = _plan(desc)
-    _expect(x, (desc.N, P, Q, desc.K), "x")
-    _expect(dy, (desc.N, desc.H, desc.W, desc.C), "dy")
+    ref, need, x_shape, w_shape, y_shape = _call_plan(desc)
+    _expect(x, y_shape, "x")
+    _expect(dy, x_shape, "dy")
     if _dtype_code(x) != desc.dtype or dy.dtype != x.dtype:
         raise TypeError("tensor dtype does not match the descriptor")
     dwt = desc.dtype if desc.dw_dtype is None else desc.dw_dtype
     if dw is None:
-        dw = torch.empty((desc.K, desc.R, desc.S, desc.C), device=x.device,
+        dw = torch.empty(w_shape, device=x.device,
                          dtype=torch.float32 if dwt == DL_F32 else x.dtype)
-    _expect(dw, (desc.K, desc.R, desc.S, desc.C), "dw")
+    _expect(dw, w_shape, "dw")
     ws, nb = _conv_workspace(desc, PASS_BWD_FILTER, need[PASS_BWD_FILTER], x.device, workspace)
     _check(_lib.conv2d_transpose_bwd_filter(ref, _dev_ptr(x), _dev_ptr(dy), _dev_ptr(dw),
                                             _dev_ptr(ws), nb, _stream()), "conv2d_transpose_bwd_filter")
