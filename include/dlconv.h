@@ -70,7 +70,8 @@ dl_status dl_conv_workspace_bytes(const dl_conv_desc *desc, int pass, size_t *by
 
 /* The fewest bytes with which the given pass runs at all; may be 0.  Any workspace from
  * this size on is accepted; below dl_conv_workspace_bytes the pass may take slower kernels
- * (no padded copies, fewer slices of a filter gradient), whose sums are added in another order. */
+ * (no padded copies, fewer slices of a filter gradient, fewer ranges of a split reduction), whose
+ * sums are added in another order. */
 dl_status dl_conv_least_workspace_bytes(const dl_conv_desc *desc, int pass, size_t *bytes);
 
 /* Which kernels the given pass of this convolution launches, in order, each with

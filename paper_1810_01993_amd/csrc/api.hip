@@ -166,7 +166,7 @@ bool use_stem_fwd(const dl_conv_desc *d)
 bool fwd_copies_pay(const dl_conv_desc *d, const dl_conv_desc *e, const dlk::IgemmArgs &a)
 {
     const int64_t taps = (int64_t)d->R * d->S, red = taps * d->C;
-    // the stem's kernel: 361 x 577 x 6 -> 64, batch 2: 56 us without the copies, 17 with them; one channel left as it was
+    // the stem's kernel: 361 x 577 x 6 -> 64, batch 2: 56 us without the copies, 21 with them; one channel left as it was
     if (use_stem_fwd(e) && !a.resid) return d->C > 1;
     if (red <= 24) return false;                         // 60 x 90 x 17 -> 64, 1x1: 9.1 us, 9.9 through the copy
     const int64_t steps = (red + 31) / 32;               // of the element-wise kernel

@@ -207,7 +207,7 @@ struct IgemmPlan { int tile, ksplits, chunks; };
 
 // GEMMs with few tiles and a long reduction leave most compute units idle, or walk it in many steps of small tiles.  Cut
 // into ranges that run side by side, with an ordered reduce of their fp32 partial sums (4 us, and 8 bytes per output
-// and range at 8 TB/s): 6912 pixels, 2048 -> 256, 3x3: 216 tiles of 128 x 64 84 us, 54 tiles of 256 x 128 in four ranges 64 us
+// and range at 8 TB/s): 6912 pixels, 2048 -> 256, 3x3: 216 tiles of 128 x 64 84 us, 54 tiles of 256 x 128 in four ranges 66 us
 // with the reduce.  room: bytes of scratch for the partial sums.
 static IgemmPlan make_plan(const IgemmArgs &a, size_t room)
 {

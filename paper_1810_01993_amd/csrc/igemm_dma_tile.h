@@ -6,8 +6,8 @@
 // each of which deposits 64 lanes x 16 bytes = 1 KB (16 tile rows of 32
 // reduction elements) contiguously in LDS.  Out-of-range offsets (zero
 // padding, ragged edges, steps past the end of the reduction) deposit zeros.
-// A ring of four LDS buffers keeps three reduction steps in flight; one
-// barrier per step.  Because the LDS image of a load is contiguous, bank
+// A ring of two to four LDS buffers keeps one to three reduction steps in
+// flight; one barrier per step.  Because the LDS image of a load is contiguous, bank
 // conflicts are avoided by swizzling which 16-byte slice of a row each lane
 // fetches instead of padding the row pitch.
 //
@@ -18,7 +18,7 @@
 //                  a workgroup re-reads the same few input rows tap after tap
 //                  while they are cached, and everything that changes from
 //                  step to step is wave-uniform: the per-lane work per load is
-//                  one add and one select.  Whether a tap of a row falls into
+//                  a bit extract, an or and an add.  Whether a tap of a row falls into
 //                  the padding is looked up in a per-row bit mask built once.
 //                  A ragged last chunk is zero-filled.  Needs <= 64 taps.
 #pragma once

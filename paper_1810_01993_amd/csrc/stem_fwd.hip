@@ -6,7 +6,7 @@
 // filter is laid out once, as MFMA fragments in registers (what does not fit, in LDS); the input patch with its halo (37 x 38
 // pixels) is fetched into one of two LDS images while the other is multiplied.  51 us (0.87 PFLOP/s); of the 6 us a patch
 // takes, 3 are products, the rest is the store and the wait of both waves of a SIMD for it.  With 8 channels 361 x 577 -> 64,
-// batch 2: 24 -> 12 us.
+// batch 2: 24 -> 16 us.
 //
 // LDS image: planes [column parity][8-channel half][row][column / 2] of 16-byte slots.  The 16 output pixels of an MFMA
 // operand read every other column, i.e. neighbouring slots of one plane: no bank conflicts, and every tap is a constant

@@ -7,7 +7,8 @@
 // in registers: 8 waves, each with up to 7 blocks of 16 columns (a tap of 16 channels, or two of 8) times two of 16 output
 // channels.  Per patch it fetches x with its halo (37 x 38 pixels) and its 32 channels of dy into one of two LDS buffers while the
 // other is multiplied.  Two workgroups share a patch (the two halves of the output channels), which halves the fp32
-// partial sums that one workgroup per compute unit leaves for the ordered reduce (25 MB instead of 51).
+// partial sums that one workgroup per compute unit leaves for the ordered reduce (25 MB instead of 51).  With that reduce the
+// pass takes 69 us where it took 94.
 //
 // The reduction index of an MFMA (16x16x32) is two rows of 16 output pixels.  x lies in planes [column parity][8-channel half]
 // [row][column / 2] of 16-byte slots, so the pixels of a row that a tap meets are neighbouring slots; a tap is a constant
