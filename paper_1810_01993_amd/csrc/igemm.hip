@@ -317,12 +317,6 @@ static hipError_t dispatch(const IgemmArgs &a, hipStream_t stream)
 int igemm_batch_cfg(const IgemmArgs *a, int n)
 {
     if (n < 2 || n > IgemmBatch::MAX || forced_cfg() >= 0) return -1;
-    // Sharing a launch pays where the single launches are short (start-up and drain of a 10 us
-    // kernel, four times over); long GEMMs run better one after the other (the 3x3 stride-2
-    // layer that produces a 768 x 1152 x 256 tensor: 0.80 ms against 0.96 ms in one launch).
-    double macs = 0;
-    for (int i = 0; i < n; ++i) macs += (double)a[i].NB * a[i].OH * a[i].OW * a[i].Nout * a[i].Cin * a[i].TR * a[i].TS;
-    if (macs > 1e10) return -1;
     for (int i = 0; i < n; ++i)
         if (a[i].Cin % 8 != 0 || thin_rows_applicable(a[i]) || thin_cols_applicable(a[i]) || !choose_c_outer(a[i]) || a[i].b_transposed != a[0].b_transposed)
             return -1;
@@ -350,6 +344,7 @@ hipError_t launch_igemm_batch(const IgemmBatch &b, bool is_bf16, hipStream_t str
     const int cfg = igemm_batch_cfg(b.a, b.n);
     if (cfg < 0) return hipErrorInvalidValue;
     IgemmBatch c = b;
+    std::sort(c.a, c.a + c.n, [](const IgemmArgs &x, const IgemmArgs &y) { return x.TR * x.TS > y.TR * y.TS; });
     for (int i = 0; i < c.n; ++i) {
         set_divisors(c.a[i]);
         c.a[i].c_outer = 1;

@@ -128,6 +128,7 @@ struct IgemmBatch {
     static constexpr int MAX = 4;
     IgemmArgs a[MAX];
     int32_t n;
+    int32_t tiles;              // of the GEMM with the most (set by the launch)
 };
 
 // Tile configuration (as for launch_igemm_dma) if these n GEMMs can share one launch of the

@@ -66,6 +66,13 @@ CASES = [
     (L("stem.w.c8.k40", 1, 33, 130, 8, 40, 7, 2), "bf16", WGRAD, "wgrad_stem_kernel<8>"),
     (L("stem.w.c8.k8.pixel", 1, 1, 1, 8, 8, 7, 2), "f16", WGRAD, "wgrad_stem_kernel<8>"),
     (L("stem.w.many", 1, 400, 570, 16, 32, 7, 2), "f16", WGRAD, "wgrad_stem_kernel<16>"),
+    # parity classes in one launch, tiles not a multiple of the eight XCDs: three taps or fewer each, one tile, two classes
+    (L("bt.batch.64x64", 1, 41, 67, 40, 64, 3, 2), "bf16", DGRAD, "batch_kernel.bt<64,64>"),
+    (L("bt.batch.128x64.k64", 1, 75, 250, 8, 64, 2, 2), "f16", DGRAD, "batch_kernel.bt.k64<128,64>"),
+    (L("bt.batch.one-tile", 1, 5, 6, 40, 64, 3, 2), "f16", DGRAD, "batch_kernel.bt<64,64>"),
+    (L("bt.batch.one-row", 1, 1, 131, 40, 64, 3, 2), "bf16", DGRAD, "batch_kernel.bt<64,64>"),
+    # 11 G multiply-adds
+    (L("bt.batch.large", 1, 185, 231, 256, 456, 3, 2), "f16", DGRAD, "batch_kernel.bt<"),
 ]
 
 
