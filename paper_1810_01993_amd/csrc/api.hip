@@ -588,8 +588,8 @@ dl_status conv2d_bwd_data(const dl_conv_desc *d, const void *dy, const void *w, 
     // class the contributing taps and the output pixels they pair with form
     // regular grids, so each class is one dense implicit GEMM over dy with the
     // filter re-laid-out as [c][tap][k].  Classes that take the plain engine with
-    // one tile shape share a launch (their tiles of one image region then run
-    // side by side); the others are launched one by one.
+    // one tile shape share a launch (longest reductions first, so that its end is
+    // short); the others are launched one by one.
     struct Pending { dlk::IgemmArgs a; FilterSrc fs; uint16_t *blk; size_t room; };
     Pending pending[dlk::IgemmBatch::MAX];
     int n_pending = 0;
