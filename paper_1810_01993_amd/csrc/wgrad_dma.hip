@@ -95,18 +95,16 @@ __global__ __launch_bounds__(WM *WN * 64) void wgrad_dma_kernel(const WgradArgs 
     // issues in the time of three MFMAs).
     const uint32_t a_bad = a_ch < p.K ? 0u : OOB_OFFSET, b_bad = b_col < RSC ? 0u : OOB_OFFSET;
     uint32_t a_off[AIW], b_off[BIW];
-    int a_left[AIW], b_left[BIW];                           // pixels from this load's to the end of the slice
+    // (load i of a lane is pixel tid / LPR + i * NW * PPI of the step)
 #pragma unroll
     for (int i = 0; i < AIW; ++i) {
-        const int pix = pix_begin + (wave + i * NW) * PPI_A + a_prow;
+        const int pix = pix_begin + tid / LPR_A + i * NW * PPI_A;
         a_off[i] = (uint32_t)(pix * p.K + a_ch) * 2u;
-        a_left[i] = pix_end - pix;
     }
     int b_ih[BIW], b_iw[BIW];                               // input pixel of the tap
 #pragma unroll
     for (int i = 0; i < BIW; ++i) {
-        const int pix = pix_begin + (wave + i * NW) * PPI_B + b_prow;
-        b_left[i] = pix_end - pix;
+        const int pix = pix_begin + tid / LPR_B + i * NW * PPI_B;
         if constexpr (LINEAR) b_off[i] = (uint32_t)(pix * p.C + b_c) * 2u;
         else {
             const int n = pix / (p.P * p.Q), rem = pix - n * (p.P * p.Q), oh = rem / p.Q;
@@ -115,10 +113,16 @@ __global__ __launch_bounds__(WM *WN * 64) void wgrad_dma_kernel(const WgradArgs 
             b_off[i] = (uint32_t)(((n * p.H + b_ih[i]) * p.W + b_iw[i]) * p.C + b_c) * 2u;
         }
     }
-    const uint32_t a_step = (uint32_t)(KB * p.K) * 2u, b_step = (uint32_t)(KB * p.sw * p.C) * 2u;
+    // The pixels of a step as whole images, rows of an image and columns of a row: rows and columns each carry at most once, and
+    // nothing grows with the step times the stride.  The offsets are sums modulo 2^32 whose last value fits; coordinates stay
+    // below 2^31 (launch_cfg).
+    const int step_rows = __builtin_amdgcn_readfirstlane(KB / p.Q), step_n = __builtin_amdgcn_readfirstlane(step_rows / p.P);
+    const int step_ih = (step_rows - step_n * p.P) * p.sh, step_iw = (KB - step_rows * p.Q) * p.sw;
+    const uint32_t a_step = (uint32_t)(KB * p.K) * 2u;
+    const uint32_t b_step = LINEAR ? (uint32_t)(KB * p.C) * 2u : (((uint32_t)step_n * p.H + step_ih) * p.W + step_iw) * p.C * 2u;
     const int row_iw = p.Q * p.sw, col_ih = p.P * p.sh;     // extents of the walk in x
     const int iw_end = row_iw + b_dw, ih_end = col_ih + b_dh;
-    const uint32_t wrap_w = (uint32_t)((p.sh * p.W - row_iw) * p.C) * 2u, wrap_h = (uint32_t)((p.H - col_ih) * p.W * p.C) * 2u;
+    const uint32_t wrap_w = ((uint32_t)p.sh * p.W - row_iw) * p.C * 2u, wrap_h = ((uint32_t)p.H - col_ih) * p.W * p.C * 2u;
     int pix_left = pix_end - pix_begin;                     // pixels from the first of the step to be issued (uniform)
 
     const uint32_t dst0 = lds_addr(lds) + (uint32_t)wave * 1024;
@@ -128,41 +132,32 @@ __global__ __launch_bounds__(WM *WN * 64) void wgrad_dma_kernel(const WgradArgs 
 #pragma unroll
         for (int i = 0; i < AIW; ++i) {
             uint32_t off = a_off[i] | a_bad;
-            if (!whole && a_left[i] <= 0) off = OOB_OFFSET;
+            if (!whole && tid >= (pix_left - i * NW * PPI_A) * LPR_A) off = OOB_OFFSET;
             dma_load_16B(rsA, sa + i * NW * 1024, off);
             a_off[i] += a_step;
-            a_left[i] -= KB;
         }
 #pragma unroll
         for (int i = 0; i < BIW; ++i) {
             uint32_t off = b_off[i] | b_bad;
-            if (!whole && b_left[i] <= 0) off = OOB_OFFSET;
+            if (!whole && tid >= (pix_left - i * NW * PPI_B) * LPR_B) off = OOB_OFFSET;
             if constexpr (!LINEAR)
                 if ((unsigned)b_ih[i] >= (unsigned)p.H || (unsigned)b_iw[i] >= (unsigned)p.W) off = OOB_OFFSET;
             dma_load_16B(rsB, sb + i * NW * 1024, off);
-            b_off[i] += b_step;
-            b_left[i] -= KB;
-            if constexpr (!LINEAR) {
-                b_iw[i] += KB * p.sw;
-                if (p.Q >= KB) {                            // uniform: at most one wrap a step
-                    const bool wrap = b_iw[i] >= iw_end;
-                    b_iw[i] -= wrap ? row_iw : 0;
-                    b_off[i] += wrap ? wrap_w : 0u;
-                    b_ih[i] += wrap ? p.sh : 0;
-                    const bool next = b_ih[i] >= ih_end;
-                    b_ih[i] -= next ? col_ih : 0;
-                    b_off[i] += next ? wrap_h : 0u;
-                } else {
-                    while (b_iw[i] >= iw_end) {
-                        b_iw[i] -= row_iw;
-                        b_off[i] += wrap_w;
-                        b_ih[i] += p.sh;
-                        if (b_ih[i] >= ih_end) {
-                            b_ih[i] -= col_ih;
-                            b_off[i] += wrap_h;
-                        }
-                    }
-                }
+            if constexpr (LINEAR) b_off[i] += b_step;
+            else {
+                b_iw[i] += step_iw;
+                b_ih[i] += step_ih;
+                b_off[i] += b_step;
+                // (all ones or zero, kept as such: as selects the six uniform values would each hold a register of every lane)
+                uint32_t carry = b_iw[i] >= iw_end ? ~0u : 0u;
+                asm("" : "+v"(carry));
+                b_iw[i] -= carry & row_iw;
+                b_off[i] += carry & wrap_w;
+                b_ih[i] += carry & p.sh;
+                uint32_t next = b_ih[i] >= ih_end ? ~0u : 0u;
+                asm("" : "+v"(next));
+                b_ih[i] -= next & col_ih;
+                b_off[i] += next & wrap_h;
             }
         }
         pix_left -= KB;
@@ -265,15 +260,19 @@ __global__ __launch_bounds__(WM *WN * 64) void wgrad_dma_kernel(const WgradArgs 
 }
 
 template <class T, int BM, int BN, int WM, int WN, int KB, int STAGES, bool PP = false>
-static hipError_t launch_cfg(const WgradArgs &a, hipStream_t stream)
+static hipError_t launch_cfg(const WgradArgs &args, hipStream_t stream)
 {
+    WgradArgs a = args;
+    // the stride of an axis with one output position moves nothing, and may be too large to calculate with
+    if (a.P == 1) a.sh = 1;
+    if (a.Q == 1) a.sw = 1;
     const int RSC = a.R * a.S * a.C;
     const int64_t tiles = (int64_t)((a.K + BM - 1) / BM) * ((RSC + BN - 1) / BN);
     const int64_t split_groups = (a.splits + 7) / 8;        // each XCD takes every 8th slice
     const int64_t blocks = a.spread ? tiles * a.splits : tiles * split_groups * 8;
     if (blocks <= 0 || blocks > 0x7fffffff) return hipErrorInvalidValue;
     const dim3 grid((unsigned)blocks), block(WM * WN * 64);
-    const bool linear = a.R * a.S == 1 && a.sh == 1 && a.sw == 1 && a.ph == 0 && a.pw == 0;
+    const bool linear = a.R * a.S == 1 && args.sh == 1 && args.sw == 1 && a.ph == 0 && a.pw == 0;
     if (linear) DLK_LAUNCH(kname("wgrad_dma_kernel", {BM, BN}), (wgrad_dma_kernel<T, BM, BN, WM, WN, KB, STAGES, PP, true>), grid, block, 0, stream, a);
     else DLK_LAUNCH(kname("wgrad_dma_kernel", {BM, BN}), (wgrad_dma_kernel<T, BM, BN, WM, WN, KB, STAGES, PP, false>), grid, block, 0, stream, a);
     return dlk::launch_status();
@@ -438,6 +437,9 @@ static hipError_t dispatch(const WgradArgs &a, int cfg, hipStream_t stream)
 
 hipError_t launch_wgrad_dma(const WgradArgs &a, bool is_bf16, int cfg, hipStream_t stream)
 {
+    // A step takes a coordinate at most one extent and two strides further than the padded image (with two and more outputs no stride
+    // is larger than that): below 2^29 all of it fits 31 bits.  The register-staged kernel counts output pixels instead.
+    if (a.H + 2 * (int64_t)a.ph >= 1 << 29 || a.W + 2 * (int64_t)a.pw >= 1 << 29) return launch_wgrad(a, is_bf16, stream);
     return is_bf16 ? dispatch<BF16>(a, cfg, stream) : dispatch<F16>(a, cfg, stream);
 }
 

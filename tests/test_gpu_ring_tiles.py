@@ -1,6 +1,8 @@
 """Tiles of the direct-to-LDS engine, of the general filter gradient and the stem's kernels at their edges: ragged pixel and
 column tiles, half a 64-channel chunk, split reductions, one patch and many.  Every case names the kernel it has to reach;
 parity against the oracle (whole tensors) within the storage types' bounds, as in the other parity tests."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -119,3 +121,43 @@ def test_stem_keeps_infinities_to_their_windows(api, C):
     met = ((h + 3 - r) % 2 == 0) & ((w + 3 - s) % 2 == 0) & ((h + 3 - r) // 2 < P) & ((w + 3 - s) // 2 < Q)
     assert np.isinf(dw[:, met][:, :, 3]).all() and (dw[:, ~met] == 0).all()
     assert (np.delete(dw, 3, axis=3) == 0).all()
+
+
+# A stride far beyond the image leaves one output column (or row) per image: what a step of pixels advances in the input is then
+# images or rows, and the step times the stride does not fit 32 bits.  2^25 and 2^26 are the first strides at which that is so
+# for steps of 64 and 32 pixels.  (N, H, W, C, K, filter, strides, padding)
+HUGE_STRIDES = [
+    (4096, 1, 1, 64, 64, 1, (1, 40_000_000), 0),
+    (700, 3, 2, 64, 40, 1, (1, 1 << 25), 0),
+    (700, 3, 2, 64, 40, 1, (2_000_000_000, 1), 0),
+    (500, 1, 5, 32, 136, 3, (2_000_000_000, 2_000_000_000), 1),
+    (300, 2, 7, 136, 256, 3, (1, 1 << 26), 1),
+    (2, 1, 3, 64, 32, 1, (1, 4_000_000), (0, 100_000_000)),          # 51 output columns, one of them inside
+    (2, 1, 3, 64, 32, 1, (1, 40_000_000), (0, 1_000_000_000)),       # so wide that the kernel that counts output pixels takes it
+]
+
+
+@pytest.mark.parametrize("N,H,W,C,K,R,stride,pad", HUGE_STRIDES)
+def test_filter_gradient_with_strides_beyond_the_image(api, N, H, W, C, K, R, stride, pad):
+    ph, pw = pad if isinstance(pad, tuple) else (pad, pad)
+    desc = api.ConvDesc(N, H, W, C, K, R, R, stride[0], stride[1], ph, pw, 1, 1, api.DL_F16, api.DL_F32)
+    assert ("wgrad_dma_kernel" if pw < 1 << 28 else "wgrad_kernel") in api.dl_conv_describe(desc, api.PASS_BWD_FILTER)
+    P, Q = api.dl_conv_out_shape(desc)
+    g = torch.Generator().manual_seed(2200 + K)
+    x, dy = torch.randn((N, H, W, C), generator=g).half(), torch.randn((N, P, Q, K), generator=g).half()
+    # (the C entry: the wrapper would also size the data gradient's workspace, class by class of the stride)
+    xd, dyd, dw = x.cuda(), dy.cuda(), torch.full((K, R, R, C), float("nan"), device="cuda")
+    ws = torch.empty(api.dl_conv_workspace_bytes(desc, api.PASS_BWD_FILTER), dtype=torch.uint8, device="cuda")
+    assert api._lib.conv2d_bwd_filter(ctypes.byref(desc.c_struct()), xd.data_ptr(), dyd.data_ptr(), dw.data_ptr(), ws.data_ptr(), ws.numel(),
+                                      torch.cuda.current_stream().cuda_stream) == 0
+    dw = dw.double().cpu()
+    ref = torch.zeros((K, R, R, C), dtype=torch.float64)
+    for p in range(P):
+        for q in range(Q):
+            for r in range(R):
+                for s in range(R):
+                    h, w = p * stride[0] - ph + r, q * stride[1] - pw + s
+                    if 0 <= h < H and 0 <= w < W:
+                        ref[:, r, s] += dy[:, p, q].double().t() @ x[:, h, w].double()
+    # fp32 sums of exact fp16 products, as in the other parity tests with fp32 filter gradients
+    assert float((dw - ref).norm()) <= 1e-5 * float(ref.norm())
