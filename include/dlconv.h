@@ -68,10 +68,10 @@ dl_status dl_conv_out_shape(const dl_conv_desc *desc, int32_t *P, int32_t *Q);
  * one (forward pass and filter gradient): 2 * N*H*W * (C rounded up to a multiple of 8) bytes. */
 dl_status dl_conv_workspace_bytes(const dl_conv_desc *desc, int pass, size_t *bytes);
 
-/* The fewest bytes with which the given pass runs at all; may be 0.  Any workspace from
- * this size on is accepted; below dl_conv_workspace_bytes the pass may take slower kernels
- * (no padded copies, fewer slices of a filter gradient, fewer ranges of a split reduction), whose
- * sums are added in another order. */
+/* The fewest bytes the given pass takes; may be 0.  Any workspace from this size on is accepted;
+ * below dl_conv_workspace_bytes the pass may take slower kernels (no padded copies, fewer slices of
+ * a filter gradient, fewer ranges of a split reduction, or none), whose sums are added in another
+ * order. */
 dl_status dl_conv_least_workspace_bytes(const dl_conv_desc *desc, int pass, size_t *bytes);
 
 /* Which kernels the given pass of this convolution launches, in order, each with

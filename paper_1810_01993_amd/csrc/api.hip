@@ -82,14 +82,12 @@ struct FilterSrc { const uint16_t *src; int64_t base, sj, sr, ss, sc; };
 int halo_columns(const dlk::IgemmArgs &a) { return dlk::igemm_halo_columns(a); }
 
 // Scratch one implicit GEMM needs: the blocked filter copy of a halo kernel, or the fp32 partial
-// sums of a split reduction of the plain engine (never both).  least: the fewest bytes it runs with.
+// sums of a split reduction of the plain engine (never both).  least: the fewest bytes it runs with (the plain engine splits
+// less, or not at all, in less room).
 size_t igemm_scratch_bytes(const dlk::IgemmArgs &a, bool least = false)
 {
     const int cols = halo_columns(a);
-    if (!cols) {
-        const size_t fewest = dlk::igemm_split_least_bytes(a);
-        return align_up(least ? fewest : std::max(fewest, dlk::igemm_split_bytes(a)), 256);
-    }
+    if (!cols) return least ? 0 : align_up(dlk::igemm_split_bytes(a), 256);
     dlk::IgemmArgs h = a;
     h.Nout = cols;
     // (the 5x5 kernel for at most 32 output channels may split its reduction on small maps: partial sums behind the copy)
@@ -564,7 +562,8 @@ dl_status conv2d_bwd_data(const dl_conv_desc *d, const void *dy, const void *w, 
     const size_t need = dgrad_workspace(d, g, stem, true);
     if (need > 0 && (!workspace || workspace_bytes < need)) return DL_ERR_WORKSPACE;
     if (need > 0 && !aligned16(workspace)) return DL_ERR_ALIGN;
-    const bool least = !workspace || !aligned16(workspace) || workspace_bytes < dgrad_workspace(d, g, stem);
+    // what there is beyond that is for partial sums; only without strides is a class dense, and so its reduction ever split
+    const size_t spare = d->stride_h == 1 && d->stride_w == 1 ? workspace_bytes - need : 0;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     const bool bf16 = d->dtype == DL_BF16;
 
@@ -600,7 +599,7 @@ dl_status conv2d_bwd_data(const dl_conv_desc *d, const void *dy, const void *w, 
     if (d->C % 8 == 0 && d->stride_h * d->stride_w <= 64) {
         for (int ca = 0; ca < d->stride_h; ++ca)
             for (int cb = 0; cb < d->stride_w; ++cb) {
-                const DgradClass c = dgrad_class(d, g, ca, cb);
+                const DgradClass c = dgrad_class(d, g, ca, cb, true);
                 if (!c.empty && !c.has_taps) zero_mask |= 1ull << (ca * d->stride_w + cb);
             }
         if (zero_mask && dlk::launch_zero_classes(static_cast<uint16_t *>(dx), d->N, d->H, d->W, d->C, d->stride_h, d->stride_w,
@@ -609,10 +608,11 @@ dl_status conv2d_bwd_data(const dl_conv_desc *d, const void *dy, const void *w, 
     }
     for (int ca = 0; ca < d->stride_h; ++ca)
         for (int cb = 0; cb < d->stride_w; ++cb) {
-            DgradClass c = dgrad_class(d, g, ca, cb, least);
+            DgradClass c = dgrad_class(d, g, ca, cb, true);
             uint16_t *wt = reinterpret_cast<uint16_t *>(static_cast<char *>(workspace) + ws_off);
             uint16_t *blk = reinterpret_cast<uint16_t *>(static_cast<char *>(workspace) + ws_off + c.wt_bytes);
             ws_off += c.wt_bytes + c.blk_bytes;
+            const size_t room = c.blk_bytes + spare;
             if (c.empty || ((zero_mask >> (ca * d->stride_w + cb)) & 1)) continue;
             dlk::IgemmArgs &a = c.args;
             a.A = static_cast<const uint16_t *>(dy);
@@ -643,12 +643,12 @@ dl_status conv2d_bwd_data(const dl_conv_desc *d, const void *dy, const void *w, 
                                c.th.rstep * SC, (int64_t)c.tw.rstep * d->C, (int64_t)d->R * SC};
             if (c.has_taps && halo_columns(a) == 0 && !overflow) {
                 if (n_pending < dlk::IgemmBatch::MAX) {
-                    pending[n_pending++] = Pending{a, fs, blk, c.blk_bytes};
+                    pending[n_pending++] = Pending{a, fs, blk, room};
                     continue;
                 }
                 overflow = true;                        // more classes than one launch holds: one by one after all
             }
-            if (run_igemm(a, bf16, fs, blk, c.blk_bytes, stream) != hipSuccess) return DL_ERR_LAUNCH;
+            if (run_igemm(a, bf16, fs, blk, room, stream) != hipSuccess) return DL_ERR_LAUNCH;
         }
     if (n_pending > 0) {
         dlk::IgemmBatch b{};

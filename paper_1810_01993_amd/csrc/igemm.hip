@@ -241,22 +241,6 @@ size_t igemm_split_bytes(const IgemmArgs &a)
     return pl.ksplits > 1 ? (size_t)pl.ksplits * a.NB * a.OH * a.OW * a.Nout * sizeof(float) : 0;
 }
 
-// The scratch a caller has to bring: what the split that this function's first version chose took (256 x 256 tiles, up to
-// eight ranges).  With less than igemm_split_bytes the plan makes do with what there is.
-size_t igemm_split_least_bytes(const IgemmArgs &a)
-{
-    if (a.Cin % 8 != 0 || !choose_c_outer(a)) return 0;
-    const bool dense = a.osh == 1 && a.osw == 1 && a.FH == a.OH && a.FW == a.OW && a.ldd == a.Nout;
-    const int64_t M = (int64_t)a.NB * a.OH * a.OW;
-    if (!dense || a.Nout < 256 || a.Nout % 256 != 0 || M * a.Nout > (4 << 20)) return 0;
-    const int64_t tiles = ((M + 255) / 256) * (a.Nout / 256), chunks = (a.Cin + BK - 1) / BK;
-    if (chunks * a.TR * a.TS < 256 || tiles > 64) return 0;
-    const int64_t ks = std::min<int64_t>({256 / tiles, 8, chunks});
-    if (ks < 2) return 0;
-    const int64_t per = (chunks + ks - 1) / ks;
-    return (size_t)((chunks + per - 1) / per) * M * a.Nout * sizeof(float);
-}
-
 bool igemm_accepts_transposed_b(const IgemmArgs &a)
 {
     return a.Cin % 8 == 0 && a.Nout % 8 == 0 && !(forced_cfg() < 0 && thin_rows_applicable(a)) && choose_c_outer(a);

@@ -142,9 +142,8 @@ hipError_t launch_igemm_dma_batch(const IgemmBatch &b, bool is_bf16, int cfg, hi
 bool igemm_accepts_transposed_b(const IgemmArgs &a);
 
 // Bytes of partial-sum scratch launch_igemm would use for this GEMM if a.part were set and large enough (0: it would not
-// split), and the fewest it accepts (it splits less, or not at all, in less room than the former).
+// split; in less room it splits less, or not at all).
 size_t igemm_split_bytes(const IgemmArgs &a);
-size_t igemm_split_least_bytes(const IgemmArgs &a);
 
 // is_bf16 selects the MFMA flavour and the output rounding.
 hipError_t launch_igemm(const IgemmArgs &a, bool is_bf16, hipStream_t stream);

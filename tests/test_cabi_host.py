@@ -69,6 +69,23 @@ def test_least_workspace(api):
     assert _code(api.dl_conv_least_workspace_bytes, api.ConvDesc(1, 8, 8, 8, 8, 3, 3, 0), 0) == 2
 
 
+# (N, H, W, C, K, filter, dilation), pass, bytes that were once the least of the pass: the filter copy of a halo kernel, the partial
+# sums of a split with 256 x 256 tiles
+FORMER_LEAST = [((260, 7, 7, 1024, 256, 3, 2), 0, 4718592), ((260, 7, 7, 256, 1024, 3, 2), 1, 9437184), ((300, 6, 8, 512, 256, 5, 1), 0, 6553600),
+                ((300, 6, 8, 256, 512, 5, 1), 1, 13107200), ((46, 107, 2, 520, 256, 5, 1), 0, 6963200), ((2, 48, 72, 2048, 256, 3, 6), 0, 56623104)]
+
+
+@pytest.mark.parametrize("shape,which,former", FORMER_LEAST)
+def test_layers_with_long_reductions_need_no_partial_sums(api, shape, which, former):
+    """The plain engine runs unsplit where there is no room for partial sums: a forward pass takes any workspace, a data gradient
+    what its re-laid-out filter may take; sizes that were enough for a layer's former kernel still are."""
+    N, H, W, C, K, R, dil = shape
+    d = api.ConvDesc(N, H, W, C, K, R, R, 1, 1, dil * (R // 2), dil * (R // 2), dil, dil, api.DL_F16)
+    least, best = api.dl_conv_least_workspace_bytes(d, which), api.dl_conv_workspace_bytes(d, which)
+    assert least == (0 if which == 0 else 2 * R * R * C * K) and least < best
+    assert least <= former
+
+
 def test_wrapper_takes_the_least_workspace_when_memory_is_short(api, monkeypatch):
     torch = api.torch
     big = api.ConvDesc(2, 768, 1152, 300, 256, 3, 3, 1, 1, 1, 1, 1, 1, api.DL_F16)

@@ -86,6 +86,30 @@ def test_tiles_at_their_edges(api, layer, dtype, which, kernel):
     check_layer(api, layer, dtype, synth.seed_for(0, 2000 + [c[0].name for c in CASES].index(layer.name)), x_kind="normal", passes=(name,), full_passes=(name,))
 
 
+@pytest.mark.parametrize("which,C,K,former", [(FWD, 352, 256, 4505600), (DGRAD, 256, 352, 9011200)], ids=["fwd", "dgrad"])
+def test_many_small_maps_without_room_for_the_partial_sums(api, which, C, K, former):
+    """260 maps of 3 x 3 (5x5, long reduction, split when there is room) in the workspace of the halo kernel that once took them, in
+    the least and in the preferred one."""
+    N, H = 260, 3
+    desc = api.ConvDesc(N, H, H, C, K, 5, 5, 1, 1, 2, 2, 1, 1, api.DL_F16)
+    least, best = api.dl_conv_least_workspace_bytes(desc, which), api.dl_conv_workspace_bytes(desc, which)
+    assert "splitk_reduce" in api.dl_conv_describe(desc, which) and least <= former < best
+    g = torch.Generator().manual_seed(2101)
+    w = (torch.randn((K, 5, 5, C), generator=g) * 0.02).half()
+    a = torch.randn((N, H, H, C if which == FWD else K), generator=g).half()
+    nchw = lambda t: t.double().permute(0, 3, 1, 2)                                              # noqa: E731
+    if which == FWD:
+        ref, call = torch.nn.functional.conv2d(nchw(a), nchw(w), padding=2), api.conv2d_fwd
+    else:
+        ref, call = torch.nn.functional.conv_transpose2d(nchw(a), nchw(w), padding=2), api.conv2d_bwd_data
+    ref = ref.permute(0, 2, 3, 1).numpy()
+    for size in (max(least, 16), former, best):
+        buf, ws = U.guarded_workspace(size)
+        out = call(desc, a.cuda(), w.cuda(), workspace=ws)
+        assert U.workspace_guards_intact(buf, size)
+        assert U.rel_err(U.to_host_f64(out), ref) <= U.TOL["f16"], size
+
+
 def test_split_forward_without_room_for_the_partial_sums(api):
     """A forward pass whose reduction is split when there is room runs unsplit, or in fewer ranges, when there is less."""
     layer = L("split.small-workspace", 1, 28, 19, 232, 128, 3, 1, 2)
