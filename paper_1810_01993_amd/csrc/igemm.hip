@@ -155,11 +155,11 @@ static const TileInfo TILES[TILE_COUNT] = {
 
 static int64_t tile_count(const TileInfo &t, int64_t M, int Nout) { return ((M + t.bm - 1) / t.bm) * ((Nout + t.bn - 1) / t.bn); }
 
-static double tiles_per_cu(const TileInfo &t, int64_t tiles)
+static double tiles_per_cu(int per_cu, int64_t tiles)
 {
     const double n = tiles / 256.0;
-    if (n > 2 * t.per_cu) return n + 0.3 * t.per_cu;
-    return n > t.per_cu ? 2 * t.per_cu : std::ceil(n);
+    if (n > 2 * per_cu) return n + 0.3 * per_cu;
+    return n > per_cu ? 2 * per_cu : std::ceil(n);
 }
 
 static double tile_work(const IgemmArgs &a, int tile, int steps)
@@ -180,26 +180,52 @@ static bool tile_considered(const IgemmArgs &a, int tile)
     return true;
 }
 
-static int best_tile(const IgemmArgs &a, double *us)
+// Tap-major order (few channels): 32-deep steps across the taps, and waves that spend longer on an address.  Constants of their
+// own, fitted to 7500 random layers (forward, 50..800000 pixels, 8..120 x 8..1040 channels, 1x1 to 7x7; fp16) timed with every
+// tile: 1.3 % behind the best of each on average, 1.43x at worst.  Tiles wider than the columns are left out, and the largest
+// for short reductions, whose epilogue nothing covers (147000 pixels, 120 -> 256, 1x1: 45 us, 128 x 128 30).
+struct TapMajorTile { int tile, bm, bn, per_cu; TileCost cost; };
+static const TapMajorTile TAP_MAJOR_TILES[] = {{TILE_64x32, 64, 32, 6, {3.77, 0.109, 0.23}},
+                                               {TILE_64x64, 64, 64, 4, {3.35, 0.126, 0.51}},
+                                               {TILE_128x64, 128, 64, 3, {3.40, 0.188, 0.98}},
+                                               {TILE_128x128, 128, 128, 2, {2.50, 0.225, 2.03}},
+                                               {TILE_256x256, 256, 256, 1, {2.50, 0.633, 6.22}}};
+
+static int best_tap_major_tile(const IgemmArgs &a, double *us)
 {
     const int64_t M = (int64_t)a.NB * a.OH * a.OW;
+    const int steps = (a.TR * a.TS * a.Cin + BK - 1) / BK;
+    // An output of more than 240 MB (the last-level cache holds 256) and little else to do: rows of it as wide as a tile can (500000
+    // pixels, 24 -> 440, 1x1: 124 us, 128 x 128 166, cut 151; below that size 128 x 128 is 1.2x as fast), cut only where the last
+    // tile would be mostly empty (506000 pixels, 24 -> 320: cut 102 us, 142 in one; from 400 MB on one launch is as fast from 65
+    // columns on).  These times are not the sum of steps that the estimates below are.
+    if (M * a.Nout >= 120000000 && a.Nout > 128 && steps < 16) {
+        const int rem = a.Nout % 256;
+        const bool cut = a.Nout > 256 && rem > 0 && rem <= (M * a.Nout < 200000000 ? 128 : 64);
+        *us = cut ? 1e9 : 0;
+        return TILE_256x256;
+    }
     int best = -1;
-    for (int t = 0; t < TILE_COUNT; ++t) {
-        if (!tile_considered(a, t)) continue;
-        const double est = TILES[t].cost[a.TR * a.TS == 1 ? 0 : 1].t0 + tile_work(a, t, tile_steps(a, t)) * tiles_per_cu(TILES[t], tile_count(TILES[t], M, a.Nout));
-        if (best < 0 || est < *us) { best = t; *us = est; }
+    for (const TapMajorTile &t : TAP_MAJOR_TILES) {
+        if ((t.tile == TILE_64x32) != (a.Nout <= 32) || (t.bn >= 128 && a.Nout <= 64) || (t.bn == 256 && (a.Nout <= 128 || steps < 16))) continue;
+        const int64_t tiles = ((M + t.bm - 1) / t.bm) * ((a.Nout + t.bn - 1) / t.bn);
+        const double est = t.cost.t0 + (steps * t.cost.step + t.cost.fix) * tiles_per_cu(t.per_cu, tiles);
+        if (best < 0 || est < *us) { best = t.tile; *us = est; }
     }
     return best;
 }
 
-// Tap-major order (few channels): only the tiles with 32-deep steps, the largest that yields enough workgroups.
-static int tap_major_tile(const IgemmArgs &a)
+static int best_tile(const IgemmArgs &a, double *us)
 {
+    if (!choose_c_outer(a)) return best_tap_major_tile(a, us);
     const int64_t M = (int64_t)a.NB * a.OH * a.OW;
-    const auto enough = [&](int bm, int bn) { return ((M + bm - 1) / bm) * ((a.Nout + bn - 1) / bn) >= 200; };
-    if (a.Nout <= 32) return TILE_64x32;
-    if (a.Nout > 64 && enough(128, 128)) return TILE_128x128;
-    return enough(128, 64) ? TILE_128x64 : TILE_64x64;
+    int best = -1;
+    for (int t = 0; t < TILE_COUNT; ++t) {
+        if (!tile_considered(a, t)) continue;
+        const double est = TILES[t].cost[a.TR * a.TS == 1 ? 0 : 1].t0 + tile_work(a, t, tile_steps(a, t)) * tiles_per_cu(TILES[t].per_cu, tile_count(TILES[t], M, a.Nout));
+        if (best < 0 || est < *us) { best = t; *us = est; }
+    }
+    return best;
 }
 
 // How a GEMM runs: tile, and the ranges its reduction is cut into (1: not cut) of `chunks` 32-channel chunks each.
@@ -213,9 +239,9 @@ static IgemmPlan make_plan(const IgemmArgs &a, size_t room)
 {
     IgemmPlan pl{0, 1, 0};
     if (forced_cfg() >= 0) { pl.tile = forced_cfg(); return pl; }
-    if (!choose_c_outer(a)) { pl.tile = tap_major_tile(a); return pl; }
     double us = 0;
     pl.tile = best_tile(a, &us);
+    if (!choose_c_outer(a)) return pl;
     const bool dense = a.osh == 1 && a.osw == 1 && a.FH == a.OH && a.FW == a.OW && a.ldd == a.Nout;
     const int64_t M = (int64_t)a.NB * a.OH * a.OW;
     if (!dense || a.Nout % 8 != 0 || M * a.Nout > (4 << 20)) return pl;
@@ -226,7 +252,7 @@ static IgemmPlan make_plan(const IgemmArgs &a, size_t room)
             const int per = (chunks + 2 * ks - 1) / (2 * ks) * 2;             // whole 64-channel steps
             const int ranges = (chunks + per - 1) / per;
             if (ranges != ks || (size_t)ks * M * a.Nout * sizeof(float) > room) continue;
-            const double est = t.cost[a.TR * a.TS == 1 ? 0 : 1].t0 + tile_work(a, tile, per / 2 * a.TR * a.TS) * tiles_per_cu(t, tile_count(t, M, a.Nout) * ks) +
+            const double est = t.cost[a.TR * a.TS == 1 ? 0 : 1].t0 + tile_work(a, tile, per / 2 * a.TR * a.TS) * tiles_per_cu(t.per_cu, tile_count(t, M, a.Nout) * ks) +
                                4.0 + 8.0 * ks * M * a.Nout / 8e6;
             if (est < us) { us = est; pl = IgemmPlan{tile, ks, per}; }
         }
@@ -281,9 +307,9 @@ static hipError_t dispatch(const IgemmArgs &a, hipStream_t stream)
         IgemmArgs lo = b, hi = b;
         lo.Nout = a.Nout - rem;
         hi.Nout = rem;
-        double whole = 1, us_lo = 0, us_hi = 0;          // (tap-major: always cut)
-        if (b.c_outer) best_tile(b, &whole);
-        const int t_lo = b.c_outer ? best_tile(lo, &us_lo) : tap_major_tile(lo), t_hi = b.c_outer ? best_tile(hi, &us_hi) : tap_major_tile(hi);
+        double whole = 0, us_lo = 0, us_hi = 0;
+        best_tile(b, &whole);
+        const int t_lo = best_tile(lo, &us_lo), t_hi = best_tile(hi, &us_hi);
         if (us_lo + us_hi < whole) {
             if (a.b_transposed) hi.b_base = a.b_base + lo.Nout;
             else hi.B = a.B + (size_t)lo.Nout * a.TR * a.TS * a.Cin;
@@ -317,7 +343,7 @@ int igemm_batch_cfg(const IgemmArgs *a, int n)
             work += own * tile_work(a[i], tile, tile_steps(a[i], tile));
         }
         const bool considered = tile == TILE_64x32 ? a[0].Nout <= 32 : true;
-        const double us = t.cost[1].t0 + work / tiles * tiles_per_cu(t, tiles);
+        const double us = t.cost[1].t0 + work / tiles * tiles_per_cu(t.per_cu, tiles);
         if (considered && (best < 0 || us < best_us)) { best = tile; best_us = us; }
     }
     return best;

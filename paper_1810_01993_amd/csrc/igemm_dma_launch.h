@@ -104,6 +104,7 @@ static hipError_t dispatch_dma(const IgemmArgs &a, int cfg, hipStream_t stream)
             case TILE_64x64: return launch_dma_tap_major<T, 64, 64, 2, 2>(a, stream);
             case TILE_128x64: return launch_dma_tap_major<T, 128, 64, 4, 1>(a, stream);
             case TILE_128x128: return launch_dma_tap_major<T, 128, 128, 4, 2>(a, stream);
+            case TILE_256x256: return launch_dma_tap_major<T, 256, 256, 2, 4>(a, stream);
             default: return hipErrorInvalidValue;
         }
     }

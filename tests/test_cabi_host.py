@@ -86,6 +86,17 @@ def test_layers_with_long_reductions_need_no_partial_sums(api, shape, which, for
     assert least <= former
 
 
+# Layers with few channels (tap-major order) and a column range behind a multiple of 256: one launch where a second one's start and
+# end would cost more than its columns save (two took 1.5-1.7x the time), two where whole rounds of tiles are saved, or where
+# the output exceeds the caches and the last of its widest tiles would be mostly empty
+@pytest.mark.parametrize("N,H,W,C,K,R,launches", [(1, 24, 36, 40, 264, 1, 1), (1, 96, 144, 56, 384, 3, 1), (1, 45, 67, 104, 320, 1, 1),
+                                                  (1, 1, 1, 8, 304, 1, 1), (1, 96, 170, 8, 576, 3, 2), (2, 400, 632, 24, 320, 1, 2),
+                                                  (2, 400, 625, 24, 440, 1, 1)])
+def test_tap_major_column_ranges(api, N, H, W, C, K, R, launches):
+    text = api.dl_conv_describe(api.ConvDesc(N, H, W, C, K, R, R, 1, 1, R // 2, R // 2, 1, 1, api.DL_F16), api.PASS_FWD)
+    assert text.count("igemm_dma_kernel.tapmajor") == launches and text.count("kernel") == launches, text
+
+
 def test_wrapper_takes_the_least_workspace_when_memory_is_short(api, monkeypatch):
     torch = api.torch
     big = api.ConvDesc(2, 768, 1152, 300, 256, 3, 3, 1, 1, 1, 1, 1, 1, api.DL_F16)

@@ -167,6 +167,8 @@ RESIDUAL_CASES = [
     (L("r.128x128.ragged", 1, 90, 101, 160, 264, 1, 1, 1, 0, 1), "bf16"),
     (L("r.128x64.ragged", 1, 90, 101, 96, 136, 1, 1, 1, 0, 1), "f16"),
     (L("r.64x64.ragged", 1, 23, 29, 256, 72, 1, 1, 1, 0, 1), "f16"),
+    (L("r.tapmajor.c40.k264", 1, 25, 36, 40, 264, 1, 1, 1, 0, 1), "bf16"),
+    (L("r.tapmajor.cut", 1, 96, 170, 8, 576, 3, 3, 1, 1, 1), "f16"),
     (L("r.short.ragged", 1, 181, 185, 64, 200, 1, 1, 1, 0, 1), "f16"),
     (L("r.short.32.s2", 1, 511, 514, 32, 72, 1, 1, 2, 0, 1), "bf16"),
     (L("r.scalar.c23.k32", 2, 19, 23, 23, 32, 1, 1, 1, 0, 1), "bf16"),
