@@ -73,34 +73,28 @@ AxisTaps class_taps(int a, int R, int stride, int pad, int dil)
     return t;
 }
 
-// ---- one implicit GEMM, with the halo-tile kernel where it applies ------------
+// ---- one implicit GEMM, with a halo-tile kernel where one applies -------------
 // Where the coefficients of the GEMM's filter operand live in the caller's
 // filter tensor: element (row j, tap (jr, js), reduction channel c) is
 // src[base + j*sj + jr*sr + js*ss + c*sc].
 struct FilterSrc { const uint16_t *src; int64_t base, sj, sr, ss, sc; };
-
-int halo_columns(const dlk::IgemmArgs &a) { return dlk::igemm_halo_columns(a); }
 
 // Scratch one implicit GEMM needs: the blocked filter copy of a halo kernel, or the fp32 partial
 // sums of a split reduction of the plain engine (never both).  least: the fewest bytes it runs with (the plain engine splits
 // less, or not at all, in less room).
 size_t igemm_scratch_bytes(const dlk::IgemmArgs &a, bool least = false)
 {
-    const int cols = halo_columns(a);
-    if (!cols) return least ? 0 : align_up(dlk::igemm_split_bytes(a), 256);
-    dlk::IgemmArgs h = a;
-    h.Nout = cols;
+    if (!dlk::igemm_halo_takes(a)) return least ? 0 : align_up(dlk::igemm_split_bytes(a), 256);
     // (the 5x5 kernel for at most 32 output channels may split its reduction on small maps: partial sums behind the copy)
-    const size_t part = dlk::igemm_narrow5x5_applicable(h) ? align_up(dlk::igemm_narrow5x5_split_bytes(h), 256) : 0;
-    return align_up(dlk::igemm_blocked_filter_bytes(h), 256) + part;
+    const size_t part = dlk::igemm_narrow5x5_applicable(a) ? align_up(dlk::igemm_narrow5x5_split_bytes(a), 256) : 0;
+    return align_up(dlk::igemm_blocked_filter_bytes(a), 256) + part;
 }
 
-// a.B: plain [Nout][taps*Cin] filter (may be null if the halo kernel takes every column).
+// a.B: plain [Nout][taps*Cin] filter (may be null if a halo kernel takes the GEMM).
 // room: bytes at scratch.
 hipError_t run_igemm(const dlk::IgemmArgs &a, bool bf16, const FilterSrc &fs, uint16_t *scratch, size_t room, hipStream_t stream)
 {
-    const int cols = halo_columns(a);
-    if (!cols) {
+    if (!dlk::igemm_halo_takes(a)) {
         dlk::IgemmArgs g = a;
         g.part = room > 0 ? reinterpret_cast<float *>(scratch) : nullptr;
         g.part_bytes = room;
@@ -109,22 +103,13 @@ hipError_t run_igemm(const dlk::IgemmArgs &a, bool bf16, const FilterSrc &fs, ui
     dlk::FilterBlockArgs f{};
     f.src = fs.src; f.dst = scratch;
     f.base = fs.base; f.sj = fs.sj; f.sr = fs.sr; f.ss = fs.ss; f.sc = fs.sc;
-    f.Nrows = cols; f.TR = a.TR; f.TS = a.TS; f.Cin = a.Cin;
-    hipError_t e = dlk::launch_filter_block(f, stream);
+    f.Nrows = a.Nout; f.TR = a.TR; f.TS = a.TS; f.Cin = a.Cin;
+    const hipError_t e = dlk::launch_filter_block(f, stream);
     if (e != hipSuccess) return e;
     dlk::IgemmArgs h = a;
-    h.Nout = cols;
     h.B = scratch;
     h.part = reinterpret_cast<float *>(reinterpret_cast<char *>(scratch) + align_up(dlk::igemm_blocked_filter_bytes(h), 256));
-    e = dlk::launch_igemm_halo(h, bf16, stream);
-    if (e != hipSuccess || cols == a.Nout) return e;
-    dlk::IgemmArgs r = a;
-    r.Nout = a.Nout - cols;
-    r.B = a.B + (size_t)cols * a.TR * a.TS * a.Cin;
-    r.D = a.D + cols;
-    if (a.bias) r.bias = a.bias + cols;
-    if (a.resid) r.resid = a.resid + cols;
-    return dlk::launch_igemm(r, bf16, stream);
+    return dlk::launch_igemm_halo(h, bf16, stream);
 }
 
 // ---- channel counts that are not a multiple of 8 -------------------------------
@@ -188,7 +173,7 @@ bool fwd_copies_pay(const dl_conv_desc *d, const dl_conv_desc *e, const dlk::Ige
     // 21 us without, 28 with it), and the padded reduction may not have too many steps of 32 against that kernel's;
     // a halo kernel takes whole 32-channel chunks of every tap.
     if (copy > 1.0 && own < (steps == 1 ? 6 : steps <= 3 ? 4 : 2) * copy) return false;
-    if (!halo_columns(a)) return 2 * ((taps * e->C + 31) / 32) <= 7 * steps;
+    if (!dlk::igemm_halo_takes(a)) return 2 * ((taps * e->C + 31) / 32) <= 7 * steps;
     // 3x3, measured with 3..13 channels: 64 outputs 0.7-1.0x up to 5 channels, 1.0-1.1x with 6 and 7; at most 16 outputs
     // 0.6-0.97x up to 10 channels, 1.0-1.2x with 11; above 64 outputs 0.98x and more from 4 channels on (dilated 0.6-0.8x
     // with 6 and 7)
@@ -618,10 +603,10 @@ dl_status conv2d_bwd_data(const dl_conv_desc *d, const void *dy, const void *w, 
             a.A = static_cast<const uint16_t *>(dy);
             a.D = static_cast<uint16_t *>(dx);
             a.B = static_cast<const uint16_t *>(w);     // never read when there are no taps
-            const bool all_halo = c.has_taps && halo_columns(a) == a.Nout;
+            const bool halo = c.has_taps && dlk::igemm_halo_takes(a);
             const int64_t SC = (int64_t)d->S * d->C;
             // the plain engine can take the filter as it lies in memory (reduction-major for this GEMM)
-            const bool direct = c.has_taps && halo_columns(a) == 0 && dlk::igemm_accepts_transposed_b(a);
+            const bool direct = c.has_taps && !halo && dlk::igemm_accepts_transposed_b(a);
             if (direct) {
                 a.b_transposed = 1;
                 a.b_base = (int32_t)(c.th.r0 * SC + (int64_t)c.tw.r0 * d->C);
@@ -629,7 +614,7 @@ dl_status conv2d_bwd_data(const dl_conv_desc *d, const void *dy, const void *w, 
                 a.b_ss = (int32_t)((int64_t)c.tw.rstep * d->C);
                 a.b_ldk = (int32_t)((int64_t)d->R * SC);
                 a.b_elems = (int32_t)g.w_elems;
-            } else if (c.has_taps && !all_halo) {
+            } else if (c.has_taps && !halo) {
                 dlk::FilterRelayoutArgs f{};
                 f.w = static_cast<const uint16_t *>(w);
                 f.wt = wt;
@@ -641,7 +626,7 @@ dl_status conv2d_bwd_data(const dl_conv_desc *d, const void *dy, const void *w, 
             }
             const FilterSrc fs{static_cast<const uint16_t *>(w), c.th.r0 * SC + (int64_t)c.tw.r0 * d->C, 1,
                                c.th.rstep * SC, (int64_t)c.tw.rstep * d->C, (int64_t)d->R * SC};
-            if (c.has_taps && halo_columns(a) == 0 && !overflow) {
+            if (c.has_taps && !halo && !overflow) {
                 if (n_pending < dlk::IgemmBatch::MAX) {
                     pending[n_pending++] = Pending{a, fs, blk, room};
                     continue;

@@ -97,8 +97,8 @@ struct IgemmArgs {
     // ... + resid[same element as D] before the activation (the skip connection of a residual block):
     // indexed exactly like D (a launch that offsets D by columns offsets resid alike); null: none.
     // The kernels with an LDS-staged coalesced store that cannot reach it before rounding (3x3 halo-tile,
-    // narrow / wide 5x5) do not take such launches; the plain engine, the general halo-tile kernel, the
-    // streaming kernel for few input channels and the split reduction do.
+    // narrow / wide 5x5) do not take such launches; the plain engine, the streaming kernel for few input
+    // channels and the split reduction do.
     const uint16_t *resid;
     // Division by OH*OW and by OW as multiplication and shift (FastDiv), set by launch_igemm / launch_igemm_batch.
     uint32_t mul_hw, mul_w;
@@ -167,9 +167,9 @@ inline bool resid_prefetchable(const IgemmArgs &a)
            ((reinterpret_cast<uintptr_t>(a.D) | reinterpret_cast<uintptr_t>(a.resid)) & 15) == 0;
 }
 
-// Halo-tile variant for stride-1 multi-tap filters.  a.B must point at the
+// Halo-tile variants for stride-1 multi-tap filters: whether one takes this GEMM, and its launch.  a.B must point at the
 // blocked filter copy [chunk][tap][a.Nout][32] made by launch_filter_block.
-int igemm_halo_columns(const IgemmArgs &a);
+bool igemm_halo_takes(const IgemmArgs &a);
 // Dense 5x5, unit stride and dilation, forward-oriented taps, 8..32 output columns (a multiple of 8), D 16-byte
 // aligned: one 32-wide column tile per 16 x 32 pixel patch; a.B as for the other halo-tile kernels.
 bool igemm_narrow5x5_applicable(const IgemmArgs &a);

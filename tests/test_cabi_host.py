@@ -97,6 +97,14 @@ def test_tap_major_column_ranges(api, N, H, W, C, K, R, launches):
     assert text.count("igemm_dma_kernel.tapmajor") == launches and text.count("kernel") == launches, text
 
 
+@pytest.mark.parametrize("N,H,W,C,K,R,dil,which", [(2, 141, 179, 96, 192, 5, 1, 0), (1, 230, 250, 32, 192, 3, 2, 0), (2, 147, 160, 256, 304, 5, 1, 0),
+                                                   (1, 182, 263, 256, 128, 3, 2, 1), (223, 20, 22, 512, 320, 3, 3, 0)])
+def test_dilated_and_5x5_layers_of_one_round_of_patches(api, N, H, W, C, K, R, dil, which):
+    """200..256 patches of 16 x 16: on the ring kernels, without a filter copy."""
+    text = api.dl_conv_describe(api.ConvDesc(N, H, W, C, K, R, R, 1, 1, dil * (R // 2), dil * (R // 2), dil, dil, api.DL_BF16), which)
+    assert "igemm_dma_kernel" in text and "filter_block" not in text, text
+
+
 def test_wrapper_takes_the_least_workspace_when_memory_is_short(api, monkeypatch):
     torch = api.torch
     big = api.ConvDesc(2, 768, 1152, 300, 256, 3, 3, 1, 1, 1, 1, 1, 1, api.DL_F16)

@@ -178,11 +178,10 @@ def test_big_tile_path(api):
     check_layer(api, L("bigtile", 2, 192, 288, 16, 256, 3, 3, 1, 1, 1), "f16", synth.seed_for(0, 501))
 
 
-# Shapes that take the halo-tile kernels (stride 1, several taps, >= 200
-# tiles): the 3x3 unit-dilation kernel and the general one; ragged patches,
-# ragged channel chunk, ragged column tile, dilation 2, a column remainder
-# handed to the plain engine, no padding, both data types, every column-tile
-# width of the 3x3 kernel (128, 160, <= 64) alone and mixed.
+# Stride 1, several taps, 200 and more patches: the 3x3 unit-dilation halo-tile
+# kernel, and the ring kernels with dilation 2 and 5x5; ragged patches, ragged
+# channel chunk, ragged column tile, no padding, both data types, every
+# column-tile width of the 3x3 kernel (128, 160, <= 64) alone and mixed.
 HALO = [
     (L("halo.ragged", 2, 150, 170, 40, 256, 3, 3, 1, 1, 1), "f16"),
     (L("halo.d2.n192", 1, 230, 250, 32, 192, 3, 3, 1, 2, 2), "bf16"),
@@ -275,7 +274,7 @@ ODD_LARGE = [
     (L("odd.narrow5x5.c20", 1, 300, 240, 20, 32, 5, 5, 1, 2, 1), "f16", "fwd", "igemm_narrow5x5_kernel"),
     (L("odd.narrow5x5.c90.split", 4, 50, 70, 90, 32, 5, 5, 1, 2, 1), "bf16", "fwd", "igemm_narrow5x5_kernel"),
     (L("odd.wide5x5.c12", 1, 150, 230, 12, 72, 5, 5, 1, 2, 1), "f16", "fwd", "igemm_wide5x5_kernel"),
-    (L("odd.halo.d2.c30", 1, 230, 250, 30, 192, 3, 3, 1, 2, 2), "bf16", "fwd", "igemm_halo_kernel"),
+    (L("odd.halo.d2.c30", 1, 230, 250, 30, 192, 3, 3, 1, 2, 2), "bf16", "fwd", "igemm_dma_kernel"),
     (L("odd.short.c60", 1, 270, 270, 60, 200, 1, 1, 1, 0, 1), "f16", "fwd", "igemm_short_kernel"),
     (L("odd.split.c997", 1, 20, 24, 997, 256, 3, 3, 1, 1, 1), "f16", "fwd", "splitk_reduce"),
     (L("odd.remainder.c70", 1, 250, 240, 70, 304, 1, 1, 1, 0, 1), "bf16", "fwd", "<128,64>"),

@@ -1,7 +1,7 @@
 """GPU parity of conv2d_fwd_bias_relu (bias and ReLU fused into the store of the
 forward convolution) against the fp64 oracle, on shapes that reach every
-forward kernel: the 3x3 halo-tile kernel with each column-tile width, the
-general halo-tile kernel, every tile of the plain engine, the one-step kernel,
+forward kernel: the 3x3 halo-tile kernel with each column-tile width,
+every tile of the plain engine, the one-step kernel,
 the split reduction, the element-wise kernel and the channel-padded copies for
 odd channel counts, the 3-column logits layer."""
 import sys
@@ -61,7 +61,7 @@ CASES = [
     (L("e.halo3x3.k256", 1, 200, 230, 40, 256, 3, 3, 1, 1, 1), "f16"),            # two 128-wide column tiles
     (L("e.halo3x3.k304", 1, 150, 260, 32, 304, 3, 3, 1, 1, 1), "bf16"),           # two 160-wide tiles, ragged
     (L("e.halo3x3.k192", 1, 210, 300, 24, 192, 3, 3, 1, 1, 1), "f16"),            # 128 + a 64-wide tile (bias offset)
-    (L("e.halo.d2.k192", 1, 230, 250, 32, 192, 3, 3, 1, 2, 2), "bf16"),           # general halo kernel + remainder launch
+    (L("e.halo.d2.k192", 1, 230, 250, 32, 192, 3, 3, 1, 2, 2), "bf16"),           # dilated, 232 patches
     (L("e.halo3x3.c16.k256", 2, 192, 288, 16, 256, 3, 3, 1, 1, 1), "f16"),
     (L("e.short.k304", 2, 150, 200, 64, 304, 1, 1, 1, 0, 1), "f16"),              # the one-step kernel
     (L("e.dma.small", 2, 19, 23, 24, 40, 3, 3, 1, 1, 1), "bf16"),
@@ -144,7 +144,7 @@ def check_residual(api, layer: ConvLayer, dtype: str, seed: int, bias=True, relu
 
 # every kernel a launch with a residual can take: the plain engine's staged store (several tile shapes, strided,
 # a remainder launch with offset pointers, output channels not a multiple of 4 or 8), its split reduction, the
-# general halo-tile kernel (+ remainder), the element-wise kernel, channel-padded copies, the streaming kernel for few
+# element-wise kernel, channel-padded copies, the streaming kernel for few
 # input channels, the one-step kernel;
 # and the shapes that would take the 3x3 or 5x5 patch kernels without one
 RESIDUAL_CASES = [
@@ -184,7 +184,7 @@ def test_bias_residual_relu(api, layer, dtype):
 # the kernel that a case is named for is the one it reaches (dl_conv_describe plans a call without a residual)
 KERNELS = {"e.scalar": "igemm_scalar_kernel", "r.scalar": "igemm_scalar_kernel", "e.padded": "pad_channels_kernel",
            "r.padded": "pad_channels_kernel", "e.short": "igemm_short_kernel", "r.short": "igemm_short_kernel",
-           "e.halo3x3": "igemm_halo3x3_kernel", "e.halo.": "igemm_halo_kernel", "e.dma": "igemm_dma_kernel",
+           "e.halo3x3": "igemm_halo3x3_kernel", "e.halo.": "igemm_dma_kernel", "e.dma": "igemm_dma_kernel",
            "e.ksplit": "splitk_reduce", "e.narrow5x5": "igemm_narrow5x5_kernel", "e.thin": "thin_rows_kernel",
            "e.logits": "thin_cols_kernel"}
 
