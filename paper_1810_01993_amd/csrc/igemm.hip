@@ -182,13 +182,14 @@ static bool tile_considered(const IgemmArgs &a, int tile)
 
 // Tap-major order (few channels): 32-deep steps across the taps, and waves that spend longer on an address.  Constants of their
 // own, fitted to 7500 random layers (forward, 50..800000 pixels, 8..120 x 8..1040 channels, 1x1 to 7x7; fp16) timed with every
-// tile: 1.3 % behind the best of each on average, 1.43x at worst.  Tiles wider than the columns are left out, and the largest
+// tile: 1.0 % behind the best of each on average, 1.43x at worst (rounds counted in halves while all tiles are resident: 270 tiles on
+// 256 compute units take less than twice as long as 256).  Tiles wider than the columns are left out, and the largest
 // for short reductions, whose epilogue nothing covers (147000 pixels, 120 -> 256, 1x1: 45 us, 128 x 128 30).
 struct TapMajorTile { int tile, bm, bn, per_cu; TileCost cost; };
-static const TapMajorTile TAP_MAJOR_TILES[] = {{TILE_64x32, 64, 32, 6, {3.77, 0.109, 0.23}},
-                                               {TILE_64x64, 64, 64, 4, {3.35, 0.126, 0.51}},
-                                               {TILE_128x64, 128, 64, 3, {3.40, 0.188, 0.98}},
-                                               {TILE_128x128, 128, 128, 2, {2.50, 0.225, 2.03}},
+static const TapMajorTile TAP_MAJOR_TILES[] = {{TILE_64x32, 64, 32, 6, {3.75, 0.113, 0.22}},
+                                               {TILE_64x64, 64, 64, 4, {3.36, 0.129, 0.51}},
+                                               {TILE_128x64, 128, 64, 3, {3.41, 0.191, 0.98}},
+                                               {TILE_128x128, 128, 128, 2, {2.50, 0.226, 2.05}},
                                                {TILE_256x256, 256, 256, 1, {2.50, 0.633, 6.22}}};
 
 static int best_tap_major_tile(const IgemmArgs &a, double *us)
@@ -209,7 +210,8 @@ static int best_tap_major_tile(const IgemmArgs &a, double *us)
     for (const TapMajorTile &t : TAP_MAJOR_TILES) {
         if ((t.tile == TILE_64x32) != (a.Nout <= 32) || (t.bn >= 128 && a.Nout <= 64) || (t.bn == 256 && (a.Nout <= 128 || steps < 16))) continue;
         const int64_t tiles = ((M + t.bm - 1) / t.bm) * ((a.Nout + t.bn - 1) / t.bn);
-        const double est = t.cost.t0 + (steps * t.cost.step + t.cost.fix) * tiles_per_cu(t.per_cu, tiles);
+        const double load = tiles <= 256 * t.per_cu ? std::max(1.0, std::ceil(tiles / 128.0) / 2) : tiles_per_cu(t.per_cu, tiles);
+        const double est = t.cost.t0 + (steps * t.cost.step + t.cost.fix) * load;
         if (best < 0 || est < *us) { best = t.tile; *us = est; }
     }
     return best;
