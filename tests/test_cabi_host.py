@@ -105,6 +105,13 @@ def test_dilated_and_5x5_layers_of_one_round_of_patches(api, N, H, W, C, K, R, d
     assert "igemm_dma_kernel" in text and "filter_block" not in text, text
 
 
+def test_stem_filter_gradient_of_a_few_pixels(api):
+    """Less than 64 output pixels, 16 channels and less than 32 outputs: the general kernel; from there on the stem's."""
+    for N, H, W, C, K, kernel in ((1, 15, 15, 16, 24, "wgrad_stem"), (1, 14, 15, 16, 24, "wgrad_kernel"), (1, 8, 8, 16, 8, "wgrad_kernel"),
+                                  (1, 8, 8, 16, 32, "wgrad_stem"), (1, 8, 8, 8, 8, "wgrad_stem")):
+        assert kernel in api.dl_conv_describe(api.ConvDesc(N, H, W, C, K, 7, 7, 2, 2, 3, 3, 1, 1, api.DL_F16), api.PASS_BWD_FILTER)
+
+
 def test_wrapper_takes_the_least_workspace_when_memory_is_short(api, monkeypatch):
     torch = api.torch
     big = api.ConvDesc(2, 768, 1152, 300, 256, 3, 3, 1, 1, 1, 1, 1, 1, api.DL_F16)
