@@ -273,8 +273,9 @@ static hipError_t launch_cfg(const WgradArgs &args, hipStream_t stream)
     if (blocks <= 0 || blocks > 0x7fffffff) return hipErrorInvalidValue;
     const dim3 grid((unsigned)blocks), block(WM * WN * 64);
     const bool linear = a.R * a.S == 1 && args.sh == 1 && args.sw == 1 && a.ph == 0 && a.pw == 0;
-    if (linear) DLK_LAUNCH(kname("wgrad_dma_kernel", {BM, BN}), (wgrad_dma_kernel<T, BM, BN, WM, WN, KB, STAGES, PP, true>), grid, block, 0, stream, a);
-    else DLK_LAUNCH(kname("wgrad_dma_kernel", {BM, BN}), (wgrad_dma_kernel<T, BM, BN, WM, WN, KB, STAGES, PP, false>), grid, block, 0, stream, a);
+    const auto label = [&]() { return kname("wgrad_dma_kernel", {BM, BN}) + (KB == 64 ? ".k64" : "") + (linear ? ".linear" : ""); };
+    if (linear) DLK_LAUNCH(label(), (wgrad_dma_kernel<T, BM, BN, WM, WN, KB, STAGES, PP, true>), grid, block, 0, stream, a);
+    else DLK_LAUNCH(label(), (wgrad_dma_kernel<T, BM, BN, WM, WN, KB, STAGES, PP, false>), grid, block, 0, stream, a);
     return dlk::launch_status();
 }
 

@@ -75,7 +75,7 @@ CASES = [
     (L("e.narrow5x5.k32", 4, 75, 200, 16, 32, 5, 5, 1, 2, 1), "f16"),             # 5x5 kernel for <= 32 output channels
     (L("e.narrow5x5.k24", 3, 100, 230, 40, 24, 5, 5, 1, 2, 1), "bf16"),
     (L("e.narrow5x5.ksplit", 4, 50, 70, 96, 32, 5, 5, 1, 2, 1), "f16"),             # its split reduction: tail in the reduce kernel
-    (L("e.dma.k304.c96.remainder", 2, 150, 200, 96, 304, 1, 1, 1, 0, 1), "bf16"),  # 256 x 256 tiles + 48 columns: two launches
+    (L("e.dma.k304.c96.remainder", 2, 150, 200, 96, 304, 1, 1, 1, 0, 1), "bf16"),  # 304 columns on 128 x 128 tiles, the last short
     (L("e.scalar.c23.k32", 2, 19, 23, 23, 32, 1, 1, 1, 0, 1), "f16"),              # element-wise: at most 24 elements to add
     (L("e.scalar.c2.k5", 2, 19, 23, 2, 5, 3, 3, 1, 1, 1), "bf16"),
     (L("e.scalar.7x7.c1.k72", 1, 40, 31, 1, 72, 7, 7, 2, 3, 1), "f16"),            # element-wise: one channel
@@ -167,12 +167,18 @@ RESIDUAL_CASES = [
     (L("r.128x128.ragged", 1, 90, 101, 160, 264, 1, 1, 1, 0, 1), "bf16"),
     (L("r.128x64.ragged", 1, 90, 101, 96, 136, 1, 1, 1, 0, 1), "f16"),
     (L("r.64x64.ragged", 1, 23, 29, 256, 72, 1, 1, 1, 0, 1), "f16"),
-    (L("r.tapmajor.c40.k264", 1, 25, 36, 40, 264, 1, 1, 1, 0, 1), "bf16"),
-    (L("r.tapmajor.cut", 1, 96, 170, 8, 576, 3, 3, 1, 1, 1), "f16"),
     (L("r.short.ragged", 1, 181, 185, 64, 200, 1, 1, 1, 0, 1), "f16"),
     (L("r.short.32.s2", 1, 511, 514, 32, 72, 1, 1, 2, 0, 1), "bf16"),
     (L("r.scalar.c23.k32", 2, 19, 23, 23, 32, 1, 1, 1, 0, 1), "bf16"),
     (L("r.scalar.c2.k5", 2, 19, 23, 2, 5, 3, 3, 1, 1, 1), "f16"),
+    # the tiles whose waves work half a step apart, ragged in rows and columns, and column ranges cut into two launches
+    (L("r.ring.128x128.k64", 2, 169, 203, 248, 80, 1, 1, 1, 0, 1), "bf16"),
+    (L("r.ring.256x128.k64", 2, 140, 135, 512, 72, 1, 1, 1, 0, 1), "f16"),
+    (L("r.ring.256x256", 1, 116, 166, 32, 392, 3, 3, 1, 2, 2), "bf16"),
+    (L("r.ring.cut.128x128", 1, 161, 96, 96, 264, 3, 3, 1, 1, 1), "f16"),
+    (L("r.ring.cut.256x256", 1, 142, 86, 32, 1312, 3, 3, 1, 2, 2), "bf16"),
+    (L("r.tapmajor.c40.k264", 1, 25, 36, 40, 264, 1, 1, 1, 0, 1), "bf16"),
+    (L("r.tapmajor.cut", 1, 96, 170, 8, 576, 3, 3, 1, 1, 1), "f16"),
 ]
 
 
@@ -189,7 +195,20 @@ KERNELS = {"e.scalar": "igemm_scalar_kernel", "r.scalar": "igemm_scalar_kernel",
            "e.logits": "thin_cols_kernel"}
 
 
+# ... and for these the whole plan: every launch with its tile and workgroups
+PLANS = {"r.128x128.ragged": "cmajor<128,128>[216]", "r.128x64.ragged": "cmajor.k64<128,64>[216]", "r.64x64.ragged": "cmajor.k64<64,64>[22]",
+         "e.dma.k304.c96.remainder": "cmajor<128,128>[1407]", "r.dma.k304.c96.remainder": "cmajor<128,128>[1407]",
+         "r.ring.128x128.k64": "cmajor.k64<128,128>[537]", "r.ring.256x128.k64": "cmajor.k64<256,128>[148]",
+         "r.ring.256x256": "cmajor<256,256>[152]", "r.ring.cut.128x128": "cmajor<128,128>[242]; cmajor<64,32>[242]",
+         "r.ring.cut.256x256": "cmajor<256,256>[240]; cmajor<64,64>[191]",
+         "r.tapmajor.cut": "tapmajor<128,128>[512]; tapmajor<64,64>[255]"}
+
+
 def test_cases_reach_the_kernels_they_are_named_for(api):
+    by_name = {layer.name: (layer, dtype) for layer, dtype in CASES + RESIDUAL_CASES}
+    for name, plan in PLANS.items():
+        text = api.dl_conv_describe(api.desc_from_layer(*by_name[name]), api.PASS_FWD)
+        assert text.replace("igemm_dma_kernel.", "") == plan, f"{name}: {text}"
     for layer, dtype in CASES + RESIDUAL_CASES:
         for prefix, kernel in KERNELS.items():
             if layer.name.startswith(prefix):

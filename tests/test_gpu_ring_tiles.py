@@ -73,6 +73,8 @@ CASES = [
     (L("bt.batch.128x64.k64", 1, 75, 250, 8, 64, 2, 2), "f16", DGRAD, "batch_kernel.bt.k64<128,64>"),
     (L("bt.batch.one-tile", 1, 5, 6, 40, 64, 3, 2), "f16", DGRAD, "batch_kernel.bt<64,64>"),
     (L("bt.batch.one-row", 1, 1, 131, 40, 64, 3, 2), "bf16", DGRAD, "batch_kernel.bt<64,64>"),
+    # 11 G multiply-adds
+    (L("bt.batch.large", 1, 185, 231, 256, 456, 3, 2), "f16", DGRAD, "batch_kernel.bt<"),
     # tap-major order (few channels): each tile, and a cut column range
     (L("tap.64x32", 1, 9, 13, 24, 24, 3), "f16", FWD, "tapmajor<64,32>"),
     (L("tap.64x64", 1, 25, 36, 40, 264, 1), "bf16", FWD, "tapmajor<64,64>"),
@@ -80,8 +82,16 @@ CASES = [
     (L("tap.128x128", 1, 179, 98, 8, 72, 1), "bf16", FWD, "tapmajor<128,128>"),
     (L("tap.256x256", 2, 66, 261, 56, 136, 3), "f16", FWD, "tapmajor<256,256>"),
     (L("tap.cut", 1, 96, 170, 8, 576, 3), "f16", FWD, "tapmajor<128,128>[512]; igemm_dma_kernel.tapmajor<64,64>[255]"),
-    # 11 G multiply-adds
-    (L("bt.batch.large", 1, 185, 231, 256, 456, 3, 2), "f16", DGRAD, "batch_kernel.bt<"),
+    # filter gradient: tiles of one shape with steps of the other depth, and read like dy (1x1, unit stride)
+    (L("w.128x128.32-pixels", 1, 95, 13, 1952, 144, 3, 2), "f16", WGRAD, "wgrad_dma_kernel<128,128>["),
+    (L("w.128x128.32-pixels.1x1", 1, 120, 285, 1328, 72, 1), "bf16", WGRAD, "wgrad_dma_kernel<128,128>.linear["),
+    (L("w.128x128.1x1", 1, 6, 54, 1216, 256, 1), "f16", WGRAD, "wgrad_dma_kernel<128,128>.k64.linear["),
+    (L("w.64x64.32-pixels", 2, 105, 2, 1048, 32, 3), "bf16", WGRAD, "wgrad_dma_kernel<64,64>["),
+    (L("w.64x64.64-pixels", 1, 24, 58, 1584, 40, 7, 2), "f16", WGRAD, "wgrad_dma_kernel<64,64>.k64["),
+    (L("w.128x256.1x1", 1, 158, 159, 672, 136, 1), "bf16", WGRAD, "wgrad_dma_kernel<128,256>.k64.linear["),
+    (L("w.256x256.1x1", 1, 101, 299, 1368, 144, 1), "f16", WGRAD, "wgrad_dma_kernel<256,256>.linear["),
+    # a stride-1 data gradient whose columns are cut: the offset into the reduction-major filter
+    (L("bt.cut", 2, 89, 175, 264, 240, 1), "f16", DGRAD, "bt<128,128>[488]; igemm_dma_kernel.bt.k64<128,64>[244]"),
 ]
 
 
