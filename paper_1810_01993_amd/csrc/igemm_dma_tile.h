@@ -6,10 +6,12 @@
 // each of which deposits 64 lanes x 16 bytes = 1 KB (16 tile rows of 32
 // reduction elements) contiguously in LDS.  Out-of-range offsets (zero
 // padding, ragged edges, steps past the end of the reduction) deposit zeros.
-// A ring of two to four LDS buffers keeps one to three reduction steps in
-// flight; one barrier per step.  Because the LDS image of a load is contiguous, bank
-// conflicts are avoided by swizzling which 16-byte slice of a row each lane
-// fetches instead of padding the row pitch.
+// A ring of three or four LDS buffers keeps one or two reduction steps in
+// flight beyond the one awaited (the one-step kernel, igemm_short.hip, has no
+// ring); one barrier per step, two where groups of waves work half a step apart.
+// Because the LDS image of a load is contiguous, bank conflicts are avoided by
+// swizzling which 16-byte slice of a row each lane fetches instead of padding
+// the row pitch.
 //
 // Two reduction orders:
 //   tap-major      kk = (tap*Cin + c) runs linearly; a 32-deep step may
@@ -54,7 +56,7 @@ typedef short bt_s16x4_t __attribute__((ext_vector_type(4)));
 // range `split` of a split reduction.
 // KB: reduction elements of a step.  SHORT: the whole reduction is one step (STAGES == 1, no ring).
 // RES: the residual input is there, aligned for 16-byte loads, and fetched into registers before the first step.
-// PP: two groups of waves half a step apart (four ring slots or three of 64 channels).
+// PP: two groups of waves half a step apart.
 template <class T, int BM, int BN, int WM, int WN, bool CMAJOR, bool BT, int KB = 32, int STAGES = 4, bool SHORT = false, bool RES = false, bool PP = false>
 __device__ __forceinline__ void igemm_dma_tile(const IgemmArgs &p, const int tile, const int split)
 {
@@ -317,8 +319,8 @@ __device__ __forceinline__ void igemm_dma_tile(const IgemmArgs &p, const int til
 
     // The residual's rows of this wave's tile, 16 bytes per lane the way the output is written.  Fetched here, ahead of
     // the first step's loads (and so awaited with them): in the epilogue every 32-row slab waited for its own round trip
-    // (6912 pixels, 256 -> 1024 17.6 -> 16.4 us, 3015 pixels 10.4 -> 9.8 us).  Only for tiles of up to 128 x 128, whose
-    // residual takes at most 32 registers.
+    // (6912 pixels, 256 -> 1024 17.6 -> 16.4 us, 3015 pixels 10.4 -> 9.8 us).  Only for tiles of at most 128 columns, whose
+    // residual takes at most 32 registers (256 x 256: 64).
     constexpr int CH = TN * 32;                          // channels per wave
     constexpr int LPR = CH / 8;                          // lanes per row when writing out
     const bool dense = (p.osh == 1 && p.osw == 1 && p.FH == p.OH && p.FW == p.OW);
