@@ -182,9 +182,11 @@ static bool tile_considered(const IgemmArgs &a, int tile)
 
 // Tap-major order (few channels): 32-deep steps across the taps, and waves that spend longer on an address.  Constants of their
 // own, fitted to 7500 random layers (forward, 50..800000 pixels, 8..120 x 8..1040 channels, 1x1 to 7x7; fp16) timed with every
-// tile: 1.0 % behind the best of each on average, 1.43x at worst (rounds counted in halves while all tiles are resident: 270 tiles on
-// 256 compute units take less than twice as long as 256).  Tiles wider than the columns are left out, and the largest
-// for short reductions, whose epilogue nothing covers (147000 pixels, 120 -> 256, 1x1: 45 us, 128 x 128 30).
+// tile: 0.4 % behind the best of each on average, 1.3x at worst.  While all tiles are resident, rounds count in halves, those of
+// 64 x 64 tiles up to the second in quarters: 260 of them on 256 compute units take 1.3x as long as 256, not twice (2 x 50 x 71,
+// 120 -> 528, 7x7, stride 2: 35.5 us; 135 tiles of 128 x 64, which an estimate in halves preferred, 52.3), 530 take 2.5x (1 x 177
+// x 192, 56 -> 64, 7x7: 36.0 us; 128 x 64 27.4).  Tiles wider than the columns are left out, and the largest for short
+// reductions, whose epilogue nothing covers (147000 pixels, 120 -> 256, 1x1: 45 us, 128 x 128 30).
 struct TapMajorTile { int tile, bm, bn, per_cu; TileCost cost; };
 static const TapMajorTile TAP_MAJOR_TILES[] = {{TILE_64x32, 64, 32, 6, {3.75, 0.113, 0.22}},
                                                {TILE_64x64, 64, 64, 4, {3.36, 0.129, 0.51}},
@@ -210,7 +212,8 @@ static int best_tap_major_tile(const IgemmArgs &a, double *us)
     for (const TapMajorTile &t : TAP_MAJOR_TILES) {
         if ((t.tile == TILE_64x32) != (a.Nout <= 32) || (t.bn >= 128 && a.Nout <= 64) || (t.bn == 256 && (a.Nout <= 128 || steps < 16))) continue;
         const int64_t tiles = ((M + t.bm - 1) / t.bm) * ((a.Nout + t.bn - 1) / t.bn);
-        const double load = tiles <= 256 * t.per_cu ? std::max(1.0, std::ceil(tiles / 128.0) / 2) : tiles_per_cu(t.per_cu, tiles);
+        const int parts = t.tile == TILE_64x64 && tiles <= 512 ? 4 : 2;
+        const double load = tiles <= 256 * t.per_cu ? std::max(1.0, std::ceil(tiles * parts / 256.0) / parts) : tiles_per_cu(t.per_cu, tiles);
         const double est = t.cost.t0 + (steps * t.cost.step + t.cost.fix) * load;
         if (best < 0 || est < *us) { best = t.tile; *us = est; }
     }

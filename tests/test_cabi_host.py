@@ -97,6 +97,14 @@ def test_tap_major_column_ranges(api, N, H, W, C, K, R, launches):
     assert text.count("igemm_dma_kernel.tapmajor") == launches and text.count("kernel") == launches, text
 
 
+@pytest.mark.parametrize("N,H,W,C,K,R,stride,tiles", [(2, 50, 71, 120, 528, 7, 2, "<64,64>[261]"), (1, 42, 59, 120, 400, 7, 1, "<64,64>[273]"),
+                                                      (1, 177, 192, 56, 64, 7, 1, "<128,64>[266]"), (1, 198, 66, 24, 80, 3, 1, "<128,64>[206]")])
+def test_tap_major_tiles_a_little_beyond_a_round(api, N, H, W, C, K, R, stride, tiles):
+    """260 tiles of 64 x 64 take 1.3 rounds' time, not 1.5: half as many larger ones are slower; 530 take 2.5."""
+    text = api.dl_conv_describe(api.ConvDesc(N, H, W, C, K, R, R, stride, stride, R // 2, R // 2, 1, 1, api.DL_F16), api.PASS_FWD)
+    assert text == "igemm_dma_kernel.tapmajor" + tiles, text
+
+
 @pytest.mark.parametrize("N,H,W,C,K,R,dil,which", [(2, 141, 179, 96, 192, 5, 1, 0), (1, 230, 250, 32, 192, 3, 2, 0), (2, 147, 160, 256, 304, 5, 1, 0),
                                                    (1, 182, 263, 256, 128, 3, 2, 1), (223, 20, 22, 512, 320, 3, 3, 0)])
 def test_dilated_and_5x5_layers_of_one_round_of_patches(api, N, H, W, C, K, R, dil, which):

@@ -78,7 +78,7 @@ CASES = [
     # tap-major order (few channels): each tile, and a cut column range
     (L("tap.64x32", 1, 9, 13, 24, 24, 3), "f16", FWD, "tapmajor<64,32>"),
     (L("tap.64x64", 1, 25, 36, 40, 264, 1), "bf16", FWD, "tapmajor<64,64>"),
-    (L("tap.128x64", 1, 198, 66, 8, 80, 1), "f16", FWD, "tapmajor<128,64>"),
+    (L("tap.128x64", 1, 198, 66, 24, 80, 3), "f16", FWD, "tapmajor<128,64>"),
     (L("tap.128x128", 1, 179, 98, 8, 72, 1), "bf16", FWD, "tapmajor<128,128>"),
     (L("tap.256x256", 2, 66, 261, 56, 136, 3), "f16", FWD, "tapmajor<256,256>"),
     (L("tap.cut", 1, 96, 170, 8, 576, 3), "f16", FWD, "tapmajor<128,128>[512]; igemm_dma_kernel.tapmajor<64,64>[255]"),
