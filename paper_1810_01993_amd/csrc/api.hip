@@ -138,10 +138,18 @@ dlk::IgemmArgs fwd_args(const dl_conv_desc *d, const Geometry &g)
     return a;
 }
 
-// The stem's forward kernel (no residual input there).
-bool use_stem_fwd(const dl_conv_desc *d)
+// 16 x 16 output patches of a layer, the unit of the stem's kernels.
+int64_t stem_patches(const dl_conv_desc *d, const Geometry &g) { return (int64_t)d->N * ((g.P + 15) / 16) * ((g.Q + 15) / 16); }
+
+// The stem's forward kernel (no residual input there).  One patch per compute unit is always worth it; every further round costs
+// 2.3..5.8 us however little of its patches is inside the image, the plain engine 0.09..0.16 us per thousand pixels, so many
+// maps that are narrow or small stay with that one: 306 x 1 x 566, 16 -> 16: 63.8 us, 13.8 there (4800 random layers; filled
+// patches, 65000 pixels a round, are never among them).
+bool use_stem_fwd(const dl_conv_desc *d, const Geometry &g)
 {
-    return dlk::stem_fwd_applicable(d->C, d->K, d->R, d->S, d->stride_h, d->stride_w, d->pad_h, d->pad_w, d->dil_h, d->dil_w);
+    if (!dlk::stem_fwd_applicable(d->C, d->K, d->R, d->S, d->stride_h, d->stride_w, d->pad_h, d->pad_w, d->dil_h, d->dil_w)) return false;
+    const int64_t round_pixels = d->C == 8 ? (d->K > 32 ? 33000 : 22000) : d->K > 32 ? 45000 : 33000;
+    return (int64_t)d->N * g.P * g.Q >= round_pixels * ((stem_patches(d, g) - 1) / 256);
 }
 
 // Whether the forward pass of d gains from the channel-padded copies, on which it is the GEMM a of the layer e.  The lines
@@ -150,7 +158,7 @@ bool fwd_copies_pay(const dl_conv_desc *d, const dl_conv_desc *e, const dlk::Ige
 {
     const int64_t taps = (int64_t)d->R * d->S, red = taps * d->C;
     // the stem's kernel: 361 x 577 x 6 -> 64, batch 2: 56 us without the copies, 21 with them; one channel left as it was
-    if (use_stem_fwd(e) && !a.resid) return d->C > 1;
+    if (use_stem_fwd(e, Geometry{a.OH, a.OW, 0, 0, 0}) && !a.resid) return d->C > 1;
     if (red <= 24) return false;                         // 60 x 90 x 17 -> 64, 1x1: 9.1 us, 9.9 through the copy
     const int64_t steps = (red + 31) / 32;               // of the element-wise kernel
     const int64_t strides = (int64_t)d->stride_h * d->stride_w;
@@ -270,6 +278,23 @@ bool use_wgrad_stem(const dl_conv_desc *d, const Geometry &g)
     return dlk::wgrad_stem_applicable(d->C, d->K, d->R, d->S, d->stride_h, d->stride_w, d->pad_h, d->pad_w, d->dil_h, d->dil_w);
 }
 
+// Patches that lie mostly outside narrow or small maps: the stem's filter gradient multiplies all of each, and writes a slice of
+// partial sums per patch up to 256.  Both kernels' times as fitted to 4100 random layers (us; the general one's is its planner's estimate with
+// its deviation on this filter): 188 x 2 x 56, 16 -> 40: 27.0 us, 13.4 on the general kernel.
+bool stem_patches_filled(const dl_conv_desc *d, const Geometry &g)
+{
+    const int64_t patches = stem_patches(d, g);
+    return patches <= 2 || (int64_t)d->N * g.P * g.Q >= patches * (d->C == 8 ? 96 : 192);
+}
+
+bool wgrad_stem_pays(const dl_conv_desc *d, const Geometry &g, int splits, const dlk::WgradPlan &general)
+{
+    if (general.cfg < 0) return true;
+    const int64_t patches = stem_patches(d, g);
+    const double run = (double)((patches + splits - 1) / splits), sums = 1e-6 * splits * g.w_elems;
+    return d->C == 8 ? 6.4 + 2.1 * run + 2.8 * sums <= 1.14 * general.us - 4.3 : 8.25 + 2.85 * run + 2.0 * sums <= 1.07 * general.us - 3.6;
+}
+
 // Plan of the kernels that serve any layer, for a workspace of `room` bytes.  A caller that brings fewer bytes than the
 // preferred plan takes (say, the size that an earlier version of the library asked for) gets as many slices as they hold, down
 // to *least.
@@ -291,18 +316,22 @@ dlk::WgradPlan wgrad_plan(const dl_conv_desc *d, const Geometry &g, size_t room 
 {
     if (use_wgrad5x5(d)) {
         const dlk::WgradStripPlan p5 = dlk::wgrad5x5_make_plan(d->N, d->H, d->W, d->C, d->K);
-        return dlk::WgradPlan{-4, p5.slices, 0};
+        return dlk::WgradPlan{-4, p5.slices, 0, 0, 0};
     }
     if (use_wgrad3x3(d)) {
         const dlk::WgradStripPlan p3 = dlk::wgrad3x3_make_plan(d->N, d->H, d->W, d->C, d->K);
-        return dlk::WgradPlan{-3, p3.slices, 0};
+        return dlk::WgradPlan{-3, p3.slices, 0, 0, 0};
     }
-    if (use_wgrad_stem(d, g)) {
-        const int splits = dlk::wgrad_stem_splits(d->N, d->K, g.P, g.Q);
-        if (splits * (size_t)g.w_elems * sizeof(float) <= room) return dlk::WgradPlan{-5, splits, 0, 0};
-    }
+    const bool stem = use_wgrad_stem(d, g);
+    const int splits = stem ? dlk::wgrad_stem_splits(d->N, d->K, g.P, g.Q) : 0;
+    const size_t slice = (size_t)g.w_elems * sizeof(float);
+    const dlk::WgradPlan stem_plan{-5, splits, 0, 0, 0};
+    if (stem && splits * slice <= room && stem_patches_filled(d, g)) return stem_plan;
     int least;
-    return wgrad_general_plan(d, g, room, &least);
+    const dlk::WgradPlan general = wgrad_general_plan(d, g, room, &least);
+    // (the stem's also where there is room for its slices alone)
+    if (stem && splits * slice <= room && (wgrad_stem_pays(d, g, splits, general) || general.splits * slice > room)) return stem_plan;
+    return general;
 }
 
 size_t wgrad_own_workspace(const dl_conv_desc *d, const Geometry &g, size_t room = SIZE_MAX)
@@ -318,6 +347,7 @@ size_t wgrad_least_workspace(const dl_conv_desc *d, const Geometry &g)
     if (best.cfg >= 0 || best.cfg == -5) {
         wgrad_general_plan(d, g, 0, &least);
         least = std::min(least, best.splits);
+        if (use_wgrad_stem(d, g)) least = std::min(least, dlk::wgrad_stem_splits(d->N, d->K, g.P, g.Q));
     }
     return (size_t)least * (size_t)g.w_elems * sizeof(float);
 }
@@ -482,7 +512,7 @@ dl_status run_fwd(const dl_conv_desc *d, const void *x, const void *w, const flo
     const size_t need = igemm_scratch_bytes(a, true);
     if (need > 0 && (!workspace || workspace_bytes < need)) return DL_ERR_WORKSPACE;
     if (need > 0 && !aligned16(workspace)) return DL_ERR_ALIGN;
-    if (!residual && use_stem_fwd(d)) {
+    if (!residual && use_stem_fwd(d, g)) {
         dlk::StemFwdArgs f{};
         f.x = static_cast<const uint16_t *>(x);
         f.w = static_cast<const uint16_t *>(w);

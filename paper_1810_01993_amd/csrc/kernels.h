@@ -264,6 +264,7 @@ struct WgradPlan {
     int splits;
     int chunk;                  // pixels per slice, multiple of 32
     int spread;                 // see WgradArgs
+    double us;                  // estimated time (direct-to-LDS kernel, else 0)
 };
 // max_splits: the most slices there is room for (one is always planned for)
 WgradPlan wgrad_make_plan(int64_t npix, int64_t x_elems, int K, int C, int RSC, bool thin_ok, bool fetch_term, int64_t max_splits);

@@ -293,7 +293,7 @@ static const WgradTile WGRAD_TILES[] = {
 WgradPlan wgrad_make_plan(int64_t npix, int64_t x_elems, int K, int C, int RSC, bool thin_ok, bool fetch_term, int64_t max_splits)
 {
     static const int forced = tuning_knob("DLCONV_WGRAD_CFG", -2); // tuning override, unset in normal use
-    WgradPlan pl{-1, 1, 32, 0};
+    WgradPlan pl{-1, 1, 32, 0, 0};
     if (thin_ok && forced != -1) {
         // streaming kernel: one workgroup per slice of pixels, about eight slices per CU
         int64_t s = (npix + 255) / 256;
@@ -366,14 +366,14 @@ WgradPlan wgrad_make_plan(int64_t npix, int64_t x_elems, int K, int C, int RSC, 
             const double est = sh.t0 + steps_us + reduce_us;
             if (est < best) {
                 best = est;
-                pl = WgradPlan{cfg, c.splits, c.chunk, c.spread ? 1 : 0};
+                pl = WgradPlan{cfg, c.splits, c.chunk, c.spread ? 1 : 0, est};
                 pl_steps = steps_us;
             }
             if (large) {
                 const double fetch_est = sh.t0 + std::max(steps_us, c.spread ? fetch_us : 0.0) + reduce_us;
                 if (fetch_est < best_local) {
                     best_local = fetch_est;
-                    local = WgradPlan{cfg, c.splits, c.chunk, c.spread ? 1 : 0};
+                    local = WgradPlan{cfg, c.splits, c.chunk, c.spread ? 1 : 0, fetch_est};
                 }
             }
         }

@@ -120,6 +120,16 @@ def test_stem_filter_gradient_of_a_few_pixels(api):
         assert kernel in api.dl_conv_describe(api.ConvDesc(N, H, W, C, K, 7, 7, 2, 2, 3, 3, 1, 1, api.DL_F16), api.PASS_BWD_FILTER)
 
 
+def test_stem_kernels_leave_narrow_maps_to_the_general_ones(api):
+    """Many images whose 16 x 16 patches lie mostly outside: the general kernels; filled patches, or one per compute unit: the stem's."""
+    for N, H, W, C, K, fwd, wgrad in ((306, 1, 566, 16, 16, "igemm_dma", "wgrad_stem"), (188, 2, 56, 16, 40, "igemm_dma", "wgrad_dma"),
+                                      (299, 256, 1, 8, 40, "igemm_dma", "wgrad_dma"), (60, 30, 30, 8, 64, "stem_fwd", "wgrad_stem"),
+                                      (2, 768, 1152, 16, 64, "stem_fwd", "wgrad_stem"), (2, 361, 577, 8, 64, "stem_fwd", "wgrad_stem")):
+        d = api.ConvDesc(N, H, W, C, K, 7, 7, 2, 2, 3, 3, 1, 1, api.DL_F16)
+        assert fwd in api.dl_conv_describe(d, api.PASS_FWD) and wgrad in api.dl_conv_describe(d, api.PASS_BWD_FILTER)
+        assert api.dl_conv_least_workspace_bytes(d, api.PASS_BWD_FILTER) <= api.dl_conv_workspace_bytes(d, api.PASS_BWD_FILTER)
+
+
 def test_wrapper_takes_the_least_workspace_when_memory_is_short(api, monkeypatch):
     torch = api.torch
     big = api.ConvDesc(2, 768, 1152, 300, 256, 3, 3, 1, 1, 1, 1, 1, 1, api.DL_F16)

@@ -67,6 +67,9 @@ CASES = [
     (L("stem.w.c16.k24", 1, 64, 96, 16, 24, 7, 2), "f16", WGRAD, "wgrad_stem_kernel<16>"),
     (L("stem.w.c8.k40", 1, 33, 130, 8, 40, 7, 2), "bf16", WGRAD, "wgrad_stem_kernel<8>"),
     (L("stem.w.c8.k8.pixel", 1, 1, 1, 8, 8, 7, 2), "f16", WGRAD, "wgrad_stem_kernel<8>"),
+    (L("stem.narrow.c16.k40", 290, 2, 31, 16, 40, 7, 2), "f16", FWD, "igemm_dma_kernel"),
+    (L("stem.w.narrow.c16.k40", 188, 2, 56, 16, 40, 7, 2), "bf16", WGRAD, "wgrad_dma_kernel"),
+    (L("stem.w.narrow.c8.k32", 130, 71, 1, 8, 32, 7, 2), "f16", WGRAD, "wgrad_dma_kernel"),
     (L("stem.w.many", 1, 400, 570, 16, 32, 7, 2), "f16", WGRAD, "wgrad_stem_kernel<16>"),
     # parity classes in one launch, tiles not a multiple of the eight XCDs: three taps or fewer each, one tile, two classes
     (L("bt.batch.64x64", 1, 41, 67, 40, 64, 3, 2), "bf16", DGRAD, "batch_kernel.bt<64,64>"),
